@@ -91,16 +91,24 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(const uint4 &u)
     return c.v;
 }
 
-// The eight 4-bit codes of a word (code j in bits 4j..4j+3) as exact bf16 numbers, in matrix-core
-// operand order: bytes of nibbles, byte -> float, then the upper halves of two floats side by side.
+// The eight 4-bit codes of a word (code j in bits 4j..4j+3) as exact bf16 numbers, in matrix-core operand
+// order.  A byte 0..15 read as an fp8 (e4m3) number is exactly code * 2^-9: the codes below 8 are its subnormals,
+// the others its first binade.  So the gfx950 conversion of two fp8 numbers to bf16 with a scale of 2^9 yields two
+// codes per instruction: nibbles to bytes in column order (5 instructions) and four conversions, against 15
+// instructions by way of float (checked on the device for every pair of codes: identical bits).  4-bit 3B shape:
+// 2.136 -> 2.092 ms per step at 16 rows, 700-token prefill 38.5 -> 37.5 ms.
 __device__ __forceinline__ uint4 q4_codes_bf16(uint32_t w)
 {
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
     const uint32_t ev = w & 0x0F0F0F0Fu, od = (w >> 4) & 0x0F0F0F0Fu;
+    const uint32_t lo = __builtin_amdgcn_perm(od, ev, 0x05010400u);   // columns 0, 1, 2, 3
+    const uint32_t hi = __builtin_amdgcn_perm(od, ev, 0x07030602u);   // columns 4, 5, 6, 7
+    const bf16x2_t c[4] = {__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.f, false),
+                           __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.f, true),
+                           __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.f, false),
+                           __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.f, true)};
     uint4 r;
-    r.x = __builtin_amdgcn_perm(__float_as_uint((float)(od & 0xFFu)), __float_as_uint((float)(ev & 0xFFu)), 0x07060302u);
-    r.y = __builtin_amdgcn_perm(__float_as_uint((float)((od >> 8) & 0xFFu)), __float_as_uint((float)((ev >> 8) & 0xFFu)), 0x07060302u);
-    r.z = __builtin_amdgcn_perm(__float_as_uint((float)((od >> 16) & 0xFFu)), __float_as_uint((float)((ev >> 16) & 0xFFu)), 0x07060302u);
-    r.w = __builtin_amdgcn_perm(__float_as_uint((float)(od >> 24)), __float_as_uint((float)(ev >> 24)), 0x07060302u);
+    __builtin_memcpy(&r, c, 16);
     return r;
 }
 
