@@ -81,14 +81,21 @@ struct SampleArgs {
 };
 
 // The digit (0..15) of a finished pass: the largest candidate whose total over all blocks,
-// added in block order, still reaches `need`.  Called by every thread of the block.
-__device__ __forceinline__ uint32_t settle_digit(const float *part, float need, float *sm /*[16]*/)
+// added in block order, still reaches `need`.  Called by every thread of the block.  The 64 x 16
+// partial totals come in one 16-byte load per thread and are added from LDS: as a loop of loads
+// in the 15 adding threads they were a chain of cache round trips.
+__device__ __forceinline__ uint32_t settle_digit(const float *part, float need, float *sm /*[16]*/, float *tot /*[1024]*/)
 {
+    static_assert(kSampleBlocks * 16 == kSampleThreads * 4, "four partial totals per thread");
     const int tid = threadIdx.x;
+    const float4 mine = ldf4(part + 4 * tid);
+    __syncthreads();
+    *reinterpret_cast<float4 *>(tot + 4 * tid) = mine;
     __syncthreads();
     if (tid < 15) {
         float t = 0.f;
-        for (int g = 0; g < kSampleBlocks; g++) t += part[g * 16 + tid];
+#pragma unroll
+        for (int g = 0; g < kSampleBlocks; g++) t += tot[g * 16 + tid];
         sm[tid] = t;
     }
     __syncthreads();
@@ -548,7 +555,8 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
 {
     __shared__ float sm[16];
     __shared__ float red[4 * 15];
-    __shared__ float scan[kSampleThreads];
+    __shared__ __align__(16) float scan[kSampleThreads];
+    __shared__ __align__(16) float tot[kSampleBlocks * 16];
     __shared__ int sm_i[12];
     const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
     const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
@@ -600,6 +608,22 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     }
 
     // ---- the threshold searches ------------------------------------------------------------
+    // What bounds a launch here is its chain of round trips, not its bytes.  A slice of at most
+    // kSampleSliceMax weights is therefore requested whole, before the digit of the pass before is
+    // settled: into registers, from clamped addresses, 16 loads in flight per thread (SAMPLE_PASS:
+    // element tid + 256 j; SAMPLE_KEEP: the thread's contiguous piece).  Same order of additions as
+    // the loops that larger slices take.  With the totals of settle_digit: 16 rows of 151936, top-p alone, 88.3 ->
+    // 84.7 us a call; with a top-k of 100 in front 156 -> 147.
+    constexpr int NREG = kSampleSliceMax / kSampleThreads;
+    const bool in_regs = slice <= kSampleSliceMax;
+    const int piece = (slice + kSampleThreads - 1) / kSampleThreads;
+    const int j0 = min(i0 + tid * piece, i1), j1 = min(j0 + piece, i1);
+    float pv[NREG];
+    if (in_regs && a.stage != SAMPLE_MASS) {
+        const int first = a.stage == SAMPLE_PASS ? i0 + tid : j0, step = a.stage == SAMPLE_PASS ? kSampleThreads : 1;
+#pragma unroll
+        for (int j = 0; j < NREG; j++) pv[j] = p[min(first + j * step, V - 1)];
+    }
     SampleState st = a.st_in[b];
     if (a.stage == SAMPLE_PASS && a.first) {
         // a new search: top-k counts every weight; top-p only the candidates of top-k (the
@@ -610,14 +634,17 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
             st.floor_bits = 0;
         }
         if (a.need_from_mass) {
+            if (tid < kSampleBlocks) tot[tid] = part_in[tid * 16];
+            __syncthreads();
             float z = 0.f;
-            for (int k = 0; k < kSampleBlocks; k++) z += part_in[k * 16];
+#pragma unroll
+            for (int k = 0; k < kSampleBlocks; k++) z += tot[k];
             st.need = a.top_p * z;
         }
     } else if (a.stage == SAMPLE_PASS || a.settle) {
         // the digit of the pass before (its position: 4 bits above this pass's, or bit 0)
         const int prev_shift = (a.stage == SAMPLE_PASS) ? a.shift + 4 : 0;
-        st.prefix |= settle_digit(part_in, st.need, sm) << prev_shift;
+        st.prefix |= settle_digit(part_in, st.need, sm, tot) << prev_shift;
     }
     const float floor_t = __uint_as_float(st.floor_bits);
 
@@ -625,13 +652,20 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
         float acc[15];
 #pragma unroll
         for (int d = 0; d < 15; d++) acc[d] = 0.f;
-        for (int i = i0 + tid; i < i1; i += kSampleThreads) {
-            const float v = p[i];
+        auto add = [&](float v) {
             const float w = (v >= floor_t) ? (a.count ? 1.f : v) : 0.f;
             const uint32_t bits = __float_as_uint(v);
 #pragma unroll
             for (int d = 0; d < 15; d++)
                 acc[d] += (bits >= (st.prefix | ((uint32_t)(d + 1) << a.shift))) ? w : 0.f;
+        };
+        if (in_regs) {
+#pragma unroll
+            for (int j = 0; j < NREG; j++)
+                if (i0 + j * kSampleThreads < i1)     // uniform; an element past the slice adds nothing (-1 is below every floor)
+                    add(i0 + tid + j * kSampleThreads < i1 ? pv[j] : -1.f);
+        } else {
+            for (int i = i0 + tid; i < i1; i += kSampleThreads) add(p[i]);
         }
 #pragma unroll
         for (int d = 0; d < 15; d++) acc[d] = sum64(acc[d]);
@@ -660,15 +694,22 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     const uint32_t tau_bits = max(st.prefix, st.floor_bits);
     const float tau = __uint_as_float(tau_bits);
     {
-        const int piece = (slice + kSampleThreads - 1) / kSampleThreads;
-        const int j0 = min(i0 + tid * piece, i1), j1 = min(j0 + piece, i1);
         float mine = 0.f;
-        for (int i = j0; i < j1; i++) mine += (p[i] >= tau) ? p[i] : 0.f;
+        if (in_regs) {
+#pragma unroll
+            for (int j = 0; j < NREG; j++) mine += (j0 + j < j1 && pv[j] >= tau) ? pv[j] : 0.f;
+        } else {
+            for (int i = j0; i < j1; i++) mine += (p[i] >= tau) ? p[i] : 0.f;
+        }
         scan[tid] = mine;
         __syncthreads();
         if (tid == 0) {
             float t = 0.f;
-            for (int k = 0; k < kSampleThreads; k++) t += scan[k];
+#pragma unroll 16
+            for (int k = 0; k < kSampleThreads; k += 4) {
+                const float4 v = ldf4(scan + k);
+                t += v.x; t += v.y; t += v.z; t += v.w;
+            }
             part_out[0] = t;
             if (g == 0) a.st_out[b] = SampleState{tau_bits, 0.f, 0u, 0u};
         }
