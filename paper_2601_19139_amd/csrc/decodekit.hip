@@ -386,7 +386,18 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
 // Rows per block tile.  Small matrices (a few MB, one or two loads per lane)
 // are latency-bound: two rows per block spread them over every compute unit.
 // Large ones (lm_head) stream better with eight rows per block.
-inline bool gemv_small(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2 < (64u << 20); }
+// With two to four batch rows the activations are the larger stream: a thread fetches 32 bytes of x per
+// batch row for every 16 bytes of a weight row, from the caches, once per RB rows.  Matrices of 16..64 MB, which
+// have rows enough to fill the chip in any case, therefore take four rows per block then; and from 16 MB on a K of
+// up to 4096 is walked by 128 threads instead of 256 (K = 3072 is three whole strides instead of one and a half).
+// Per step, before -> after: 3B shape (19..50 MB a matrix) 2 rows 2051 -> 1924 us, 3 rows 2680 -> 2180, 4 rows
+// 3119 -> 2790; 8B shape (33 MB and up) 4 rows 5736 -> 5397, 2 rows 3959 -> 3944.  The 0.6B shape (4..6 MB) loses
+// with four rows per block (3 rows 1034 -> 1071 us, with 128 threads as well 1123) and stays below the line.
+inline size_t gemv_bytes(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2; }
+inline bool gemv_small(const dk::GemvArgs &a) { return gemv_bytes(a) < (64u << 20); }
+inline bool gemv_several(const dk::GemvArgs &a, int nb) { return nb >= 2 && gemv_bytes(a) >= (16u << 20); }
+// the lm_head's grid is fixed by its table of running maxima
+inline bool gemv_mid(const dk::GemvArgs &a, int nb) { return gemv_several(a, nb) && gemv_small(a) && a.pmax_val == nullptr; }
 template <int EPI>
 inline int gemv_rows_per_tile(const dk::GemvArgs &a)
 {
@@ -397,7 +408,7 @@ template <int NB, int RB, int EPI, bool NORM, bool XATTN>
 dk_status launch_gemv_rb(const dk::GemvArgs &a, hipStream_t st)
 {
     const int grid = (a.N + RB * a.tiles - 1) / (RB * a.tiles);
-    if (a.K >= 2048)
+    if (a.K >= 2048 && !(a.K <= 4096 && gemv_several(a, NB)))
         DK_LAUNCH(DK_K_GEMV, (dk::gemv_kernel<NB, 256, RB, EPI, NORM, XATTN>), dim3(grid), dim3(256), 0, st, a);
     else if (a.K >= 1024)
         DK_LAUNCH(DK_K_GEMV, (dk::gemv_kernel<NB, 128, RB, EPI, NORM, XATTN>), dim3(grid), dim3(128), 0, st, a);
@@ -410,6 +421,8 @@ dk_status launch_gemv_rb(const dk::GemvArgs &a, hipStream_t st)
 template <int NB, int EPI, bool NORM, bool XATTN = false>
 dk_status launch_gemv_nb(const dk::GemvArgs &a, hipStream_t st)
 {
+    if constexpr (NB >= 2)
+        if (gemv_mid(a, NB)) return launch_gemv_rb<NB, 4, EPI, NORM, XATTN>(a, st);
     if (gemv_small(a)) return launch_gemv_rb<NB, 2, EPI, NORM, XATTN>(a, st);
     return launch_gemv_rb<NB, (EPI == dk::EPI_SWIGLU ? 4 : 8), EPI, NORM, XATTN>(a, st);
 }

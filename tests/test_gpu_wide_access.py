@@ -4,6 +4,7 @@ import pytest
 
 import workloads as W
 from workloads.blocktable import build_block_tables
+from gpu_common import run_both, check_parity, check_pool
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +20,12 @@ def dk():
     import paper_2601_19139_amd as dk
     dk.lib()
     return dk
+
+
+@pytest.fixture(scope="module")
+def orc():
+    from oracle import oracle_f64
+    return oracle_f64()
 
 
 @pytest.mark.parametrize("batch", [5, 17, 64])
@@ -45,3 +52,19 @@ def test_logits_at_any_float_address(dk, batch, vocab, shift):
     assert bool((flat[:shift] == 7.5).all()) and bool((flat[shift + batch * vocab:] == 7.5).all())
     dkv.close()
     dm.close()
+
+
+@pytest.mark.parametrize("batch", [2, 3, 4])
+@pytest.mark.parametrize("hidden,ffn", [(3072, 3072), (3000, 2800), (2048, 4104)])
+def test_few_rows_on_matrices_around_the_line(dk, orc, batch, hidden, ffn):
+    """Two to four rows of matrices just above and just below 16 MB, K a multiple of the 128 threads' stride or not:
+    four weight rows per block above the line, two below.  Bound: that of the other dense parity tests."""
+    shape = variant("tiny", n_layers=1, hidden=hidden, n_q_heads=24, n_kv_heads=8, head_dim=128, ffn=ffn, vocab=2003,
+                    rope_theta=1e6)
+    lay = build_block_tables([40 + 31 * i for i in range(batch)], 16, 2, seed=7)
+    pool = W.fill_kv_pool(shape, lay, 8)
+    out = run_both(orc, shape, W.make_weights(shape, 9), lay, pool, W.initial_tokens(shape, batch, 10), 2,
+                   gpu_flags=dk.STEP_NO_FUSED)
+    worst, agree = check_parity(out)
+    check_pool(out, pool, shape, lay, 2)
+    assert worst < 2e-4 and agree == 1.0
