@@ -390,8 +390,8 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
 // batch row for every 16 bytes of a weight row, from the caches, once per RB rows.  Matrices of 16..64 MB, which
 // have rows enough to fill the chip in any case, therefore take four rows per block then; and from 16 MB on a K of
 // up to 4096 is walked by 128 threads instead of 256 (K = 3072 is three whole strides instead of one and a half).
-// Per step, before -> after: 3B shape (19..50 MB a matrix) 2 rows 2051 -> 1924 us, 3 rows 2680 -> 2180, 4 rows
-// 3119 -> 2790; 8B shape (33 MB and up) 4 rows 5736 -> 5397, 2 rows 3959 -> 3944.  The 0.6B shape (4..6 MB) loses
+// Per step, before -> after: 3B shape (19..50 MB a matrix) 2 rows 2051 -> 1985 us, 3 rows 2680 -> 2178, 4 rows
+// 3119 -> 2782; 8B shape (33 MB and up) 4 rows 5736 -> 5376, 2 rows 3959 -> 3944.  The 0.6B shape (4..6 MB) loses
 // with four rows per block (3 rows 1034 -> 1071 us, with 128 threads as well 1123) and stays below the line.
 inline size_t gemv_bytes(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2; }
 inline bool gemv_small(const dk::GemvArgs &a) { return gemv_bytes(a) < (64u << 20); }
