@@ -81,21 +81,22 @@ struct SampleArgs {
 };
 
 // The digit (0..15) of a finished pass: the largest candidate whose total over all blocks,
-// added in block order, still reaches `need`.  Called by every thread of the block.  The 64 x 16
-// partial totals come in one 16-byte load per thread and are added from LDS: as a loop of loads
-// in the 15 adding threads they were a chain of cache round trips.
-__device__ __forceinline__ uint32_t settle_digit(const float *part, float need, float *sm /*[16]*/, float *tot /*[1024]*/)
+// added in block order, still reaches `need`.  Called by every thread of the block.  A candidate's
+// 64 partial totals are requested together and then added: with the requests inside the adding loop
+// a settle is a few round trips instead of one.  Top-p alone, a call of 12 launches, adding loop -> this, together
+// with the same change where the mass and the kept mass are added up: one row of 1000 weights 50.0 -> 42.0 us,
+// 64 rows of 1000 111.9 -> 101.6, 64 rows of 151936 217.6 -> 201.1.  Bringing the totals in by all threads and
+// adding them from LDS costs two more barriers and an LDS pass: 43.0, 110.0 and 206.4 us.
+__device__ __forceinline__ uint32_t settle_digit(const float *part, float need, float *sm /*[16]*/)
 {
-    static_assert(kSampleBlocks * 16 == kSampleThreads * 4, "four partial totals per thread");
     const int tid = threadIdx.x;
-    const float4 mine = ldf4(part + 4 * tid);
-    __syncthreads();
-    *reinterpret_cast<float4 *>(tot + 4 * tid) = mine;
     __syncthreads();
     if (tid < 15) {
-        float t = 0.f;
+        float v[kSampleBlocks], t = 0.f;
 #pragma unroll
-        for (int g = 0; g < kSampleBlocks; g++) t += tot[g * 16 + tid];
+        for (int g = 0; g < kSampleBlocks; g++) v[g] = part[g * 16 + tid];
+#pragma unroll
+        for (int g = 0; g < kSampleBlocks; g++) t += v[g];
         sm[tid] = t;
     }
     __syncthreads();
@@ -556,7 +557,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     __shared__ float sm[16];
     __shared__ float red[4 * 15];
     __shared__ __align__(16) float scan[kSampleThreads];
-    __shared__ __align__(16) float tot[kSampleBlocks * 16];
+    __shared__ float tot[kSampleBlocks];
     __shared__ int sm_i[12];
     const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
     const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
@@ -608,22 +609,11 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     }
 
     // ---- the threshold searches ------------------------------------------------------------
-    // What bounds a launch here is its chain of round trips, not its bytes.  A slice of at most
-    // kSampleSliceMax weights is therefore requested whole, before the digit of the pass before is
-    // settled: into registers, from clamped addresses, 16 loads in flight per thread (SAMPLE_PASS:
-    // element tid + 256 j; SAMPLE_KEEP: the thread's contiguous piece).  Same order of additions as
-    // the loops that larger slices take.  With the totals of settle_digit: 16 rows of 151936, top-p alone, 88.3 ->
-    // 84.7 us a call; with a top-k of 100 in front 156 -> 147.
-    constexpr int NREG = kSampleSliceMax / kSampleThreads;
-    const bool in_regs = slice <= kSampleSliceMax;
-    const int piece = (slice + kSampleThreads - 1) / kSampleThreads;
-    const int j0 = min(i0 + tid * piece, i1), j1 = min(j0 + piece, i1);
-    float pv[NREG];
-    if (in_regs && a.stage != SAMPLE_MASS) {
-        const int first = a.stage == SAMPLE_PASS ? i0 + tid : j0, step = a.stage == SAMPLE_PASS ? kSampleThreads : 1;
-#pragma unroll
-        for (int j = 0; j < NREG; j++) pv[j] = p[min(first + j * step, V - 1)];
-    }
+    // What bounds a launch here is its chain of round trips (state, totals of the pass before, slice), not its
+    // bytes.  The slice is walked after the digit is settled, by a plain loop: holding it in registers, requested
+    // ahead of the settle, saves a round trip (one row of 151936: 61.8 -> 61.2 us a call) but unrolls the
+    // candidates' sums sixteen times, which costs every launch more than that on short slices (one row of 1000: 42.0 -> 49.2)
+    // and on many rows (64 rows of 32000: 113.7 -> 164.9).
     SampleState st = a.st_in[b];
     if (a.stage == SAMPLE_PASS && a.first) {
         // a new search: top-k counts every weight; top-p only the candidates of top-k (the
@@ -644,7 +634,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     } else if (a.stage == SAMPLE_PASS || a.settle) {
         // the digit of the pass before (its position: 4 bits above this pass's, or bit 0)
         const int prev_shift = (a.stage == SAMPLE_PASS) ? a.shift + 4 : 0;
-        st.prefix |= settle_digit(part_in, st.need, sm, tot) << prev_shift;
+        st.prefix |= settle_digit(part_in, st.need, sm) << prev_shift;
     }
     const float floor_t = __uint_as_float(st.floor_bits);
 
@@ -652,20 +642,13 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
         float acc[15];
 #pragma unroll
         for (int d = 0; d < 15; d++) acc[d] = 0.f;
-        auto add = [&](float v) {
+        for (int i = i0 + tid; i < i1; i += kSampleThreads) {
+            const float v = p[i];
             const float w = (v >= floor_t) ? (a.count ? 1.f : v) : 0.f;
             const uint32_t bits = __float_as_uint(v);
 #pragma unroll
             for (int d = 0; d < 15; d++)
                 acc[d] += (bits >= (st.prefix | ((uint32_t)(d + 1) << a.shift))) ? w : 0.f;
-        };
-        if (in_regs) {
-#pragma unroll
-            for (int j = 0; j < NREG; j++)
-                if (i0 + j * kSampleThreads < i1)     // uniform; an element past the slice adds nothing (-1 is below every floor)
-                    add(i0 + tid + j * kSampleThreads < i1 ? pv[j] : -1.f);
-        } else {
-            for (int i = i0 + tid; i < i1; i += kSampleThreads) add(p[i]);
         }
 #pragma unroll
         for (int d = 0; d < 15; d++) acc[d] = sum64(acc[d]);
@@ -694,13 +677,10 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     const uint32_t tau_bits = max(st.prefix, st.floor_bits);
     const float tau = __uint_as_float(tau_bits);
     {
+        const int piece = (slice + kSampleThreads - 1) / kSampleThreads;
+        const int j0 = min(i0 + tid * piece, i1), j1 = min(j0 + piece, i1);
         float mine = 0.f;
-        if (in_regs) {
-#pragma unroll
-            for (int j = 0; j < NREG; j++) mine += (j0 + j < j1 && pv[j] >= tau) ? pv[j] : 0.f;
-        } else {
-            for (int i = j0; i < j1; i++) mine += (p[i] >= tau) ? p[i] : 0.f;
-        }
+        for (int i = j0; i < j1; i++) mine += (p[i] >= tau) ? p[i] : 0.f;
         scan[tid] = mine;
         __syncthreads();
         if (tid == 0) {

@@ -60,6 +60,9 @@ CASES = [
     (300001, 1, 0.9, 0, 1.0),
     (5000, 2, 1.0, 64, 0.5001),      # 63 copies of the largest weight in every 1/64 of the row: ~4000 candidates
     (300, 3, 1e-3, 0, 1.0),          # tiny temperature: the argmax
+    (70, 64, 1.0, 0, 0.9),           # the general chain where most slices are empty, at the largest batch
+    (5000, 64, 1.0, 100, 0.9),       # both of its searches there
+    (16449, 3, 1.1, 0, 0.7),         # a slice one weight longer than the block has threads, the last ones short
 ]
 
 
