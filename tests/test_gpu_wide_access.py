@@ -54,12 +54,41 @@ def test_logits_at_any_float_address(dk, batch, vocab, shift):
     dm.close()
 
 
+# One layer of 24 query and 8 kv heads of 128: q/k/v [5120][hidden], output projection [hidden][3072], gate and up
+# [ffn][hidden], down [hidden][ffn], lm_head [vocab][hidden].
+FEW_ROWS = [
+    # hidden, ffn, vocab
+    (2048, 4088, 2003),      # gate, up and down 32 KB below 16 MB ...
+    (2048, 4096, 2003),      # ... exactly 16 MB ...
+    (2048, 4104, 2003),      # ... and 32 KB above
+    (3072, 3072, 2003),      # 18 MB each: K is three strides of 128 threads
+    (3000, 2800, 2003),      # K ends inside a stride
+    (2456, 512, 2003),       # q/k/v just below the 24 MB of four weight rows per block ...
+    (2464, 512, 2003),       # ... and just above
+    (3400, 2552, 2003),      # gate/up just below the 2560 weight rows from which three batch rows take four of them ...
+    (3400, 2560, 2003),      # ... and on the line
+    (2048, 6144, 2003),      # gate/up at four batch rows: the most weight rows that take four per block at 128 threads ...
+    (2048, 6152, 2003),      # ... and more
+    (5120, 3072, 2003),      # the same at 256 threads ...
+    (5120, 3080, 2003),      # ... and more
+    (1592, 8192, 2003),      # the down projection, K above 4096, just below its 1600 weight rows ...
+    (1600, 8192, 2003),      # ... and on them
+    (3072, 512, 4003),       # lm_head of 23 MB: two weight rows per block, two waves in the argmax
+    (3072, 512, 12003),      # 70 MB: eight; 128 threads at three and four batch rows
+    (4096, 512, 10235),      # 80 MB at K = 4096: four batch rows, below the 10240 weight rows of 128 threads ...
+    (4096, 512, 10243),      # ... and above
+    (3072, 10928, 2003),     # gate/up and down just above 64 MB; gate/up with 128 threads at three and four batch rows
+    (4096, 10240, 2003),     # gate/up at four batch rows with 128 threads, K = 4096
+]
+
+
 @pytest.mark.parametrize("batch", [2, 3, 4])
-@pytest.mark.parametrize("hidden,ffn", [(3072, 3072), (3000, 2800), (2048, 4104)])
-def test_few_rows_on_matrices_around_the_line(dk, orc, batch, hidden, ffn):
-    """Two to four rows of matrices just above and just below 16 MB, K a multiple of the 128 threads' stride or not:
-    four weight rows per block above the line, two below.  Bound: that of the other dense parity tests."""
-    shape = variant("tiny", n_layers=1, hidden=hidden, n_q_heads=24, n_kv_heads=8, head_dim=128, ffn=ffn, vocab=2003,
+@pytest.mark.parametrize("hidden,ffn,vocab", FEW_ROWS)
+def test_few_rows_on_matrices_around_the_line(dk, orc, batch, hidden, ffn, vocab):
+    """Two to four rows: both sides of every line at which the vector kernel's rows per block or threads change, K a
+    multiple of a block's stride or not, a last block with fewer weight rows than the others (the odd vocabularies).
+    Bound: that of the other dense parity tests."""
+    shape = variant("tiny", n_layers=1, hidden=hidden, n_q_heads=24, n_kv_heads=8, head_dim=128, ffn=ffn, vocab=vocab,
                     rope_theta=1e6)
     lay = build_block_tables([40 + 31 * i for i in range(batch)], 16, 2, seed=7)
     pool = W.fill_kv_pool(shape, lay, 8)
