@@ -594,6 +594,8 @@ template <int EPI, bool NORM>
 dk_status launch_gemm(const dk::GemmArgs &a, int Bp, hipStream_t st)
 {
     constexpr int NM = (EPI == dk::GEPI_SWIGLU) ? 2 : 1;
+    // hidden and ffn sizes (check_config): the epilogue moves their elements in fours without a narrow path
+    if (EPI != dk::GEPI_STORE && a.N % 8) return fail(DK_E_UNSUPPORTED_SHAPE, "GEMM with %d output rows (a multiple of 8 is needed)", a.N);
     const GemmPlan plan = gemm_plan(EPI, a.N, a.K, Bp, a.q4 != 0);
     if (plan.w) return launch_shared_gemm<EPI, NORM>(a, Bp, plan, st);
     // the variant of the K-split-per-wave kernel (dk_gemm_plan.h)

@@ -112,27 +112,25 @@ __device__ __forceinline__ uint4 q4_codes_bf16(uint32_t w)
     return r;
 }
 
-// The four residual values xres[n][r .. r+3] of a lane (r a multiple of 4; rows past the end are clamped: valid
-// addresses, unused values).
+// The four residual values xres[n][r .. r+3] of a lane.  r and N are multiples of 4; rows past the end are clamped:
+// valid addresses, unused values.
 __device__ __forceinline__ void load_resid4(const float *xrow, int r, int N, float (&x)[4])
 {
-    if ((N & 3) == 0) {
-        const float4 v = ldf4(xrow + min(r, N - 4));
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; i++) x[i] = xrow[min(r + i, N - 1)];
-    }
+    const float4 v = ldf4(xrow + min(r, N - 4));
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
 }
 
 // Epilogue of one finished 16-row tile.  The lane holds D[row0 + 4*lg + i][n = 16*t + ln], i = 0..3, in
 // v[t][matrix][i] (already scaled by 1/rms where the input norm is fused).  xr / gn: the residual rows and the
 // next norm's gains of exactly those elements (GEPI_RESID; loaded by the caller ahead of the weight stream).
-// A lane's four rows lie side by side in every output (act_offset keeps runs of 8 columns together), so with N a
-// multiple of 4 - every real shape - they leave in one store each: 8 bytes for the hi and the lo half, 16 for
-// float32, a quarter of the requests on the tail of the kernel (501-token prefill of the 8B shape 48.7 -> 45.7 ms, 700 tokens
-// of the 3B shape with 4-bit weights 37.5 -> 34.9, 16 rows of it 2.12 -> 2.08 ms per step).  Other N, and logits that are not 16-byte aligned, go
-// element by element.
+// A lane's four rows lie side by side in every output (act_offset keeps runs of 8 columns together) and leave in one
+// store each: 8 bytes for the hi and the lo half, 16 for float32, a quarter of the requests on the tail of the
+// kernel (501-token prefill of the 8B shape 48.7 -> 45.7 ms, 700 tokens of the 3B shape with 4-bit weights 37.5 ->
+// 34.9, 16 rows of it 2.12 -> 2.08 ms per step).  For GEPI_RESID and GEPI_SWIGLU N is the model's hidden or ffn size,
+// a multiple of 8 (checked where a model is created, and at the launch).  Only logits (GEPI_STORE) can have another
+// N or an address that is not 16-byte aligned; those go element by element.  A narrow path in the other two, which
+// nothing reached, cost registers and branches there: 16 rows of the 0.6B shape 1225 -> 1200 us per step without it,
+// 700 tokens of the 3B shape with 4-bit weights 34.4 -> 33.5 ms.
 template <int MT, int EPI>
 __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_tile, int lane,
                                                    const float (&v)[MT][(EPI == GEPI_SWIGLU) ? 2 : 1][4],
@@ -144,7 +142,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
     const int onks = (N + 127) >> 7;   // K-steps of the GEMM that consumes this output
     const int n_tiles = (N + 15) >> 4;
     const int row0 = out_tile * 16;
-    const bool wide = (N & 3) == 0 && (EPI != GEPI_STORE || ((uintptr_t)a.y & 15) == 0);
+    const bool wide = EPI != GEPI_STORE || ((N & 3) == 0 && ((uintptr_t)a.y & 15) == 0);
     float best = -INFINITY;
     int best_i = 0x7fffffff;
 #pragma unroll
@@ -189,15 +187,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
             if (!nvalid || r >= N) continue;
             if (EPI == GEPI_STORE && out[i] > best) { best = out[i]; best_i = r; }
             if (EPI == GEPI_RESID) sq += out[i] * out[i];
-            if (wide) continue;
-            if (EPI == GEPI_STORE) {
-                if (a.y != nullptr) a.y[(int64_t)n * N + r] = out[i];
-            } else {
-                const int64_t oo = act_offset(n, r, onks);
-                a.ohi[oo] = (uint16_t)(hi[i >> 1] >> (16 * (i & 1)));
-                a.olo[oo] = (uint16_t)(lo[i >> 1] >> (16 * (i & 1)));
-                if (EPI == GEPI_RESID) a.xres[(int64_t)n * N + r] = out[i];
-            }
+            if (!wide && a.y != nullptr) a.y[(int64_t)n * N + r] = out[i];
         }
         if (EPI == GEPI_RESID) {
             // the tile's 16 rows of batch row n are spread over the 4 lane groups
