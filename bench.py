@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # kernel: x2.0 and x1.0 to KiB), see profiles/decode_step_cfg1_hbm_counters.md.
 # Quoted only while the library reports the kernel revision they were taken on.
 MEASURED_TRAFFIC = {("cfg1", "fused_step"): ("fused r9", 1290928457),      # the whole step, one launch
-                    ("cfg1", "gemv"): ("gemv r3", 10805373)}             # --kernel-per-stage
+                    ("cfg1", "gemv"): ("gemv r4", 10803020)}             # --kernel-per-stage
 
 
 def cpu_baseline(shape, weights, layout, pool_bits, tokens, budget_s=12.0, max_steps=64, max_rows=2):
