@@ -17,7 +17,8 @@
 // layer matrices of the 0.6B, 3B, 8B and 30B-A3B shapes at 16..64 rows, 1..8 slices (about 400
 // timings; the fit reproduces them to 13 % rms for the shared kernel, 16 % for the other).  What
 // matters is the ranking: on those sweeps the estimate's choice is the measured best, or within 5 %
-// of it, except where two candidates are within the sweeps' own scatter.
+// of it, except where two candidates are within the sweeps' own scatter.  The sweeps are older than the 16-byte hand-over
+// of K slices and the four-element stores of the epilogue, which shorten the fixed part of both kernels.
 #pragma once
 #include <algorithm>
 #include <cmath>
