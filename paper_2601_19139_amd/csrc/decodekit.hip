@@ -383,27 +383,27 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
 }
 
 // ---- GEMV dispatch ----------------------------------------------------------
-// Rows per block tile.  Small matrices (a few MB, one or two loads per lane)
-// are latency-bound: two rows per block spread them over every compute unit.
-// Large ones (lm_head) stream better with eight rows per block.
+// Rows per block tile.  Small matrices (a few MB, one or two loads per lane) are latency-bound: two rows per block
+// spread them over every compute unit. Large ones (lm_head) stream better with eight rows per block.
 //
-// With two to four batch rows the activations are the larger stream: a thread fetches 32 bytes of x per batch row for
-// every 16 bytes of a weight row, from the caches, once per weight row of its block.  From 16 MB on the rows per block
-// and the threads that walk K are therefore chosen by two more rules.  Both lines come from a sweep of the kernel alone
-// over weights from HBM (K = 1024..14336, 8..600 MB, 2..4 rows, about 1800 shapes, every epilogue; "before" is two rows and
-// 256 threads below 64 MB, eight rows - gate/up four - and 256 threads above).
-// Whole steps at 2 / 3 / 4 rows, before -> after: 3B shape (19..50 MB a matrix) 1934 / 2502 / 3011 -> 1809 / 2038 / 2520
-// us, 8B shape (33 MB and up) 3678 / 4262 / 5627 -> 3612 / 4163 / 5262; the 0.6B shape (4..6 MB) lies below the lines.
+// With two to four batch rows the activations are the larger stream: a thread fetches 32 bytes of x per batch row
+// for every 16 bytes of a weight row, from the caches, once per weight row of its block.  From 16 MB on the rows
+// per block and the threads that walk K are therefore chosen by two more rules.  Both lines come from a sweep of
+// the kernel alone over weights from HBM (K = 1024..14336, 8..600 MB, 2..4 rows, about 1800 shapes, every epilogue;
+// "before" is two rows and 256 threads below 64 MB, eight rows - gate/up four - and 256 threads above). Whole steps
+// at 2 / 3 / 4 rows, before -> after: 3B shape (19..50 MB a matrix) 1934 / 2502 / 3011 -> 1809 / 2038 / 2520 us, 8B
+// shape (33 MB and up) 3678 / 4262 / 5627 -> 3612 / 4163 / 5262; the 0.6B shape (4..6 MB) lies below the lines.
 inline size_t gemv_bytes(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2; }
 inline bool gemv_small(const dk::GemvArgs &a) { return gemv_bytes(a) < (64u << 20); }
 
-// Four weight rows per block between 16 and 64 MB, where the blocks still fill the chip: half the activation traffic
-// (before -> after, 48 MB: K = 3072, 4 rows, plain store 27.2 -> 17.1 us with the 128 threads below; K = 8192, 2 rows, residual 13.5 ->
-// 12.4).  Below the line the fewer blocks cost more: K = 12288, 24 MB, 1024 weight rows: 18.2 -> 23.7 for gate/up; K = 2048, 17 MB: 7.3 -> 7.8.
-// A gate/up block of two rows carries four weight rows already.  Another four pay at three batch rows (K = 2048, 48 MB
-// 33.3 -> 23.3) and, at two, beyond K = 4096 (K = 8192, 48 MB 23.3 -> 21.7; K = 2048, 17 MB 10.2 -> 11.3).
-// At four batch rows such a block needs 151 registers per lane, three waves per SIMD: it pays where the blocks
-// are one round on the chip at least two thirds full (K = 4096, 6144 weight rows 34.8 -> 28.5; 7168: 39.5 -> 43.9).
+// Four weight rows per block between 16 and 64 MB, where the blocks still fill the chip: half the activation
+// traffic (before -> after, 48 MB: K = 3072, 4 rows, plain store 27.2 -> 17.1 us with the 128 threads below; K =
+// 8192, 2 rows, residual 13.5 -> 12.4).  Below the line the fewer blocks cost more: K = 12288, 24 MB, 1024 weight
+// rows: 18.2 -> 23.7 for gate/up; K = 2048, 17 MB: 7.3 -> 7.8. A gate/up block of two rows carries four weight rows
+// already.  Another four pay at three batch rows (K = 2048, 48 MB 33.3 -> 23.3) and, at two, beyond K = 4096 (K =
+// 8192, 48 MB 23.3 -> 21.7; K = 2048, 17 MB 10.2 -> 11.3). At four batch rows such a block needs 151 registers per
+// lane, three waves per SIMD: it pays where the blocks are one round on the chip at least two thirds full (K =
+// 4096, 6144 weight rows 34.8 -> 28.5; 7168: 39.5 -> 43.9).
 inline bool gemv_four_rows(const dk::GemvArgs &a, int nb, int epi)
 {
     const size_t bytes = gemv_bytes(a);
@@ -419,12 +419,13 @@ inline bool gemv_four_rows(const dk::GemvArgs &a, int nb, int epi)
     return a.K >= 2048 && a.N >= 4096 && bytes >= (24u << 20);
 }
 
-// 128 threads instead of 256 for 2048 <= K <= 4096: a thread takes two to four strides of K instead of one or two (one
-// and a half at K = 3072), so a block's fixed part - sums across lanes and waves - is shared by more of them.  Up to
-// 64 MB at any number of rows (0.72..1.05 of the time before).  Above 64 MB blocks of eight rows have fewer waves in flight with 128
-// threads: that loses at two batch rows (K = 2048, 200 MB, residual 35.9 -> 39.9 us) and at K = 4096 (3 rows, 200 MB
-// 42.7 -> 46.7), and wins where the arithmetic weighs more: three rows below K = 4096 (K = 2560, 200 MB 52.5 -> 45.1), four rows
-// (K = 3584, 400 MB 139.8 -> 115.7), at K = 4096 from 10240 weight rows on (600 MB 189.8 -> 170.1; 64 MB 19.1 -> 21.9).
+// 128 threads instead of 256 for 2048 <= K <= 4096: a thread takes two to four strides of K instead of one or two
+// (one and a half at K = 3072), so a block's fixed part - sums across lanes and waves - is shared by more of them.
+// Up to 64 MB at any number of rows (0.72..1.05 of the time before).  Above 64 MB blocks of eight rows have fewer
+// waves in flight with 128 threads: that loses at two batch rows (K = 2048, 200 MB, residual 35.9 -> 39.9 us) and
+// at K = 4096 (3 rows, 200 MB 42.7 -> 46.7), and wins where the arithmetic weighs more: three rows below K = 4096
+// (K = 2560, 200 MB 52.5 -> 45.1), four rows (K = 3584, 400 MB 139.8 -> 115.7), at K = 4096 from 10240 weight rows
+// on (600 MB 189.8 -> 170.1; 64 MB 19.1 -> 21.9).
 inline bool gemv_128_threads(const dk::GemvArgs &a, int nb)
 {
     if (nb < 2 || a.K < 2048 || a.K > 4096 || gemv_bytes(a) < (16u << 20)) return false;

@@ -612,8 +612,8 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     // What bounds a launch here is its chain of round trips (state, totals of the pass before, slice), not its
     // bytes.  The slice is walked after the digit is settled, by a plain loop: holding it in registers, requested
     // ahead of the settle, saves a round trip (one row of 151936: 61.8 -> 61.2 us a call) but unrolls the
-    // candidates' sums sixteen times, which costs every launch more than that on short slices (one row of 1000: 42.0 -> 49.2)
-    // and on many rows (64 rows of 32000: 113.7 -> 164.9).
+    // candidates' sums sixteen times, which costs every launch more than that on short slices (one row of 1000:
+    // 42.0 -> 49.2) and on many rows (64 rows of 32000: 113.7 -> 164.9).
     SampleState st = a.st_in[b];
     if (a.stage == SAMPLE_PASS && a.first) {
         // a new search: top-k counts every weight; top-p only the candidates of top-k (the

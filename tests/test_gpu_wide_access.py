@@ -63,6 +63,8 @@ FEW_ROWS = [
     (2048, 4104, 2003),      # ... and 32 KB above
     (3072, 3072, 2003),      # 18 MB each: K is three strides of 128 threads
     (3000, 2800, 2003),      # K ends inside a stride
+    (2040, 4120, 2003),      # more than 16 MB, K just below the 2048 ...
+    (4104, 2048, 2003),      # ... and just above the 4096 between which a block has 128 threads
     (2456, 512, 2003),       # q/k/v just below the 24 MB of four weight rows per block ...
     (2464, 512, 2003),       # ... and just above
     (3400, 2552, 2003),      # gate/up just below the 2560 weight rows from which three batch rows take four of them ...
