@@ -212,6 +212,58 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
     }
 }
 
+// The sum-of-squares partials of the input rows (NORM), for one of NW waves that share them; a partial is a row of
+// kSsqStride floats.  request() comes ahead of the first weights, store() - out[0..16*MT) - behind their requests, so
+// that the sums are made while the weights are under way.  Up to 16 batch rows a load brings 16 partials (16 bytes a
+// lane, four lanes to a partial): one float a lane and load was 16 times as many requests, all of them in front of
+// the first weights, and loads return in order.  (8B shape, 16 rows, together with the rotated K-steps below: 5.73 ->
+// 5.61 ms per step; 0.6B shape 1.202 -> 1.176.)  Beyond 16 rows the same measured nothing.
+template <int MT, int NW>
+struct SsqPartials {
+    static constexpr int U = MT == 1 ? 4 : 32;   // loads held in registers
+    float4 q[MT == 1 ? U : 1];
+    float v[MT == 1 ? 1 : U];
+    __device__ __forceinline__ int part(int wv, int lane, int u) const
+    {
+        return MT == 1 ? (u * NW + wv) * 16 + (lane >> 2) : u * NW + wv;
+    }
+    __device__ __forceinline__ void request(const float *ssq, int n_part, int wv, int lane)
+    {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const float *row = ssq + (int64_t)min(part(wv, lane, u), n_part - 1) * kSsqStride;
+            if constexpr (MT == 1) q[u] = ldf4(row + (lane & 3) * 4);
+            else v[u] = row[min(lane, 16 * MT - 1)];
+        }
+    }
+    __device__ __forceinline__ void store(const float *ssq, int n_part, int wv, int lane, float *out)
+    {
+        if constexpr (MT == 1) {
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            auto add = [&](const float4 &w) { s.x += w.x; s.y += w.y; s.z += w.z; s.w += w.w; };
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                if (part(wv, lane, u) < n_part) add(q[u]);
+            for (int p = part(wv, lane, U); p < n_part; p += NW * 16)   // very wide models only
+                add(ldf4(ssq + (int64_t)p * kSsqStride + (lane & 3) * 4));
+#pragma unroll
+            for (int off = 4; off < 64; off <<= 1) {
+                s.x += __shfl_xor(s.x, off);
+                s.y += __shfl_xor(s.y, off);
+                s.z += __shfl_xor(s.z, off);
+                s.w += __shfl_xor(s.w, off);
+            }
+            if (lane < 4) *reinterpret_cast<float4 *>(out + lane * 4) = s;
+        } else {
+            float s = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; u++) s += part(wv, lane, u) < n_part ? v[u] : 0.f;
+            for (int p = part(wv, lane, U); p < n_part; p += NW) s += ssq[(int64_t)p * kSsqStride + min(lane, 16 * MT - 1)];
+            out[lane] = s;
+        }
+    }
+};
+
 // KALIGNED: K is a multiple of 128 (every real model shape); the K-steps are then
 // whole and the loaded registers feed the MFMAs untouched.
 // Q4 (needs KALIGNED): per row K/2 bytes of codes, a K-step of 128 columns being 16 words
@@ -278,10 +330,16 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
     struct Stage {
         uint4 wa[NA][4], bh[MT][4], bl[MT][4];
     };
+    // Up to 16 batch rows block b begins b steps into K and wraps around: started together at the same column, the
+    // blocks would ask the same few memory channels at the same time all along K (201 MB read this way and nothing
+    // else: 38.1 us from a common first column, 32.5 from rotated ones).  Beyond 16 rows, and where groups of rows share
+    // the weights through the caches, the stream is not the limit.
+    const int rot = MT == 1 && gridDim.y == 1 ? (int)blockIdx.x % nks : 0;
+    auto step = [&](int it) { const int ks = min(it * KS + wv, nks - 1) + rot; return ks < nks ? ks : ks - nks; };
     int it_i = 0;   // step to issue next
     auto issue = [&](Stage &st) {
         const int g = (int)blockIdx.x;
-        const int ks = min(it_i * KS + wv, nks - 1);
+        const int ks = step(it_i);
         const int kb = ks * 128 + lg * 8;
         if constexpr (Q4) {
             const int n_tiles16 = (N + 15) >> 4;
@@ -331,8 +389,8 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
         it_i++;
     };
     auto consume = [&](Stage &st, int it) {
-        const int ks = it * KS + wv;
-        if (ks >= nks) return;   // a padding step of this wave (uniform branch)
+        if (it * KS + wv >= nks) return;   // a padding step of this wave (uniform branch)
+        const int ks = step(it);
         if constexpr (Q4) {
             const uint4 one4 = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
             const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -410,15 +468,9 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
     };
 
     // Sum-of-squares partials of the input rows: requested before the weight
-    // stream starts and added up after it, so their latency is hidden and the
-    // main loop never waits for them alone.  Wave wv takes partials wv, wv+KS, ...
-    constexpr int SSQ_REGS = 32;
-    float sv[SSQ_REGS];
-    if (NORM) {
-#pragma unroll
-        for (int u = 0; u < SSQ_REGS; u++)
-            sv[u] = a.ssq_in[(int64_t)min(wv + u * KS, a.n_part - 1) * kSsqStride + min(lane, 16 * MT - 1)];
-    }
+    // stream starts and added up while its first stages are under way.
+    SsqPartials<MT, KS> ssq;
+    if (NORM) ssq.request(a.ssq_in, a.n_part, wv, lane);
 
     // The residual rows and the next norm's gains that the epilogue of wave rt < RT will
     // need: requested ahead of the weight stream as well (clamped addresses; used only
@@ -435,6 +487,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
     Stage st[PD];
 #pragma unroll
     for (int p = 0; p < PD; p++) issue(st[p]);
+    if (NORM) ssq.store(a.ssq_in, a.n_part, wv, lane, ssq_s[wv]);   // while the first weights are under way
 
     {
         for (int it = 0; it + PD < niter2; it += PD) {
@@ -446,14 +499,6 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
         }
 #pragma unroll
         for (int p = 0; p < PD; p++) consume(st[p], niter2 - PD + p);
-        if (NORM) {
-            float ss = 0.f;
-#pragma unroll
-            for (int u = 0; u < SSQ_REGS; u++) ss += (wv + u * KS < a.n_part) ? sv[u] : 0.f;
-            for (int p = wv + SSQ_REGS * KS; p < a.n_part; p += KS)   // very wide models only
-                ss += a.ssq_in[(int64_t)p * kSsqStride + min(lane, 16 * MT - 1)];
-            ssq_s[wv][lane] = ss;
-        }
         // K-splits meet in LDS
         RedBuf &rb = red[0];
 #pragma unroll

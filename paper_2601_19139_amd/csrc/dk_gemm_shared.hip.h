@@ -65,7 +65,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     constexpr int PPT = PIECES / TPB;
     extern __shared__ uint4 sm_act_dyn[];   // two slots of one step's activation tile (shared_gemm_lds_bytes)
     uint4 (*sm_act)[PIECES] = reinterpret_cast<uint4 (*)[PIECES]>(sm_act_dyn);
-    __shared__ float sm_ssq[W][64];
+    __shared__ __align__(16) float sm_ssq[W][64];
     __shared__ int sm_last;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -90,9 +90,12 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     struct Stage {
         uint4 wa[NA][Q4 ? 3 : 4], act[PPT];   // Q4: codes of the whole step, (scale, bias) of its two groups
     };
+    const int rot = MT == 1 ? (int)blockIdx.x % max(niter, 1) : 0;   // each block begins at another column (see skinny_gemm_kernel)
     int it_i = 0;
     auto issue = [&](Stage &st) {
-        const int ks = max(min(ks0 + it_i, ks1 - 1), 0);   // (an empty slice - more slices than steps - reads step 0, unused)
+        // (a step past the slice, or an empty slice - more slices than steps: a valid step, unused)
+        int ks = max(min(it_i, niter - 1), 0) + rot;
+        ks = min(ks0 + (ks < niter ? ks : ks - niter), nks - 1);
 #pragma unroll
         for (int p = 0; p < PPT; p++) {
             const int piece = p * TPB + tid;
@@ -183,15 +186,9 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
             }
     };
 
-    // sum-of-squares partials of the input rows (NORM), requested ahead of the stream:
-    // wave wv takes partials wv, wv+W, ...; lane = batch row
-    constexpr int SSQ_REGS = 32;
-    float sv[SSQ_REGS];
-    if (NORM) {
-#pragma unroll
-        for (int u = 0; u < SSQ_REGS; u++)
-            sv[u] = a.ssq_in[(int64_t)min(wv + u * W, a.n_part - 1) * kSsqStride + lane];
-    }
+    // sum-of-squares partials of the input rows (NORM), requested ahead of the stream
+    SsqPartials<MT, W> ssq;
+    if (NORM) ssq.request(a.ssq_in, a.n_part, wv, lane);
     // residual rows and next gains of this wave's tiles (GEPI_RESID)
     float xr[RT][MT][4], gn[RT][4];
     if (EPI == GEPI_RESID) {
@@ -208,6 +205,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     Stage st[PD];
 #pragma unroll
     for (int p = 0; p < PD; p++) issue(st[p]);
+    if (NORM) ssq.store(a.ssq_in, a.n_part, wv, lane, sm_ssq[wv]);   // while the first weights are under way
     for (int it = 0; it + PD < niter2; it += PD) {
 #pragma unroll
         for (int p = 0; p < PD; p++) {
@@ -217,14 +215,6 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     }
 #pragma unroll
     for (int p = 0; p < PD; p++) consume(st[p], niter2 - PD + p);
-
-    if (NORM) {
-        float ss = 0.f;
-#pragma unroll
-        for (int u = 0; u < SSQ_REGS; u++) ss += (wv + u * W < a.n_part) ? sv[u] : 0.f;
-        for (int p = wv + SSQ_REGS * W; p < a.n_part; p += W) ss += a.ssq_in[(int64_t)p * kSsqStride + lane];
-        sm_ssq[wv][lane] = ss;
-    }
 
     if (S > 1) {
         // partial tiles out, ticket, and only the last block of this row block goes on

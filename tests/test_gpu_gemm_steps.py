@@ -1,0 +1,37 @@
+"""The matrix-core GEMMs at the edges of their steps over K and of their tables of partial sums."""
+import pytest
+
+import workloads as W
+from workloads.blocktable import build_block_tables
+from gpu_common import run_both, check_parity, check_pool
+
+pytestmark = pytest.mark.gpu
+
+
+def variant(base, **kw):
+    return W.ModelConfig(**{**W.CONFIGS[base].as_dict(), **kw})
+
+
+@pytest.mark.parametrize("hidden,ffn,batch", [
+    (136, 120, 5),       # two steps of K for eight waves; 9 sum-of-squares partials
+    (136, 120, 16),
+    (1288, 1032, 5),     # a last step of 8 columns; 81 partials
+    (1288, 1032, 16),
+    (1152, 2176, 16),    # 9 and 17 whole steps
+    (4104, 512, 16),     # 257 partials
+    (8192, 256, 5),      # 512 partials: as many as eight waves hold in registers ...
+    (8200, 256, 5),      # ... and more; 65 steps, the last of 8 columns
+])
+def test_rotated_steps_and_partials(orc, hidden, ffn, batch):
+    """Up to 16 rows a block starts at its own step of K and wraps around: steps that do not divide among the waves,
+    fewer steps than waves, a last step that is not whole.  Bound: that of the other dense parity tests."""
+    # No short contexts: with an empty one the attention output is the new token's v, and one of its 128 elements
+    # rounded to the other bf16 neighbour (2^-8 of it) is 2^-8 / sqrt(128) = 3.5e-4 of the row, above the bound,
+    # whatever the order of the sums; among 30 tokens it is a thirtieth of that.
+    shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=1003, qk_norm=True)
+    lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 2, seed=11)
+    pool = W.fill_kv_pool(shape, lay, 12)
+    out = run_both(orc, shape, W.make_weights(shape, 13), lay, pool, W.initial_tokens(shape, batch, 14), 2)
+    worst, agree = check_parity(out)
+    check_pool(out, pool, shape, lay, 2)
+    assert worst < 2e-4 and agree == 1.0
