@@ -423,8 +423,9 @@ dk_status dk_read_stream(const void *d_buf, size_t bytes, void *d_sink, void *hi
 
 /* Introspection (host only, launches nothing): which kernel a batched weight-streaming GEMM of the decode
  * step takes for a matrix of N rows and K columns at B batch rows (5..64), on a device with
- * `compute_units` compute units (0: the current device's count, 256 if none answers).  The choice is the
- * candidate with the smallest estimated duration of a latency/occupancy model of the weight stream.
+ * `compute_units` compute units (0: the current device's count, 256 if none answers).  Up to 16 rows the choice
+ * follows measured rules on the matrix; above it is the candidate with the smallest estimated duration of a
+ * latency/occupancy model of the weight stream.
  * epilogue: 0 plain store (q | k | v, lm_head), 1 residual projection (attention output, down), 2 the
  * gate/up pair with SwiGLU (N = rows of each of the two matrices).  four_bit: 1 for 4-bit weights.
  * out_waves: 0 = the kernel whose waves split K (then out_slices = 1); otherwise the waves per block of

@@ -175,6 +175,7 @@ struct Workspace {
     bool fused;
     int Bp;             // batch rows padded to a multiple of 16
     bool batched;
+    int pack;           // batched path: the terms of an activation share one 16-column operand (2 or 3 terms; 0: hi and lo apart)
     int chunk_tokens, max_chunks, lm_blocks;
     int pf_chunk_tokens, pf_max_chunks;   // the same split for the kernel that takes a prefill chunk's rows in groups
     bool defer_merge;   // small problems: the output projection merges the attention chunks
@@ -233,15 +234,33 @@ int fused_variant(const dk_model_config &c, int B)
 using dkplan::GemmPlan;
 static_assert(dkplan::EPI_STORE == dk::GEPI_STORE && dkplan::EPI_RESID == dk::GEPI_RESID && dkplan::EPI_SWIGLU == dk::GEPI_SWIGLU,
               "the plan's epilogue codes are the kernels'");
-GemmPlan gemm_plan(int epi, int N, int K, int Bp, bool q4) { return dkplan::gemm_plan(epi, N, K, Bp, q4, device_cus()); }
+GemmPlan gemm_plan(int epi, int N, int K, int Bp, bool q4, int pack) { return dkplan::gemm_plan(epi, N, K, Bp, q4, pack != 0, device_cus()); }
 // Row blocks (= tickets) and partial-tile floats of that plan.
-void gemm_plan_needs(int epi, int N, int K, int Bp, bool q4, size_t &tickets, size_t &part_floats)
+void gemm_plan_needs(int epi, int N, int K, int Bp, bool q4, int pack, size_t &tickets, size_t &part_floats)
 {
-    const GemmPlan p = gemm_plan(epi, N, K, Bp, q4);
+    const GemmPlan p = gemm_plan(epi, N, K, Bp, q4, pack);
     if (p.w == 0 || p.slices == 1) return;
     const size_t tiles = (size_t)(N + 15) / 16;
     tickets = std::max(tickets, (tiles + p.w - 1) / p.w);
     part_floats = std::max(part_floats, dk::shared_gemm_part_floats(N, p.slices, epi == dk::GEPI_SWIGLU ? 2 : 1, Bp / 16));
+}
+
+// Terms of an activation that share one operand of the matrix-core GEMMs (dk_gemm.hip.h, kPackCols): two for 5..8 rows
+// (and fewer of expert and 4-bit models), half the activations and products of hi and lo apart (6 rows, whole step:
+// 0.6B shape 1114 -> 1010 us, 3B 2180 -> 1998, 8B 4434 -> 4019; 4 bit 3B 1651 -> 1375).
+// Three or four rows of a dense model take three terms, all of float32's bits, instead of the vector-ALU products, which
+// re-read float32 activations per two to four weight rows: 4 rows, 0.6B shape 1072 -> 985 us, 3B 2484 -> 1996, 8B 5208 ->
+// 3809.  Three rows gain from the 3B shape on (50 MB a matrix; 2021 -> 1975, 8B 4108 -> 3740) and lose 2 % at the 0.6B shape,
+// two lose on all but the 8B shape (equal there): the vector kernel's work grows with the rows, this one's does not.
+constexpr int kPackRows2 = dk::kPackCols(2);
+static_assert(kMaxGemvBatch <= dk::kPackCols(3), "three terms of the few-row batches fit one operand");
+int pack_terms(const dk_model_config &c, int B, bool q4)
+{
+    const size_t H = (size_t)c.hidden, qd = (size_t)c.n_q_heads * c.head_dim;
+    if (H % 128 || qd % 128 || (c.n_experts == 0 && c.ffn % 128) || B > kPackRows2) return 0;
+    if (B > kMaxGemvBatch || c.n_experts > 0 || q4) return 2;
+    const size_t mb = (H * c.ffn * 2) >> 20;   // of the gate matrix
+    return mb >= (B == 4 ? 4u : 32u) && B >= 3 ? 3 : 0;
 }
 
 // q4: the model's matrices are 4-bit; every batch size then takes the matrix-core kernels
@@ -264,7 +283,8 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     //    unit, one round of at most 768 blocks - beats both (3B shape, ragged contexts up to 2 k:
     //    25.4 -> 22.5 us per launch; 0.6B shape, 16 rows of context 512: 15.1 -> 12.9 us); with 4 k
     //    contexts or groups of 8 it is slower and is not taken.
-    const bool batched_attn = B > kMaxGemvBatch || c.n_experts > 0 || q4;
+    const bool batched_attn = B > kMaxGemvBatch || c.n_experts > 0 || q4;   // (three terms: the vector-ALU kernel's float32 probabilities)
+    w.pack = pack_terms(c, B, q4);
     const int pairs = B * c.n_kv_heads;
     auto round64 = [](int v) { v = (v + 63) / 64 * 64; return v < 64 ? 64 : v; };
     auto chunk_for = [&](int want_blocks) {
@@ -291,7 +311,7 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     // the output projection then merges them as it loads its input (at most 8
     // chunks, one round of loads), which saves the attention kernel a round of
     // device-wide synchronisation.
-    if (B <= kMaxGemvBatch && c.n_experts == 0 && !q4) {   // the vector-ALU path only
+    if (B <= kMaxGemvBatch && c.n_experts == 0 && !q4 && w.pack == 0) {   // the vector-ALU path only
         int chunk8 = ((ctx_max + 7) / 8 + 63) / 64 * 64;
         if (chunk8 < chunk) chunk8 = chunk;
         const int n8 = (ctx_max + chunk8 - 1) / chunk8;
@@ -325,17 +345,18 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     }
     w.part = take(part_floats * 4);
     w.Bp = (B + 15) / 16 * 16;
-    w.batched = B > kMaxGemvBatch || c.n_experts > 0 || q4;   // expert layers and 4-bit weights use the matrix-core kernels
+    // expert layers and 4-bit weights use the matrix-core kernels
+    w.batched = B > kMaxGemvBatch || c.n_experts > 0 || q4 || w.pack == 3;
     size_t gemm_tickets = 0, gemm_part = 0;
     if (w.batched) {
         const int H = c.hidden, qd = c.n_q_heads * d;
-        gemm_plan_needs(dk::GEPI_STORE, (int)qkv_dim, H, w.Bp, q4, gemm_tickets, gemm_part);
-        gemm_plan_needs(dk::GEPI_RESID, H, qd, w.Bp, q4, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_STORE, (int)qkv_dim, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_RESID, H, qd, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
         if (c.n_experts == 0) {
-            gemm_plan_needs(dk::GEPI_SWIGLU, c.ffn, H, w.Bp, q4, gemm_tickets, gemm_part);
-            gemm_plan_needs(dk::GEPI_RESID, H, c.ffn, w.Bp, q4, gemm_tickets, gemm_part);
+            gemm_plan_needs(dk::GEPI_SWIGLU, c.ffn, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
+            gemm_plan_needs(dk::GEPI_RESID, H, c.ffn, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
         }
-        gemm_plan_needs(dk::GEPI_STORE, c.vocab, H, w.Bp, q4, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_STORE, c.vocab, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
     }
     w.n_tickets = B * c.n_kv_heads + (int)gemm_tickets;
     w.tickets = take((size_t)w.n_tickets * 4);
@@ -496,7 +517,7 @@ dk_status launch_gemv(dk::GemvArgs a, int B, hipStream_t st)
 
 // ---- skinny GEMM dispatch (batches of 5..64 rows) ---------------------------
 // col_groups > 1: the batch rows are split into that many groups of 16*MT across blockIdx.y
-template <int MT, int KS, int RT, int EPI, bool NORM, bool KALIGNED, bool Q4 = false>
+template <int MT, int KS, int RT, int EPI, bool NORM, bool KALIGNED, bool Q4 = false, int PACK = 0>
 dk_status launch_gemm_inst(const dk::GemmArgs &a, int col_groups, hipStream_t st)
 {
     constexpr size_t lds = dk::skinny_gemm_lds_bytes<MT, KS, RT, EPI>();
@@ -506,10 +527,10 @@ dk_status launch_gemm_inst(const dk::GemmArgs &a, int col_groups, hipStream_t st
     // step anyway (K <= 128 * KS: the second stage would only fetch a step it never uses - q/k/v of
     // the 0.6B shape at 16 rows 6.3 -> 5.4 us, gate/up 8.1 -> 6.8 us)
     if ((a.K + 127) / 128 <= KS) {
-        DK_LAUNCH(DK_K_GEMM, (dk::skinny_gemm_kernel<MT, KS, RT, 1, EPI, NORM, KALIGNED, Q4>), grid,
+        DK_LAUNCH(DK_K_GEMM, (dk::skinny_gemm_kernel<MT, KS, RT, 1, EPI, NORM, KALIGNED, Q4, PACK>), grid,
                   dim3(KS * 64), lds, st, a);
     } else {
-        DK_LAUNCH(DK_K_GEMM, (dk::skinny_gemm_kernel<MT, KS, RT, 2, EPI, NORM, KALIGNED, Q4>), grid,
+        DK_LAUNCH(DK_K_GEMM, (dk::skinny_gemm_kernel<MT, KS, RT, 2, EPI, NORM, KALIGNED, Q4, PACK>), grid,
                   dim3(KS * 64), lds, st, a);
     }
     DK_HIP(hipGetLastError());
@@ -519,9 +540,16 @@ dk_status launch_gemm_inst(const dk::GemmArgs &a, int col_groups, hipStream_t st
 template <int MT, int KS, int RT, int EPI, bool NORM>
 dk_status launch_gemm_cfg(const dk::GemmArgs &a, hipStream_t st, int col_groups = 1)
 {
+    if (a.pack && (MT != 1 || KS != 4 || col_groups != 1 || a.K % 128)) return fail(DK_E_INVALID_ARG, "packed terms with %d rows, K = %d", a.B, a.K);
     if (a.q4) {
         if (a.K % 128) return fail(DK_E_UNSUPPORTED_SHAPE, "4-bit matrix with K = %d (a multiple of 128 is needed)", a.K);
+        if constexpr (MT == 1 && KS == 4)
+            if (a.pack == 2) return launch_gemm_inst<MT, KS, RT, EPI, NORM, true, true, 2>(a, col_groups, st);
         return launch_gemm_inst<MT, KS, RT, EPI, NORM, true, true>(a, col_groups, st);
+    }
+    if constexpr (MT == 1 && KS == 4) {
+        if (a.pack == 2) return launch_gemm_inst<MT, KS, RT, EPI, NORM, true, false, 2>(a, col_groups, st);
+        if (a.pack == 3) return launch_gemm_inst<MT, KS, RT, EPI, NORM, true, false, 3>(a, col_groups, st);
     }
     if (a.K % 128 == 0) return launch_gemm_inst<MT, KS, RT, EPI, NORM, true>(a, col_groups, st);
     return launch_gemm_inst<MT, KS, RT, EPI, NORM, false>(a, col_groups, st);
@@ -533,11 +561,18 @@ dk_status launch_gemm_cfg(const dk::GemmArgs &a, hipStream_t st, int col_groups 
 // the 8B-class shapes: 4 tiles per wave for the lm_head, 2 for the fused q/k/v
 // matrix, 1 for the square-ish projections and the gate/up pair).
 // ---- shared-activation GEMM dispatch (see gemm_plan) -------------------------
-template <int MT, int W, int EPI, bool NORM, bool Q4 = false>
+template <int MT, int W, int EPI, bool NORM, bool Q4 = false, int PACK = 0>
 dk_status launch_shared_gemm_inst(const dk::GemmArgs &a, int slices, hipStream_t st)
 {
+    // packed terms: what gemm_plan_16 can ask for
+    if constexpr (MT == 1 && PACK == 0 && (Q4 ? EPI == dk::GEPI_STORE : EPI != dk::GEPI_STORE)) {
+        if (a.pack == 2) return launch_shared_gemm_inst<MT, W, EPI, NORM, Q4, 2>(a, slices, st);
+        if constexpr (!Q4)
+            if (a.pack == 3) return launch_shared_gemm_inst<MT, W, EPI, NORM, Q4, 3>(a, slices, st);
+    }
+    if (a.pack != PACK) return fail(DK_E_INVALID_ARG, "no shared-activation GEMM for %d packed terms", a.pack);
     constexpr size_t lds = dk::shared_gemm_lds_bytes(MT);
-    auto kernel = dk::shared_gemm_kernel<MT, W, 1, 2, EPI, NORM, Q4>;
+    auto kernel = dk::shared_gemm_kernel<MT, W, 1, 2, EPI, NORM, Q4, PACK>;
     static bool lds_allowed = false;   // above 64 KB together with the kernel's static LDS: ask once
     if (!lds_allowed) {
         DK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -572,9 +607,10 @@ dk_status launch_shared_gemm(const dk::GemmArgs &a, int Bp, const GemmPlan &p, h
         return fail(DK_E_INVALID_ARG, "no shared-activation 4-bit GEMM for %d rows and %d waves", Bp, p.w);
     }
     // instances: 8 waves for q | k | v, the lm_head and the gate/up pair, 4 waves for the residual
-    // projections (and the gate/up pair of a large model at 16 rows)
-    if constexpr (EPI == dk::GEPI_STORE || EPI == dk::GEPI_SWIGLU) {
+    // projections (and the gate/up pair of a large model up to 16 rows)
+    if constexpr (EPI == dk::GEPI_STORE)
         if (p.w == 8 && mt == 1) return launch_shared_gemm_inst<1, 8, EPI, NORM>(a, p.slices, st);
+    if constexpr (EPI == dk::GEPI_STORE || EPI == dk::GEPI_SWIGLU) {
         if (p.w == 8 && mt == 2) return launch_shared_gemm_inst<2, 8, EPI, NORM>(a, p.slices, st);
         if (p.w == 8 && mt == 3) return launch_shared_gemm_inst<3, 8, EPI, NORM>(a, p.slices, st);
         if (p.w == 8 && mt == 4) return launch_shared_gemm_inst<4, 8, EPI, NORM>(a, p.slices, st);
@@ -597,19 +633,18 @@ dk_status launch_gemm(const dk::GemmArgs &a, int Bp, hipStream_t st)
     constexpr int NM = (EPI == dk::GEPI_SWIGLU) ? 2 : 1;
     // hidden and ffn sizes (check_config): the epilogue moves their elements in fours without a narrow path
     if (EPI != dk::GEPI_STORE && a.N % 8) return fail(DK_E_UNSUPPORTED_SHAPE, "GEMM with %d output rows (a multiple of 8 is needed)", a.N);
-    const GemmPlan plan = gemm_plan(EPI, a.N, a.K, Bp, a.q4 != 0);
+    const GemmPlan plan = gemm_plan(EPI, a.N, a.K, Bp, a.q4 != 0, a.pack);
     if (plan.w) return launch_shared_gemm<EPI, NORM>(a, Bp, plan, st);
     // the variant of the K-split-per-wave kernel (dk_gemm_plan.h)
-    const dkplan::SkinnyVariant v = dkplan::skinny_variant(EPI, a.N, Bp, a.q4 != 0, device_cus());
+    const dkplan::SkinnyVariant v = dkplan::skinny_variant(EPI, a.N, a.K, Bp, a.q4 != 0, a.pack != 0, device_cus());
 #define DK_SKINNY_CASE(MT_, KS_, RT_)                                                     \
     if (v.mt == MT_ && v.ks == KS_ && v.rt == RT_) return launch_gemm_cfg<MT_, KS_, RT_, EPI, NORM>(a, st, v.groups)
-    if constexpr (NM == 1) {
-        DK_SKINNY_CASE(1, 8, 4);
-        DK_SKINNY_CASE(1, 8, 2);
-        DK_SKINNY_CASE(1, 2, 1);
-        DK_SKINNY_CASE(2, 8, 2);
-    }
+    if constexpr (NM == 1) DK_SKINNY_CASE(2, 8, 2);
+    if constexpr (EPI == dk::GEPI_RESID) DK_SKINNY_CASE(1, 2, 1);
     DK_SKINNY_CASE(1, 8, 1);
+    DK_SKINNY_CASE(1, 8, 2);
+    DK_SKINNY_CASE(1, 4, 1);
+    DK_SKINNY_CASE(1, 4, 2);
     DK_SKINNY_CASE(2, 8, 1);
     DK_SKINNY_CASE(3, 4, 1);
     DK_SKINNY_CASE(4, 4, 1);
@@ -811,7 +846,7 @@ const char *dk_last_error(void) { return g_err; }
 
 // The kernel revisions change whenever a kernel's memory behaviour changes; the
 // benchmark quotes stored counter measurements only for a matching revision.
-const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r13, attention r9, moe r4, fused r9, prefill r2, sample r3)"; }
+const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r14, attention r10, moe r4, fused r9, prefill r2, sample r3)"; }
 
 // ------------------------------------------------------------------- pool --
 dk_status dk_kv_pool_bytes(const dk_model_config *cfg, int32_t num_blocks, int32_t block_size,
@@ -1353,6 +1388,14 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
     uint16_t *xhi = reinterpret_cast<uint16_t *>(ws + w.xhi), *xlo = reinterpret_cast<uint16_t *>(ws + w.xlo);
     uint16_t *ahi = reinterpret_cast<uint16_t *>(ws + w.ahi), *alo = reinterpret_cast<uint16_t *>(ws + w.alo);
     uint16_t *fhi = reinterpret_cast<uint16_t *>(ws + w.fhi), *flo = reinterpret_cast<uint16_t *>(ws + w.flo);
+    uint16_t *x3 = nullptr, *a3 = nullptr, *f3 = nullptr;
+    if (w.pack) {   // the other terms lie in further columns of the first one's operand
+        const int next = dk::kPackCols(w.pack) * 8;
+        xlo = xhi + next;
+        alo = ahi + next;
+        if (c.n_experts == 0) flo = fhi + next;
+        if (w.pack == 3) { x3 = xlo + next; a3 = alo + next; f3 = flo + next; }
+    }
     float *ssq = reinterpret_cast<float *>(ws + w.ssq);
 
     const int H = c.hidden, d = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads;
@@ -1379,6 +1422,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             e.gain = u16(model->layers[0].g_attn);
             e.xhi = xhi;
             e.xlo = xlo;
+            e.x3 = x3;
             e.ssq_out = ssq;
         }
         std::memcpy(e.inv_freq, model->inv_freq, sizeof e.inv_freq);
@@ -1396,6 +1440,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = H;
             g.B = B;
             g.q4 = model->q4;
+            g.pack = w.pack;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = xhi;
@@ -1430,6 +1475,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             if (batched) {
                 a.out_hi = ahi;
                 a.out_lo = alo;
+                a.out_x3 = a3;
             }
             a.part = part;
             a.tickets = tickets;
@@ -1467,7 +1513,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             a.scale = (float)(1.0 / std::sqrt((double)d));
             a.eps = eps;
             a.n_rows = B;
-            if (prefill && batched) {
+            if (prefill && batched && w.pack != 3) {
                 // rows of one sequence: 16 / G of them share every K/V tile
                 const int G = nq / nkv;
                 a.chunk_tokens = w.pf_chunk_tokens;
@@ -1491,6 +1537,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = nq * d;
             g.B = B;
             g.q4 = model->q4;
+            g.pack = w.pack;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = ahi;
@@ -1499,6 +1546,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.gain_next = u16(L.g_mlp);
             g.ohi = xhi;
             g.olo = xlo;
+            g.ox3 = x3;
             g.ssq_out = ssq;
             if ((s = launch_gemm<dk::GEPI_RESID, false>(g, w.Bp, st)) != DK_OK) return s;
         } else {
@@ -1629,6 +1677,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = H;
             g.B = B;
             g.q4 = model->q4;
+            g.pack = w.pack;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = xhi;
@@ -1638,6 +1687,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.eps = eps;
             g.ohi = fhi;
             g.olo = flo;
+            g.ox3 = f3;
             if ((s = launch_gemm<dk::GEPI_SWIGLU, true>(g, w.Bp, st)) != DK_OK) return s;
             dk::GemmArgs h{};
             h.W = u16(L.w_down);
@@ -1645,6 +1695,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             h.K = c.ffn;
             h.B = B;
             h.q4 = model->q4;
+            h.pack = w.pack;
             h.kpart = kpart;
             h.ktickets = ktickets;
             h.xhi = fhi;
@@ -1653,6 +1704,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             h.gain_next = gain_after;
             h.ohi = xhi;
             h.olo = xlo;
+            h.ox3 = x3;
             h.ssq_out = ssq;
             if ((s = launch_gemm<dk::GEPI_RESID, false>(h, w.Bp, st)) != DK_OK) return s;
         } else {
@@ -1688,6 +1740,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
         g.K = H;
         g.B = B;
         g.q4 = model->q4;
+        g.pack = w.pack;
         g.kpart = kpart;
         g.ktickets = ktickets;
         g.xhi = xhi;
@@ -1853,7 +1906,7 @@ dk_status dk_gemm_plan_query(int32_t epilogue, int32_t N, int32_t K, int32_t B, 
     if (epilogue < 0 || epilogue > 2 || N < 1 || K < 1 || B <= kMaxGemvBatch || B > DK_MAX_BATCH || compute_units < 0)
         return fail(DK_E_INVALID_ARG, "epilogue %d, N %d, K %d, B %d, compute units %d", epilogue, N, K, B, compute_units);
     const int Bp = (B + 15) / 16 * 16;
-    const GemmPlan p = dkplan::gemm_plan(epilogue, N, K, Bp, four_bit != 0, compute_units ? compute_units : device_cus(),
+    const GemmPlan p = dkplan::gemm_plan(epilogue, N, K, Bp, four_bit != 0, B <= kPackRows2 && K % 128 == 0, compute_units ? compute_units : device_cus(),
                                          out_estimate_us);
     *out_waves = p.w;
     *out_slices = p.slices;

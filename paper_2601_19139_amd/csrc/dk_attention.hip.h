@@ -20,7 +20,7 @@ struct EmbedArgs {
     // batched path (null otherwise): (x * gain) as bf16 hi/lo in act_offset() order and the
     // row's sum of x^2 in ssq_out[b], for the first matrix-core GEMM
     const uint16_t *gain;
-    uint16_t *xhi, *xlo;
+    uint16_t *xhi, *xlo, *x3;   // x3: the third of three terms (few rows), or null
     float *ssq_out;
     double inv_freq[64];    // theta^(-2i/d), i < d/2
 };
@@ -41,20 +41,22 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a)
         if (a.xhi != nullptr) {
             float g[8];
             unpack8(ld16(a.gain + k), g);
-            uint32_t hw[4], lw[4];
+            uint32_t hw[4], lw[4], tw[4];
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 ss += f[2 * e] * f[2 * e] + f[2 * e + 1] * f[2 * e + 1];
                 const float v0 = f[2 * e] * g[2 * e], v1 = f[2 * e + 1] * g[2 * e + 1];
                 const uint32_t h0 = f32_to_bf16_rne(v0), h1 = f32_to_bf16_rne(v1);
-                const uint32_t l0 = f32_to_bf16_rne(v0 - __uint_as_float(h0 << 16));
-                const uint32_t l1 = f32_to_bf16_rne(v1 - __uint_as_float(h1 << 16));
+                const float r0 = v0 - __uint_as_float(h0 << 16), r1 = v1 - __uint_as_float(h1 << 16);
+                const uint32_t l0 = f32_to_bf16_rne(r0), l1 = f32_to_bf16_rne(r1);
+                tw[e] = f32x2_to_bf16x2_rne(r0 - __uint_as_float(l0 << 16), r1 - __uint_as_float(l1 << 16));
                 hw[e] = h0 | (h1 << 16);
                 lw[e] = l0 | (l1 << 16);
             }
             const int64_t oo = act_offset(b, k, (a.H + 127) >> 7);
             *reinterpret_cast<uint4 *>(a.xhi + oo) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
             *reinterpret_cast<uint4 *>(a.xlo + oo) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+            if (a.x3 != nullptr) *reinterpret_cast<uint4 *>(a.x3 + oo) = make_uint4(tw[0], tw[1], tw[2], tw[3]);
         }
     }
     if (a.xhi != nullptr) {
@@ -147,6 +149,7 @@ struct AttnArgs {
     const int *seq_lens;
     float *out;              // [B][nq*d] float32 result, or
     uint16_t *out_hi, *out_lo;  // (batched path) the result as bf16 hi/lo in act_offset() order
+    uint16_t *out_x3;           // ... and the third of three terms (few rows), or null
     float *part;             // [B][nkv][max_chunks][G][d+2]
     int *tickets;            // [B*nkv], zero before the launch, zero after
     int max_blocks, num_blocks, layer, nq, nkv;
@@ -227,6 +230,12 @@ __device__ __forceinline__ void store_attn_out(const AttnArgs &a, int b, int k, 
     } else {
         a.out[(int64_t)b * width + k] = v;
     }
+}
+// ... and its third term, where three are kept (few rows)
+__device__ __forceinline__ void store_attn_x3(const AttnArgs &a, int b, int k, int width, float v)
+{
+    const float r = v - bf16_to_f32(f32_to_bf16_rne(v));
+    a.out_x3[act_offset(b, k, (width + 127) >> 7)] = f32_to_bf16_rne(r - bf16_to_f32(f32_to_bf16_rne(r)));
 }
 
 // One head held as 8 dims per lane by an aligned group of TPR = D/8 lanes:
@@ -563,6 +572,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
             if (dim == 0) { pp[D] = mn; pp[D + 1] = ls; }
         } else if (nact == 1) {
             store_attn_out(a, b, (j * G + g) * D + dim, a.nq * D, os / ls);
+            if (a.out_x3 != nullptr) store_attn_x3(a, b, (j * G + g) * D + dim, a.nq * D, os / ls);
         } else {
             st_coherent(pp + dim, os);
             if (dim == 0) { st_coherent(pp + D, mn); st_coherent(pp + D + 1, ls); }
@@ -587,6 +597,13 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
     for (int i = 0; i < (G * D + 255) / 256; i++) {
         const int idx = tid + 256 * i;
         if (idx < G * D) store_attn_out(a, b, j * G * D + idx, a.nq * D, mv[i]);
+    }
+    if (a.out_x3 != nullptr) {
+#pragma unroll
+        for (int i = 0; i < (G * D + 255) / 256; i++) {
+            const int idx = tid + 256 * i;
+            if (idx < G * D) store_attn_x3(a, b, j * G * D + idx, a.nq * D, mv[i]);
+        }
     }
     if (tid == 0)
         __hip_atomic_store(&a.tickets[b * a.nkv + j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -47,6 +47,7 @@ struct GemmArgs {
     const uint16_t *W2;      // GEPI_SWIGLU: the "up" matrix, same format as W
     int N, K, B;             // B valid batch rows (<= 16*MT)
     int q4;                  // host side only: W / W2 are packed 4-bit matrices (selects the Q4 kernels)
+    int pack;                // host side only: the terms of an activation share one operand (2 or 3, see kPackCols)
     const uint16_t *xhi;     // hi part of the input, bf16 in act_offset() order
     const uint16_t *xlo;     // lo part
     // NORM: sum over p < n_part of ssq_in[p][n] = sum_k x[n][k]^2
@@ -60,6 +61,7 @@ struct GemmArgs {
     // GEPI_SWIGLU and GEPI_RESID: result as hi/lo bf16 in act_offset() order (K = N)
     // for the next GEMM
     uint16_t *ohi, *olo;
+    uint16_t *ox3;           // three terms: the third one
     // GEPI_RESID: xres[B][N] += D; the hi/lo output is (xres * gain_next); the
     // sum of xres^2 over each 16-row tile and batch row goes to ssq_out[tile][n]
     float *xres;
@@ -82,6 +84,34 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uin
 {
     hi = f32x2_to_bf16x2_rne(a, b);
     lo = f32x2_to_bf16x2_rne(a - bf16lo(hi), b - bf16hi(hi));
+}
+
+// x = hi + mid + lo: all 24 bits of a float32
+__device__ __forceinline__ void split_bf16x3(float x, uint16_t &hi, uint16_t &mid, uint16_t &lo)
+{
+    hi = f32_to_bf16_rne(x);
+    const float r = x - bf16_to_f32(hi);
+    mid = f32_to_bf16_rne(r);
+    lo = f32_to_bf16_rne(r - bf16_to_f32(mid));
+}
+
+// Few batch rows: a 16-column operand holds all terms of every row side by side - term i of row n in column
+// i * kPackCols(terms) + n, so up to eight rows of two terms or five of three.  One matrix product then does what two
+// (three) did, the activations are half (a half) of the bytes, and a row's terms are added up across the columns
+// afterwards.  In act_offset() order the next term of a row lies kPackCols * 8 elements further on: writers only see
+// other pointers.  Columns that belong to no row hold whatever the buffer held; a column never meets another.
+constexpr int kPackCols(int terms) { return terms == 2 ? 8 : 5; }
+
+// The sum over a row's terms, smallest first, for the lane of the row's first column.
+template <int PACK>
+__device__ __forceinline__ float pack_sum(float v, int lane)
+{
+    if (PACK == 0) return v;
+    const int row = lane & 48, ln = lane & 15;
+    const float v1 = __shfl(v, row | ((ln + kPackCols(PACK)) & 15));
+    if (PACK == 2) return v1 + v;
+    const float v2 = __shfl(v, row | ((ln + 2 * kPackCols(PACK)) & 15));
+    return (v2 + v1) + v;
 }
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(const uint4 &u)
@@ -131,7 +161,7 @@ __device__ __forceinline__ void load_resid4(const float *xrow, int r, int N, flo
 // N or an address that is not 16-byte aligned; those go element by element.  A narrow path in the other two, which
 // nothing reached, cost registers and branches there: 16 rows of the 0.6B shape 1225 -> 1200 us per step without it,
 // 700 tokens of the 3B shape with 4-bit weights 34.4 -> 33.5 ms.
-template <int MT, int EPI>
+template <int MT, int EPI, int PACK = 0>
 __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_tile, int lane,
                                                    const float (&v)[MT][(EPI == GEPI_SWIGLU) ? 2 : 1][4],
                                                    const float (&xr)[MT][4], const float (&gn)[4])
@@ -152,7 +182,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
         const int rr = row0 + 4 * lg;
         float sq = 0.f;
         float out[4];
-        uint32_t hi[2], lo[2];   // two elements a word
+        uint32_t hi[2], lo[2], x3[2];   // two elements a word
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             if (EPI == GEPI_SWIGLU) {
@@ -166,7 +196,16 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
 #pragma unroll
             for (int h = 0; h < 2; h++) {
                 const float g0 = EPI == GEPI_RESID ? gn[2 * h] : 1.f, g1 = EPI == GEPI_RESID ? gn[2 * h + 1] : 1.f;
-                split_bf16x2(out[2 * h] * g0, out[2 * h + 1] * g1, hi[h], lo[h]);
+                if constexpr (PACK == 3) {
+                    uint16_t t[2][3];
+                    split_bf16x3(out[2 * h] * g0, t[0][0], t[0][1], t[0][2]);
+                    split_bf16x3(out[2 * h + 1] * g1, t[1][0], t[1][1], t[1][2]);
+                    hi[h] = t[0][0] | (uint32_t)t[1][0] << 16;
+                    lo[h] = t[0][1] | (uint32_t)t[1][1] << 16;
+                    x3[h] = t[0][2] | (uint32_t)t[1][2] << 16;
+                } else {
+                    split_bf16x2(out[2 * h] * g0, out[2 * h + 1] * g1, hi[h], lo[h]);
+                }
             }
         }
         if (wide && nvalid && rr < N) {
@@ -177,6 +216,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
                 const int64_t oo = act_offset(n, rr, onks);
                 *reinterpret_cast<uint2 *>(a.ohi + oo) = make_uint2(hi[0], hi[1]);
                 *reinterpret_cast<uint2 *>(a.olo + oo) = make_uint2(lo[0], lo[1]);
+                if (PACK == 3) *reinterpret_cast<uint2 *>(a.ox3 + oo) = make_uint2(x3[0], x3[1]);
                 if (EPI == GEPI_RESID)
                     *reinterpret_cast<float4 *>(a.xres + (int64_t)n * N + rr) = make_float4(out[0], out[1], out[2], out[3]);
             }
@@ -270,9 +310,11 @@ struct SsqPartials {
 // [lane group lg][sub-step s] whose nibble j (bits 4j..4j+3) is column s*32 + lg*8 + j;
 // after the N rows, per 16-row tile and K-step 128 bytes [lg][group h of the step][row 4*lg+i]
 // of (scale, bias) bf16 pairs - the order in which the accumulator lanes need them.
-template <int MT, int KS, int RT, int PD, int EPI, bool NORM, bool KALIGNED, bool Q4 = false>
+// PACK (MT = 1, KALIGNED): xhi is one operand with PACK terms of every row (kPackCols).
+template <int MT, int KS, int RT, int PD, int EPI, bool NORM, bool KALIGNED, bool Q4 = false, int PACK = 0>
 __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
 {
+    static_assert(PACK == 0 || (MT == 1 && KALIGNED && !(Q4 && PACK == 3)), "packed terms fill one 16-column operand");
     static_assert(!Q4 || KALIGNED, "4-bit weights need whole K-steps");
     constexpr int NM = (EPI == GEPI_SWIGLU) ? 2 : 1;
     constexpr int NA = NM * RT;   // weight tiles (accumulator sets) per wave
@@ -328,7 +370,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
     // multiple of PD; a step past the end of K reads clamped (valid, cached)
     // addresses and is not used.
     struct Stage {
-        uint4 wa[NA][4], bh[MT][4], bl[MT][4];
+        uint4 wa[NA][4], bh[MT][4], bl[PACK ? 1 : MT][4];
     };
     // Up to 16 batch rows block b begins b steps into K and wraps around: started together at the same column, the
     // blocks would ask the same few memory channels at the same time all along K (201 MB read this way and nothing
@@ -360,7 +402,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
                 for (int t = 0; t < MT; t++) {
                     const int64_t xo = xb + ((int64_t)t * nks * 4 + s) * 512;
                     st.bh[t][s] = ld16(a.xhi + xo);
-                    st.bl[t][s] = ld16(a.xlo + xo);
+                    if (!PACK) st.bl[t][s] = ld16(a.xlo + xo);
                 }
             it_i++;
             return;
@@ -383,7 +425,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
             for (int t = 0; t < MT; t++) {
                 const int64_t xo = xb + ((int64_t)t * nks * 4 + s) * 512;
                 st.bh[t][s] = ld16(a.xhi + xo);
-                st.bl[t][s] = ld16(a.xlo + xo);
+                if (!PACK) st.bl[t][s] = ld16(a.xlo + xo);
             }
         }
         it_i++;
@@ -401,9 +443,9 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
 #pragma unroll
                 for (int t = 0; t < MT; t++) {
                     S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bh[t][2 * h]), zero, 0, 0, 0);
-                    S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bl[t][2 * h]), S[t], 0, 0, 0);
+                    if (!PACK) S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bl[t][2 * h]), S[t], 0, 0, 0);
                     S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bh[t][2 * h + 1]), S[t], 0, 0, 0);
-                    S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bl[t][2 * h + 1]), S[t], 0, 0, 0);
+                    if (!PACK) S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(st.bl[t][2 * h + 1]), S[t], 0, 0, 0);
                 }
 #pragma unroll
                 for (int m = 0; m < NA; m++) {
@@ -420,9 +462,9 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
 #pragma unroll
                     for (int t = 0; t < MT; t++) {
                         f32x4_t D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(st.bh[t][2 * h]), zero, 0, 0, 0);
-                        D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(st.bl[t][2 * h]), D, 0, 0, 0);
+                        if (!PACK) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), as_bf16x8(st.bl[t][2 * h]), D, 0, 0, 0);
                         D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(st.bh[t][2 * h + 1]), D, 0, 0, 0);
-                        D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(st.bl[t][2 * h + 1]), D, 0, 0, 0);
+                        if (!PACK) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), as_bf16x8(st.bl[t][2 * h + 1]), D, 0, 0, 0);
 #pragma unroll
                         for (int i = 0; i < 4; i++)
                             acc[m][t][i] = fmaf(sc[i], D[i], fmaf(b2[i], S[t][i], acc[m][t][i]));
@@ -431,7 +473,19 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
             }
             return;
         }
-        if (KALIGNED) {
+        if constexpr (PACK == 3) {
+            // A step's sum on its own, then onto the total: half the rounding error of one long chain in the matrix
+            // cores, and below that of the vector kernel (relative error against float64, K = 1024 / 4096 / 12288:
+            // 0.8 / 0.9 / 1.2e-7; one chain 1.0 / 1.9 / 3.3e-7, vector kernel 0.9 / 1.1 / 1.4e-7).
+#pragma unroll
+            for (int m = 0; m < NA; m++) {
+                f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.wa[m][s]), as_bf16x8(st.bh[0][s]), d, 0, 0, 0);
+                acc[m][0] += d;
+            }
+        } else if constexpr (KALIGNED) {
 #pragma unroll
             for (int s = 0; s < 4; s++)
 #pragma unroll
@@ -440,10 +494,11 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
                     for (int m = 0; m < NA; m++) {
                         acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                             as_bf16x8(st.wa[m][s]), as_bf16x8(st.bh[t][s]), acc[m][t], 0, 0, 0);
-                        acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf16x8(st.wa[m][s]), as_bf16x8(st.bl[t][s]), acc[m][t], 0, 0, 0);
+                        if (!PACK)
+                            acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf16x8(st.wa[m][s]), as_bf16x8(st.bl[t][s]), acc[m][t], 0, 0, 0);
                     }
-        } else {
+        } else if constexpr (!KALIGNED) {
             const int kb = ks * 128 + lg * 8;
 #pragma unroll
             for (int s = 0; s < 4; s++) {
@@ -527,7 +582,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
                     float s = 0.f;
 #pragma unroll
                     for (int w = 0; w < KS; w++) s += rb[w][m * RT + rt][t][i][lane];
-                    v[t][m][i] = s;
+                    v[t][m][i] = pack_sum<PACK>(s, lane);
                 }
             if (NORM) {
                 float s = 0.f;
@@ -540,7 +595,7 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
                     for (int i = 0; i < 4; i++) v[t][m][i] *= inv;
             }
         }
-        gemm_tile_epilogue<MT, EPI>(a, out_tile, lane, v, xr, gn);
+        gemm_tile_epilogue<MT, EPI, PACK>(a, out_tile, lane, v, xr, gn);
     }
 }
 

@@ -1,8 +1,8 @@
-// Which kernel a batched (5..64 rows) weight-streaming GEMM takes - host code only.
+// Which kernel a batched weight-streaming GEMM (2..64 rows) takes - host code only.
 //
-// Two kernels exist (dk_gemm.hip.h, dk_gemm_shared.hip.h).  The choice between them, and the number
-// of K slices of the second, comes from an estimate of each candidate's duration, not from a table
-// of shapes.  The estimate is a latency/occupancy model of a weight stream:
+// Two kernels exist (dk_gemm.hip.h, dk_gemm_shared.hip.h).  Up to 16 batch rows the choice follows a few rules, given
+// with both sides at gemm_plan_16().  Above, the choice between them, and the number of K slices of the second, comes
+// from an estimate of each candidate's duration.  The estimate is a latency/occupancy model of a weight stream:
 //
 //   * a wave keeps a fixed number of bytes in flight, so a block streams at (waves x rate per wave)
 //     until the compute units that are busy together reach the device's rate;
@@ -33,24 +33,31 @@ struct GemmPlan { int w, slices; };   // w == 0: skinny_gemm_kernel; else shared
 // wave, `groups` groups of 16 batch rows across blockIdx.y (then MT == 1).
 struct SkinnyVariant { int mt, ks, rt, groups; };
 
-// A wave that handles several row tiles per K-step reuses the activation operand it has loaded; it pays
-// while enough blocks remain to fill the chip: four tiles per wave from 16 blocks per compute unit on,
-// two from 1.25.  Residual projections with at most one block per compute unit take two-wave blocks
-// (less to add up across waves).  A small matrix at 32..64 rows whose row tiles x groups of 16 rows
-// still make at most two blocks per compute unit runs the 16-row kernel over all groups at once.
-inline SkinnyVariant skinny_variant(int epi, int N, int Bp, bool q4, int cus)
+// Up to 16 batch rows what bounds a block is the bytes its compute unit fetches, about 40 GB/s of weights and
+// activations together.
+//   * Row tiles per wave: two - the activations once for both - where that leaves the busiest compute unit no more row
+//     tiles than one each would: plain stores from 1.25 tiles per compute unit on (3B shape, q/k/v, 320 tiles, 16 rows
+//     15.3 -> 12.6 us; 0.6B shape, 256 tiles 5.2 -> 6.1), the gate/up pair between one and two (512 tiles 24.2 -> 21.9
+//     us, 384 15.9 -> 14.3; 192 6.3 -> 8.4, 608 30.9 -> 35.1).
+//   * Waves: four; a second block on the same compute unit hides the start and the end of the first, and steps that
+//     do not divide among the waves cost less (eight -> four, 3B shape, K = 3072: gate/up 25.4 -> 21.9 us, q/k/v 14.1 ->
+//     12.6; 4 rows with packed terms 23.7 -> 21.2 and 12.4 -> 11.0).  Unpacked terms: eight where a wave's two steps in
+//     flight come out even (K = 2048: q/k/v 9.3 -> 8.9; 4 bit 7.3 -> 7.2, gate/up 10.3 -> 9.9) or are its only one
+//     (K = 1024, whole step of the 0.6B shape 1191 -> 1176), two for residual projections that make at most one block
+//     per compute unit (less to add up: K = 2048 6.4 -> 6.3, 4096 11.0 -> 10.8).
+// Above 16 rows: a small matrix whose row tiles x groups of 16 rows still make at most two blocks per compute unit runs
+// the 16-row kernel over all groups at once, residual projections with two-wave blocks.
+inline SkinnyVariant skinny_variant(int epi, int N, int K, int Bp, bool q4, bool pack, int cus)
 {
     const int tiles = (N + 15) / 16, mt = Bp / 16;
     const bool one_matrix = epi != EPI_SWIGLU;
-    const int groups = (mt >= 2 && tiles * mt <= 2 * cus) ? mt : 1;
-    switch (groups > 1 ? 1 : mt) {
-        case 1:
-            if (one_matrix) {
-                if (tiles >= 16 * cus) return {1, 8, 4, groups};
-                if (tiles >= cus + cus / 4) return {1, 8, 2, groups};
-                if (tiles <= cus && epi == EPI_RESID && !q4) return {1, 2, 1, groups};
-            }
-            return {1, 8, 1, groups};
+    if (mt == 1) {
+        const bool two = one_matrix ? tiles >= cus + cus / 4 : tiles > cus && tiles <= 2 * cus;
+        if (!pack && epi == EPI_RESID && !q4 && tiles <= cus) return {1, 2, 1, 1};
+        return {1, !pack && (K <= 1024 || K % 2048 == 0) ? 8 : 4, two ? 2 : 1, 1};
+    }
+    if (tiles * mt <= 2 * cus) return {1, epi == EPI_RESID && !q4 ? 2 : 8, 1, mt};
+    switch (mt) {
         case 2:
             if (one_matrix && tiles >= 4 * cus) return {2, 8, 2, 1};
             return {2, 8, 1, 1};
@@ -117,50 +124,85 @@ inline int shared_gemm_slices(int N, int K, int w, int cus)
     return std::max(1, std::min(std::min(cus / row_blocks, 8), K / 512));
 }
 
-// 4-bit weights: thresholds from a sweep of the 4-bit kernels over the same shapes (their streams are a
+// 4-bit weights above 16 rows: thresholds from a sweep of the 4-bit kernels over the same shapes (their streams are a
 // quarter as long and their steps carry the dequantisation, which this model's constants do not cover):
 // the lm_head at every batch size; q | k | v from 32 rows on; the gate/up pair and the down projection of
 // the 3B / 8B shapes; never the output projection.
-inline GemmPlan gemm_plan_q4(int epi, int N, int K, int mt)
+inline GemmPlan gemm_plan_q4(int epi, int N, int K)
 {
     const long long elems = (long long)N * K;
     if (epi == EPI_STORE) {
         if ((N + 15) / 16 >= 4096) return {8, 1};
-        if (mt >= 2 && elems >= (8ll << 20)) return {8, 4};
+        if (elems >= (8ll << 20)) return {8, 4};
     } else if (epi == EPI_SWIGLU) {
         if (elems >= (40ll << 20)) return {8, 2};
         if (elems >= (20ll << 20)) return {8, 4};
     } else {
-        if (elems >= (mt >= 2 ? (20ll << 20) : (40ll << 20))) return {4, 8};
+        if (elems >= (20ll << 20)) return {4, 8};
     }
     return {0, 1};
 }
 
-// The plan: the candidate with the smallest estimate.  Candidates are the skinny kernel (its variant by
+// Up to 16 batch rows.  Sweep of the 3B, 8B, 0.6B, 30B-A3B layer matrices and of layers of 2560 x 9728 and 1536 x 8960;
+// `pack`: the terms of an activation share one operand, so the activations, which a wave of skinny_gemm_kernel fetches
+// for itself, are half as many bytes and the line moves.  us, skinny / shared:
+//   * long residual projections, whose few row tiles leave a compute unit one long block, are cut into K slices:
+//     K = 6144 14.4 / 11.2, 8192 18.2 / 14.0, 12288 27.7 / 22.3, K = 4096 equal, 3072 8.8 / 9.0; packed 8192 14.2 / 13.9,
+//     12288 equal, 6144 equal, 4096 8.8 / 10.8; 4 bit 8192 13.2 / 12.5, 12288 19.0 / 16.1, 6144 equal; 4 bit packed
+//     never (8192 9.4 / 12+);
+//   * gate/up pairs of more than two row tiles per compute unit: 608 tiles 30.9 / 25.3, 768 equal; packed only where the
+//     tiles do not fill their rounds of blocks (608: 26.7 / 24.7, 768: 37.0 / 42.0); 4 bit 608 17.6 / 15.3, 768 24.4 / 21.9,
+//     packed 768 equal.  Slices: the count that fills the compute units best (608 tiles, 3 / 4 / 5 slices: 25.3 / 29.3 /
+//     25.3 us; 768 tiles, 2 / 3 / 4 / 5: 46.7 / 48.9 / 42.2 / 46.0);
+//   * the lm_head, where the stream is long enough for one slice: 151936 x 1024 60 / 53, x 4096 237 / 212; packed 50 / 53,
+//     205 / 211; 4 bit 36 / 30, 132 / 100, packed 30 / 25, 101 / 87.
+inline GemmPlan gemm_plan_16(int epi, int N, int K, bool q4, bool pack, int cus)
+{
+    const int tiles = (N + 15) / 16;
+    if (epi == EPI_STORE) return tiles >= (q4 ? 16 : 4) * cus && (q4 || !pack) ? GemmPlan{8, 1} : GemmPlan{0, 1};
+    if (epi == EPI_RESID) {
+        if (K < (q4 || pack ? 8192 : 4097) || (q4 && pack)) return {0, 1};
+        return {4, q4 ? 8 : shared_gemm_slices(N, K, 4, cus)};
+    }
+    const int rounds = (tiles + cus - 1) / cus;
+    if (rounds <= 2 || (pack && (q4 || tiles * 20 >= rounds * cus * 17))) return {0, 1};
+    const int w = q4 ? 8 : 4, row_blocks = (tiles + w - 1) / w;
+    GemmPlan best{w, 1};
+    if (row_blocks >= 2 * cus) return best;
+    double best_fill = 0.0;
+    for (int s = 2; s <= std::min(5, K / 512); s++) {
+        const int blocks = row_blocks * s;
+        const double fill = (double)blocks / ((double)cus * ((blocks + cus - 1) / cus));
+        if (fill > best_fill) { best_fill = fill; best.slices = s; }
+    }
+    return best;
+}
+
+// The plan.  Above 16 rows: the candidate with the smallest estimate.  Candidates are the skinny kernel (its variant by
 // skinny_variant) and the shared kernel in the block widths that are instantiated for the epilogue - 8
-// waves for plain stores and the gate/up pair (4 as well at 16 rows), 4 waves for residual projections -
+// waves for plain stores and the gate/up pair, 4 waves for residual projections -
 // with shared_gemm_slices() slices (one slice when the row blocks alone make several rounds: the lm_head).
-// est_us (optional) receives the estimate of the winner.
-inline GemmPlan gemm_plan(int epi, int N, int K, int Bp, bool q4, int cus, double *est_us = nullptr)
+// est_us (optional) receives the estimate for the plan.
+inline GemmPlan gemm_plan(int epi, int N, int K, int Bp, bool q4, bool pack, int cus, double *est_us = nullptr)
 {
     const int mt = Bp / 16;
     if (est_us) *est_us = 0.0;
     if (K % 128) return {0, 1};
-    if (q4) return gemm_plan_q4(epi, N, K, mt);
     const int n_mat = epi == EPI_SWIGLU ? 2 : 1;
-    GemmPlan best{0, 1};
-    double best_us = skinny_gemm_us(N, K, n_mat, skinny_variant(epi, N, Bp, false, cus), cus);
-    auto consider = [&](int w) {
-        const int row_blocks = ((N + 15) / 16 + w - 1) / w;
-        const int s = row_blocks >= 2 * cus ? 1 : shared_gemm_slices(N, K, w, cus);
-        const double us = shared_gemm_us(N, K, n_mat, mt, w, s, cus);
-        if (us < best_us) { best_us = us; best = {w, s}; }
-    };
-    if (epi == EPI_RESID) consider(4);
-    else {
-        consider(8);
-        if (epi == EPI_SWIGLU && mt == 1) consider(4);
+    if (mt == 1) {
+        const GemmPlan p = gemm_plan_16(epi, N, K, q4, pack, cus);
+        if (est_us && !q4)
+            *est_us = p.w ? shared_gemm_us(N, K, n_mat, 1, p.w, p.slices, cus)
+                          : skinny_gemm_us(N, K, n_mat, skinny_variant(epi, N, K, Bp, false, pack, cus), cus);
+        return p;
     }
+    if (q4) return gemm_plan_q4(epi, N, K);
+    GemmPlan best{0, 1};
+    double best_us = skinny_gemm_us(N, K, n_mat, skinny_variant(epi, N, K, Bp, false, pack, cus), cus);
+    const int w = epi == EPI_RESID ? 4 : 8, row_blocks = ((N + 15) / 16 + w - 1) / w;
+    const int s = row_blocks >= 2 * cus ? 1 : shared_gemm_slices(N, K, w, cus);
+    const double us = shared_gemm_us(N, K, n_mat, mt, w, s, cus);
+    if (us < best_us) { best_us = us; best = {w, s}; }
     if (est_us) *est_us = best_us;
     return best;
 }

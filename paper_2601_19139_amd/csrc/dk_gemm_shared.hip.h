@@ -54,15 +54,16 @@ constexpr size_t shared_gemm_lds_bytes(int MT) { return (size_t)2 * 512 * MT * 1
 // in flight per wave.  K must be a multiple of 128.  grid = (ceil(tiles / (W*RT)), slices).
 // Q4: packed 4-bit weights, evaluated as in skinny_gemm_kernel's Q4 variant (codes through the matrix
 // cores, group sums of x from an all-ones operand, scale and bias applied to the fp32 tiles).
-template <int MT, int W, int RT, int PD, int EPI, bool NORM, bool Q4 = false>
+// PACK (MT = 1): xhi is one operand with PACK terms of every row, half of the pieces (both halves of an 8-wave block fetch them).
+template <int MT, int W, int RT, int PD, int EPI, bool NORM, bool Q4 = false, int PACK = 0>
 __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
 {
     constexpr int NM = (EPI == GEPI_SWIGLU) ? 2 : 1;
     constexpr int NA = NM * RT;
     constexpr int TPB = W * 64;
-    constexpr int PIECES = 512 * MT;          // 16-byte pieces of one step's activation tile (hi and lo)
-    static_assert(PIECES % TPB == 0, "every thread fetches the same number of pieces");
-    constexpr int PPT = PIECES / TPB;
+    constexpr int PIECES = PACK ? 256 : 512 * MT;   // 16-byte pieces of one step's activation tile (hi and lo)
+    static_assert((PACK == 0 && PIECES % TPB == 0) || (MT == 1 && TPB % 256 == 0), "every thread fetches the same number of pieces");
+    constexpr int PPT = PACK ? 1 : PIECES / TPB;
     extern __shared__ uint4 sm_act_dyn[];   // two slots of one step's activation tile (shared_gemm_lds_bytes)
     uint4 (*sm_act)[PIECES] = reinterpret_cast<uint4 (*)[PIECES]>(sm_act_dyn);
     __shared__ __align__(16) float sm_ssq[W][64];
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         ks = min(ks0 + (ks < niter ? ks : ks - niter), nks - 1);
 #pragma unroll
         for (int p = 0; p < PPT; p++) {
-            const int piece = p * TPB + tid;
+            const int piece = PACK ? (tid & 255) : p * TPB + tid;
             const int t = piece >> 9, lo = (piece >> 8) & 1, idx = piece & 255;
             st.act[p] = ld16((lo ? a.xlo : a.xhi) + (((int64_t)t * nks + ks) * 256 + idx) * 8);
         }
@@ -125,7 +126,8 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         if (it < 0 || it >= niter) return;   // a padding step (the same for the whole block)
         uint4 *slot = sm_act[it & 1];
 #pragma unroll
-        for (int p = 0; p < PPT; p++) slot[p * TPB + tid] = st.act[p];
+        for (int p = 0; p < PPT; p++)
+            if (!PACK || tid < 256) slot[p * TPB + tid] = st.act[p];
         // one barrier per step is enough with two slots: nobody can write this slot again
         // before every wave has passed the next step's barrier, i.e. has finished reading it
         __syncthreads();
@@ -150,19 +152,20 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
                 }
 #pragma unroll
                 for (int t = 0; t < MT; t++) {
-                    const uint4 bh0 = slot[t * 512 + (2 * h) * 64 + lane], bl0 = slot[t * 512 + 256 + (2 * h) * 64 + lane];
-                    const uint4 bh1 = slot[t * 512 + (2 * h + 1) * 64 + lane], bl1 = slot[t * 512 + 256 + (2 * h + 1) * 64 + lane];
+                    constexpr int LO = PACK ? 0 : 256;   // (packed: the lo operand does not exist and is not used)
+                    const uint4 bh0 = slot[t * 512 + (2 * h) * 64 + lane], bl0 = slot[t * 512 + LO + (2 * h) * 64 + lane];
+                    const uint4 bh1 = slot[t * 512 + (2 * h + 1) * 64 + lane], bl1 = slot[t * 512 + LO + (2 * h + 1) * 64 + lane];
                     // group sums of x for this lane's batch row (the same in all four accumulator rows)
                     f32x4_t S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bh0), zero, 0, 0, 0);
-                    S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bl0), S, 0, 0, 0);
+                    if (!PACK) S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bl0), S, 0, 0, 0);
                     S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bh1), S, 0, 0, 0);
-                    S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bl1), S, 0, 0, 0);
+                    if (!PACK) S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(one4), as_bf16x8(bl1), S, 0, 0, 0);
 #pragma unroll
                     for (int m = 0; m < NA; m++) {
                         f32x4_t D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c0[m]), as_bf16x8(bh0), zero, 0, 0, 0);
-                        D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c0[m]), as_bf16x8(bl0), D, 0, 0, 0);
+                        if (!PACK) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c0[m]), as_bf16x8(bl0), D, 0, 0, 0);
                         D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c1[m]), as_bf16x8(bh1), D, 0, 0, 0);
-                        D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c1[m]), as_bf16x8(bl1), D, 0, 0, 0);
+                        if (!PACK) D = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c1[m]), as_bf16x8(bl1), D, 0, 0, 0);
 #pragma unroll
                         for (int i = 0; i < 4; i++)
                             acc[m][t][i] = fmaf(sc[m][i], D[i], fmaf(bi[m][i], S[i], acc[m][t][i]));
@@ -171,17 +174,29 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
             }
             return;
         }
+        if constexpr (PACK == 3) {   // a step's sum on its own, then onto the total (see skinny_gemm_kernel)
+#pragma unroll
+            for (int m = 0; m < NA; m++) {
+                f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.wa[m][s]), as_bf16x8(slot[s * 64 + lane]), d, 0, 0, 0);
+                acc[m][0] += d;
+            }
+            return;
+        }
 #pragma unroll
         for (int s = 0; s < 4; s++)
 #pragma unroll
             for (int t = 0; t < MT; t++) {
-                const uint4 bh = slot[t * 512 + s * 64 + lane], bl = slot[t * 512 + 256 + s * 64 + lane];
+                const uint4 bh = slot[t * 512 + s * 64 + lane], bl = slot[t * 512 + (PACK ? 0 : 256) + s * 64 + lane];
 #pragma unroll
                 for (int m = 0; m < NA; m++) {
                     acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.wa[m][s]), as_bf16x8(bh),
                                                                         acc[m][t], 0, 0, 0);
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.wa[m][s]), as_bf16x8(bl),
-                                                                        acc[m][t], 0, 0, 0);
+                    if (!PACK)
+                        acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.wa[m][s]), as_bf16x8(bl),
+                                                                            acc[m][t], 0, 0, 0);
                 }
             }
     };
@@ -294,8 +309,8 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
 #pragma unroll
             for (int m = 0; m < NM; m++)
 #pragma unroll
-                for (int i = 0; i < 4; i++) v[t][m][i] = acc[m * RT + r][t][i] * inv[t];
-        gemm_tile_epilogue<MT, EPI>(a, tile, lane, v, xr[r], gn[r]);
+                for (int i = 0; i < 4; i++) v[t][m][i] = pack_sum<PACK>(acc[m * RT + r][t][i], lane) * inv[t];
+        gemm_tile_epilogue<MT, EPI, PACK>(a, tile, lane, v, xr[r], gn[r]);
     }
 }
 

@@ -3,6 +3,7 @@ import pytest
 
 import workloads as W
 from workloads.blocktable import build_block_tables
+from workloads.quant import quantize_weights
 from gpu_common import run_both, check_parity, check_pool
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +33,34 @@ def test_rotated_steps_and_partials(orc, hidden, ffn, batch):
     lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 2, seed=11)
     pool = W.fill_kv_pool(shape, lay, 12)
     out = run_both(orc, shape, W.make_weights(shape, 13), lay, pool, W.initial_tokens(shape, batch, 14), 2)
+    worst, agree = check_parity(out)
+    check_pool(out, pool, shape, lay, 2)
+    assert worst < 2e-4 and agree == 1.0
+
+
+@pytest.mark.parametrize("batch", [3, 4, 5, 8, 9])
+@pytest.mark.parametrize("model,hidden,ffn,q4", [
+    ("dense", 4096, 4096, False),     # three and four rows: three terms of an activation in one operand; 5..8: two
+    ("dense", 1024, 2048, False),     # 4 MB a matrix: the smallest that four rows take so, three stay on the vector kernel
+    ("dense", 1024, 1920, False),     # below: four rows stay there too
+    ("dense", 384, 8192, False),      # the down projection in K slices across blocks
+    ("dense", 256, 9728, False),      # gate/up of 608 row tiles: K slices where terms are packed too
+    ("dense", 392, 1032, False),      # sizes off the 128 grid: terms stay apart
+    ("dense", 1024, 2048, True),
+    ("moe", 1024, 768, False),
+])
+def test_packed_terms(orc, model, hidden, ffn, q4, batch):
+    """Up to eight rows the terms of an activation lie side by side in one matrix-core operand: both sides of the row
+    counts and sizes at which that begins and ends.  Bound: that of the other parity tests."""
+    kw = dict(n_experts=8, top_k=2, expert_ffn=ffn, ffn=0) if model == "moe" else dict(ffn=ffn)
+    shape = variant("tiny_moe" if model == "moe" else "tiny", n_layers=1, hidden=hidden, vocab=2003, n_q_heads=8,
+                    n_kv_heads=4, head_dim=64 if hidden != 4096 else 128, qk_norm=True, **kw)
+    lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 2, seed=21)
+    weights = W.make_weights(shape, 22)
+    if q4:
+        weights = quantize_weights(weights)
+    pool = W.fill_kv_pool(shape, lay, 23)
+    out = run_both(orc, shape, weights, lay, pool, W.initial_tokens(shape, batch, 24), 2)
     worst, agree = check_parity(out)
     check_pool(out, pool, shape, lay, 2)
     assert worst < 2e-4 and agree == 1.0
