@@ -429,7 +429,8 @@ dk_status dk_read_stream(const void *d_buf, size_t bytes, void *d_sink, void *hi
  * epilogue: 0 plain store (q | k | v, lm_head), 1 residual projection (attention output, down), 2 the
  * gate/up pair with SwiGLU (N = rows of each of the two matrices).  four_bit: 1 for 4-bit weights.
  * out_waves: 0 = the kernel whose waves split K (then out_slices = 1); otherwise the waves per block of
- * the kernel whose waves share the activation tile, with K cut into out_slices slices across blocks.
+ * the kernel whose waves share the activation tile, with K cut into out_slices slices across blocks (a gate/up pair
+ * planned with eight runs with six where that fills the compute units better).
  * out_estimate_us: the model's estimate for the choice (0 where no estimate is made: 4-bit weights, K
  * not a multiple of 128).  DK_E_INVALID_ARG for NULL outputs, B outside 5..64 or non-positive sizes. */
 dk_status dk_gemm_plan_query(int32_t epilogue, int32_t N, int32_t K, int32_t B, int32_t four_bit,

@@ -241,7 +241,8 @@ void gemm_plan_needs(int epi, int N, int K, int Bp, bool q4, int pack, size_t &t
     const GemmPlan p = gemm_plan(epi, N, K, Bp, q4, pack);
     if (p.w == 0 || p.slices == 1) return;
     const size_t tiles = (size_t)(N + 15) / 16;
-    tickets = std::max(tickets, (tiles + p.w - 1) / p.w);
+    const int w = dkplan::shared_waves(epi, N, Bp / 16, p, device_cus());
+    tickets = std::max(tickets, (tiles + w - 1) / w);
     part_floats = std::max(part_floats, dk::shared_gemm_part_floats(N, p.slices, epi == dk::GEPI_SWIGLU ? 2 : 1, Bp / 16));
 }
 
@@ -592,6 +593,13 @@ dk_status launch_shared_gemm(const dk::GemmArgs &a, int Bp, const GemmPlan &p, h
         return fail(DK_E_INVALID_ARG, "K-sliced GEMM without its partial buffer");
     if (p.slices < 1 || p.slices > a.K / 128) return fail(DK_E_INVALID_ARG, "%d K slices of %d columns", p.slices, a.K);
     const int mt = Bp / 16;
+    if constexpr (EPI == dk::GEPI_SWIGLU) {
+        if (dkplan::shared_waves(EPI, a.N, mt, p, device_cus()) == 6) {
+            if (mt == 2) return a.q4 ? launch_shared_gemm_inst<2, 6, EPI, NORM, true>(a, p.slices, st) : launch_shared_gemm_inst<2, 6, EPI, NORM>(a, p.slices, st);
+            if (mt == 3) return a.q4 ? launch_shared_gemm_inst<3, 6, EPI, NORM, true>(a, p.slices, st) : launch_shared_gemm_inst<3, 6, EPI, NORM>(a, p.slices, st);
+            if (mt == 4) return a.q4 ? launch_shared_gemm_inst<4, 6, EPI, NORM, true>(a, p.slices, st) : launch_shared_gemm_inst<4, 6, EPI, NORM>(a, p.slices, st);
+        }
+    }
     if (a.q4) {
         if constexpr (EPI == dk::GEPI_RESID) {
             if (p.w == 4 && mt == 1) return launch_shared_gemm_inst<1, 4, EPI, NORM, true>(a, p.slices, st);

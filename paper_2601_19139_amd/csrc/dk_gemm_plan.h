@@ -178,6 +178,18 @@ inline GemmPlan gemm_plan_16(int epi, int N, int K, bool q4, bool pack, int cus)
     return best;
 }
 
+// Waves per block a plan runs with.  Gate/up pairs of more than 16 rows that are planned with eight take six where the
+// busiest compute unit then gets fewer row tiles: the 8B shape's 768 tiles in two slices are 192 blocks of eight, three
+// quarters of the chip, or 256 of six (64 rows 61.0 -> 54.8 us; 688 tiles 58.0 -> 52.2; the 3B shape's 512 tiles in four
+// slices fill the chip with eight: 30.8, with six 40.4).  Sums and their order are the same.
+inline int shared_waves(int epi, int N, int mt, const GemmPlan &p, int cus)
+{
+    if (epi != EPI_SWIGLU || mt < 2 || p.w != 8) return p.w;
+    const int tiles = (N + 15) / 16;
+    auto busiest = [&](int w) { return ((tiles + w - 1) / w * p.slices + cus - 1) / cus * w; };
+    return busiest(6) < busiest(8) ? 6 : 8;
+}
+
 // The plan.  Above 16 rows: the candidate with the smallest estimate.  Candidates are the skinny kernel (its variant by
 // skinny_variant) and the shared kernel in the block widths that are instantiated for the epilogue - 8
 // waves for plain stores and the gate/up pair, 4 waves for residual projections -

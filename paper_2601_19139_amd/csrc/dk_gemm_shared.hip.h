@@ -62,11 +62,12 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     constexpr int NA = NM * RT;
     constexpr int TPB = W * 64;
     constexpr int PIECES = PACK ? 256 : 512 * MT;   // 16-byte pieces of one step's activation tile (hi and lo)
-    static_assert((PACK == 0 && PIECES % TPB == 0) || (MT == 1 && TPB % 256 == 0), "every thread fetches the same number of pieces");
-    constexpr int PPT = PACK ? 1 : PIECES / TPB;
+    static_assert(PACK == 0 || (MT == 1 && TPB % 256 == 0), "a packed tile is 256 pieces");
+    constexpr int PPT = PACK ? 1 : (PIECES + TPB - 1) / TPB;   // (six waves: the last round is one of whole waves)
+    constexpr int NC = W == 6 ? 8 : W;                         // classes of the sum-of-squares partials: as with eight waves
     extern __shared__ uint4 sm_act_dyn[];   // two slots of one step's activation tile (shared_gemm_lds_bytes)
     uint4 (*sm_act)[PIECES] = reinterpret_cast<uint4 (*)[PIECES]>(sm_act_dyn);
-    __shared__ __align__(16) float sm_ssq[W][64];
+    __shared__ __align__(16) float sm_ssq[NC][64];
     __shared__ int sm_last;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         ks = min(ks0 + (ks < niter ? ks : ks - niter), nks - 1);
 #pragma unroll
         for (int p = 0; p < PPT; p++) {
-            const int piece = PACK ? (tid & 255) : p * TPB + tid;
+            const int piece = PACK ? (tid & 255) : PIECES % TPB ? min(p * TPB + tid, PIECES - 1) : p * TPB + tid;
             const int t = piece >> 9, lo = (piece >> 8) & 1, idx = piece & 255;
             st.act[p] = ld16((lo ? a.xlo : a.xhi) + (((int64_t)t * nks + ks) * 256 + idx) * 8);
         }
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         uint4 *slot = sm_act[it & 1];
 #pragma unroll
         for (int p = 0; p < PPT; p++)
-            if (!PACK || tid < 256) slot[p * TPB + tid] = st.act[p];
+            if (PACK ? tid < 256 : (PIECES % TPB == 0 || p * TPB + tid < PIECES)) slot[p * TPB + tid] = st.act[p];
         // one barrier per step is enough with two slots: nobody can write this slot again
         // before every wave has passed the next step's barrier, i.e. has finished reading it
         __syncthreads();
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     };
 
     // sum-of-squares partials of the input rows (NORM), requested ahead of the stream
-    SsqPartials<MT, W> ssq;
+    SsqPartials<MT, NC> ssq;
     if (NORM) ssq.request(a.ssq_in, a.n_part, wv, lane);
     // residual rows and next gains of this wave's tiles (GEPI_RESID)
     float xr[RT][MT][4], gn[RT][4];
@@ -230,6 +231,11 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     }
 #pragma unroll
     for (int p = 0; p < PD; p++) consume(st[p], niter2 - PD + p);
+
+    if (NORM && W < NC && wv + W < NC) {   // the classes without a wave of their own
+        ssq.request(a.ssq_in, a.n_part, wv + W, lane);
+        ssq.store(a.ssq_in, a.n_part, wv + W, lane, sm_ssq[wv + W]);
+    }
 
     if (S > 1) {
         // partial tiles out, ticket, and only the last block of this row block goes on
@@ -295,7 +301,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         if (NORM) {
             float s = 0.f;
 #pragma unroll
-            for (int w = 0; w < W; w++) s += sm_ssq[w][t * 16 + ln];
+            for (int w = 0; w < NC; w++) s += sm_ssq[w][t * 16 + ln];
             inv[t] = rsqrtf(s / (float)K + a.eps);
         }
     }

@@ -4,7 +4,7 @@ import pytest
 import workloads as W
 from workloads.blocktable import build_block_tables
 from workloads.quant import quantize_weights
-from gpu_common import run_both, check_parity, check_pool
+from gpu_common import run_both, run_sampled, check_parity, check_pool, check_pool_sampled
 
 pytestmark = pytest.mark.gpu
 
@@ -63,4 +63,26 @@ def test_packed_terms(orc, model, hidden, ffn, q4, batch):
     out = run_both(orc, shape, weights, lay, pool, W.initial_tokens(shape, batch, 24), 2)
     worst, agree = check_parity(out)
     check_pool(out, pool, shape, lay, 2)
+    assert worst < 2e-4 and agree == 1.0
+
+
+@pytest.mark.parametrize("hidden,ffn,batch,q4", [
+    (1024, 12288, 17, False),    # 768 row tiles in two slices: blocks of six waves, all whole
+    (1024, 12288, 64, False),
+    (1152, 12160, 48, False),    # 760: a last block of four row tiles, slices of four and five steps
+    (1152, 12160, 64, False),
+    (4096, 10368, 64, True),     # 648 row tiles
+])
+def test_gate_up_in_blocks_of_six_waves(orc, hidden, ffn, batch, q4):
+    """Six waves share an activation tile that does not divide among them, and sum the partials of eight.  Bound: that
+    of the other dense parity tests."""
+    shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=1003, qk_norm=True)
+    lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 1, seed=31)
+    weights, pool = W.make_weights(shape, 32), W.fill_kv_pool(shape, lay, 33)
+    if q4:
+        weights = quantize_weights(weights)
+    rows = sorted({0, batch // 2, batch - 1})
+    out = run_sampled(orc, shape, weights, lay, pool, W.initial_tokens(shape, batch, 34), 1, rows)
+    worst, agree = check_parity(out)
+    check_pool_sampled(out, pool, shape, lay, 1, rows)
     assert worst < 2e-4 and agree == 1.0
