@@ -415,6 +415,7 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
 // "before" is two rows and 256 threads below 64 MB, eight rows - gate/up four - and 256 threads above). Whole steps
 // at 2 / 3 / 4 rows, before -> after: 3B shape (19..50 MB a matrix) 1934 / 2502 / 3011 -> 1809 / 2038 / 2520 us, 8B
 // shape (33 MB and up) 3678 / 4262 / 5627 -> 3612 / 4163 / 5262; the 0.6B shape (4..6 MB) lies below the lines.
+// (Those steps of 3 and 4 rows have since left this kernel, see pack_terms; sizes off the 128 grid have not.)
 inline size_t gemv_bytes(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2; }
 inline bool gemv_small(const dk::GemvArgs &a) { return gemv_bytes(a) < (64u << 20); }
 
@@ -516,7 +517,7 @@ dk_status launch_gemv(dk::GemvArgs a, int B, hipStream_t st)
     return DK_OK;
 }
 
-// ---- skinny GEMM dispatch (batches of 5..64 rows) ---------------------------
+// ---- skinny GEMM dispatch (up to 64 rows; which take it: carve, pack_terms) ---
 // col_groups > 1: the batch rows are split into that many groups of 16*MT across blockIdx.y
 template <int MT, int KS, int RT, int EPI, bool NORM, bool KALIGNED, bool Q4 = false, int PACK = 0>
 dk_status launch_gemm_inst(const dk::GemmArgs &a, int col_groups, hipStream_t st)
@@ -556,11 +557,6 @@ dk_status launch_gemm_cfg(const dk::GemmArgs &a, hipStream_t st, int col_groups 
     return launch_gemm_inst<MT, KS, RT, EPI, NORM, false>(a, col_groups, st);
 }
 
-// A wave that handles several 16-row weight tiles per K-step reuses the
-// activation operand it has loaded, which cuts the cache traffic of the
-// activations; it pays when enough blocks remain to fill the chip (measured on
-// the 8B-class shapes: 4 tiles per wave for the lm_head, 2 for the fused q/k/v
-// matrix, 1 for the square-ish projections and the gate/up pair).
 // ---- shared-activation GEMM dispatch (see gemm_plan) -------------------------
 template <int MT, int W, int EPI, bool NORM, bool Q4 = false, int PACK = 0>
 dk_status launch_shared_gemm_inst(const dk::GemmArgs &a, int slices, hipStream_t st)
