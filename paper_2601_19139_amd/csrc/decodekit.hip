@@ -850,7 +850,7 @@ const char *dk_last_error(void) { return g_err; }
 
 // The kernel revisions change whenever a kernel's memory behaviour changes; the
 // benchmark quotes stored counter measurements only for a matching revision.
-const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r14, attention r10, moe r4, fused r9, prefill r2, sample r3)"; }
+const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r15, attention r10, moe r4, fused r9, prefill r2, sample r3)"; }
 
 // ------------------------------------------------------------------- pool --
 dk_status dk_kv_pool_bytes(const dk_model_config *cfg, int32_t num_blocks, int32_t block_size,

@@ -256,8 +256,8 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs &a, int out_ti
 // kSsqStride floats.  request() comes ahead of the first weights, store() - out[0..16*MT) - behind their requests, so
 // that the sums are made while the weights are under way.  Up to 16 batch rows a load brings 16 partials (16 bytes a
 // lane, four lanes to a partial): one float a lane and load was 16 times as many requests, all of them in front of
-// the first weights, and loads return in order.  (8B shape, 16 rows, together with the rotated K-steps below: 5.73 ->
-// 5.61 ms per step; 0.6B shape 1.202 -> 1.176.)  Beyond 16 rows the same measured nothing.
+// the first weights, and loads return in order (shared_gemm_kernel, 16 rows, blocks of four waves, gate/up of 9472 x 3584
+// 33.2 -> 29.9 us, 8960 x 1536 16.8 -> 16.3; blocks of eight the same).  Beyond 16 rows the same measured nothing.
 template <int MT, int NW>
 struct SsqPartials {
     static constexpr int U = MT == 1 ? 4 : 32;   // loads held in registers
@@ -374,9 +374,14 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
     };
     // Up to 16 batch rows block b begins b steps into K and wraps around: started together at the same column, the
     // blocks would ask the same few memory channels at the same time all along K (201 MB read this way and nothing
-    // else: 38.1 us from a common first column, 32.5 from rotated ones).  Beyond 16 rows, and where groups of rows share
-    // the weights through the caches, the stream is not the limit.
-    const int rot = MT == 1 && gridDim.y == 1 ? (int)blockIdx.x % nks : 0;
+    // else: 38.1 us from a common first column, 32.5 from rotated ones).  Where a row is a multiple of 4 KB, so that all
+    // rows begin on the same channels, the kernels of K = 2048, 4096, 6144, 8192 gained 5, 8, 8 and 9 % on average over 4, 6
+    // and 16 rows; other lengths are within 3 % (K = 11008 and 22016 gained 2 and 10, 9472 lost 3).  4-bit rows are a
+    // quarter as long: rotation cost 1 % on average, whole step of the 8B shape at 4 rows 605 -> 613 us, and paid at
+    // K = 8192 only (rows of 4 KB; layers of 8192 x 22016, 4 rows 506 -> 497).  Rows off the 128 grid lost (layers of
+    // 4104 x 11000, 16 rows 1310 -> 1362).  Beyond 16 rows, and where groups of rows share the weights through the caches,
+    // the stream is not the limit.
+    const int rot = MT == 1 && KALIGNED && (!Q4 || K % 8192 == 0) && gridDim.y == 1 ? (int)blockIdx.x % nks : 0;
     auto step = [&](int it) { const int ks = min(it * KS + wv, nks - 1) + rot; return ks < nks ? ks : ks - nks; };
     int it_i = 0;   // step to issue next
     auto issue = [&](Stage &st) {

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     struct Stage {
         uint4 wa[NA][Q4 ? 3 : 4], act[PPT];   // Q4: codes of the whole step, (scale, bias) of its two groups
     };
-    const int rot = MT == 1 ? (int)blockIdx.x % max(niter, 1) : 0;   // each block begins at another column (see skinny_gemm_kernel)
+    const int rot = MT == 1 && (!Q4 || K % 8192 == 0) ? (int)blockIdx.x % max(niter, 1) : 0;   // each block begins at another column (see skinny_gemm_kernel)
     int it_i = 0;
     auto issue = [&](Stage &st) {
         // (a step past the slice, or an empty slice - more slices than steps: a valid step, unused)

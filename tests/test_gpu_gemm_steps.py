@@ -20,12 +20,14 @@ def variant(base, **kw):
     (1288, 1032, 16),
     (1152, 2176, 16),    # 9 and 17 whole steps
     (4104, 512, 16),     # 257 partials
-    (8192, 256, 5),      # 512 partials: as many as eight waves hold in registers ...
-    (8200, 256, 5),      # ... and more; 65 steps, the last of 8 columns
+    (8192, 256, 5),      # four waves hold 256 partials in registers: 512, with packed terms
+    (8200, 256, 5),      # 513, terms apart; 65 steps, the last of 8 columns
+    (8192, 256, 16),     # eight waves (terms apart, K a multiple of 2048) hold 512: all of them ...
+    (10240, 256, 16),    # ... and 640, the rest one by one
 ])
 def test_rotated_steps_and_partials(orc, hidden, ffn, batch):
-    """Up to 16 rows a block starts at its own step of K and wraps around: steps that do not divide among the waves,
-    fewer steps than waves, a last step that is not whole.  Bound: that of the other dense parity tests."""
+    """Up to 16 rows a block starts at its own step of K and wraps around where the steps are whole: steps that do not
+    divide among the waves, fewer steps than waves, a last step that is not whole.  Bound: that of the other dense parity tests."""
     # No short contexts: with an empty one the attention output is the new token's v, and one of its 128 elements
     # rounded to the other bf16 neighbour (2^-8 of it) is 2^-8 / sqrt(128) = 3.5e-4 of the row, above the bound,
     # whatever the order of the sums; among 30 tokens it is a thirtieth of that.
