@@ -1,4 +1,4 @@
-// Which kernel a batched weight-streaming GEMM (2..64 rows) takes - host code only.
+// Which kernel a batched weight-streaming GEMM (1..64 rows) takes - host code only.
 //
 // Two kernels exist (dk_gemm.hip.h, dk_gemm_shared.hip.h).  Up to 16 batch rows the choice follows a few rules, given
 // with both sides at gemm_plan_16().  Above, the choice between them, and the number of K slices of the second, comes
@@ -36,15 +36,17 @@ struct SkinnyVariant { int mt, ks, rt, groups; };
 // Up to 16 batch rows what bounds a block is the bytes its compute unit fetches, about 40 GB/s of weights and
 // activations together.
 //   * Row tiles per wave: two - the activations once for both - where that leaves the busiest compute unit no more row
-//     tiles than one each would: plain stores from 1.25 tiles per compute unit on (3B shape, q/k/v, 320 tiles, 16 rows
-//     15.3 -> 12.6 us; 0.6B shape, 256 tiles 5.2 -> 6.1), the gate/up pair between one and two (512 tiles 24.2 -> 21.9
-//     us, 384 15.9 -> 14.3; 192 6.3 -> 8.4, 608 30.9 -> 35.1).
+//     tiles than one each would: single matrices from more than one tile per compute unit on (3B shape, q/k/v, 320 tiles,
+//     16 rows 15.3 -> 12.6 us; 288 tiles of K = 3072 and 3584 14.8 -> 12.4 and 17.2 -> 14.0, packed 13.6 -> 11.7; 0.6B shape,
+//     256 tiles 5.2 -> 6.1), the gate/up pair between one and two (512 tiles 24.2 -> 21.9 us, 384 15.9 -> 14.3; 192 6.3 ->
+//     8.4, 608 30.9 -> 35.1).
 //   * Waves: four; a second block on the same compute unit hides the start and the end of the first, and steps that
 //     do not divide among the waves cost less (eight -> four, 3B shape, K = 3072: gate/up 25.4 -> 21.9 us, q/k/v 14.1 ->
 //     12.6; 4 rows with packed terms 23.7 -> 21.2 and 12.4 -> 11.0).  Unpacked terms: eight where a wave's two steps in
-//     flight come out even (K = 2048: q/k/v 9.3 -> 8.9; 4 bit 7.3 -> 7.2, gate/up 10.3 -> 9.9) or are its only one
-//     (K = 1024, whole step of the 0.6B shape 1191 -> 1176), two for residual projections that make at most one block
-//     per compute unit (less to add up: K = 2048 6.4 -> 6.3, 4096 11.0 -> 10.8).
+//     flight come out even (K = 2048: q/k/v 9.3 -> 8.9; 4 bit 7.3 -> 7.2, gate/up 10.3 -> 9.9; K = 4096, whole step of the 8B
+//     shape, four / eight: 9 rows equal, 16 rows 1136 / 1133, 4 bit 707 / 703; K = 6144, 4 bit 556 / 544, bf16 825 / 831) or are
+//     its only one (K = 1024, whole step of the 0.6B shape 1191 -> 1176), two for residual projections that make at most
+//     one block per compute unit (less to add up: K = 2048 6.4 -> 6.3, 4096 11.0 -> 10.8).
 // Above 16 rows: a small matrix whose row tiles x groups of 16 rows still make at most two blocks per compute unit runs
 // the 16-row kernel over all groups at once, residual projections with two-wave blocks.
 inline SkinnyVariant skinny_variant(int epi, int N, int K, int Bp, bool q4, bool pack, int cus)
@@ -52,7 +54,7 @@ inline SkinnyVariant skinny_variant(int epi, int N, int K, int Bp, bool q4, bool
     const int tiles = (N + 15) / 16, mt = Bp / 16;
     const bool one_matrix = epi != EPI_SWIGLU;
     if (mt == 1) {
-        const bool two = one_matrix ? tiles >= cus + cus / 4 : tiles > cus && tiles <= 2 * cus;
+        const bool two = tiles > cus && (one_matrix || tiles <= 2 * cus);
         if (!pack && epi == EPI_RESID && !q4 && tiles <= cus) return {1, 2, 1, 1};
         return {1, !pack && (K <= 1024 || K % 2048 == 0) ? 8 : 4, two ? 2 : 1, 1};
     }
@@ -153,13 +155,24 @@ inline GemmPlan gemm_plan_q4(int epi, int N, int K)
 //   * gate/up pairs of more than two row tiles per compute unit: 608 tiles 30.9 / 25.3, 768 equal; packed only where the
 //     tiles do not fill their rounds of blocks (608: 26.7 / 24.7, 768: 37.0 / 42.0); 4 bit 608 17.6 / 15.3, 768 24.4 / 21.9,
 //     packed 768 equal.  Slices: the count that fills the compute units best (608 tiles, 3 / 4 / 5 slices: 25.3 / 29.3 /
-//     25.3 us; 768 tiles, 2 / 3 / 4 / 5: 46.7 / 48.9 / 42.2 / 46.0);
+//     25.3 us; 768 tiles, 2 / 3 / 4 / 5: 46.7 / 48.9 / 42.2 / 46.0), the smaller one where that fills them within 15 % as
+//     well (576 tiles of K = 3072, 3 / 5: 26.6 / 29.9; 592 30.7 / 31.6; 1376 of K = 8192, 2 / 5: 139.6 / 141.3; 4 bit, 1184
+//     tiles, 3 / 5, whole step of layers of 3584 x 18944 275 / 291); one where a stream is short (K = 2048, 688 tiles, 1 / 4:
+//     21.5 / 24.9, 864 tiles, 1 / 2: 22.7 / 28.3, packed 22.2 / 28.0; K = 1536, 560 tiles, 1 / 3: equal; K = 2304, 576 tiles
+//     24.4 / 21.5);
 //   * the lm_head, where the stream is long enough for one slice: 151936 x 1024 60 / 53, x 4096 237 / 212; packed 50 / 53,
-//     205 / 211; 4 bit 36 / 30, 132 / 100, packed 30 / 25, 101 / 87.
+//     205 / 211; 4 bit 36 / 30, 132 / 100, packed 30 / 25, 101 / 87;
+//   * shorter plain stores of three and four row tiles per compute unit, which two tiles per wave fill badly, in slices:
+//     640 tiles of K = 8192 52.1 / 34.4, 1000 of K = 2560 23.6 / 20.8, 3584 29.2 / 25.3, 5120 39.5 / 35.6, 8192 62.0 / 50.0 (K =
+//     2048 and 4096 16.8 / 17.4 and 29.3 / 31.0); 512 tiles of K = 6144 equal, 448 of K = 5120 20.6 / 20.0.
 inline GemmPlan gemm_plan_16(int epi, int N, int K, bool q4, bool pack, int cus)
 {
     const int tiles = (N + 15) / 16;
-    if (epi == EPI_STORE) return tiles >= (q4 ? 16 : 4) * cus && (q4 || !pack) ? GemmPlan{8, 1} : GemmPlan{0, 1};
+    if (epi == EPI_STORE) {
+        if (q4) return tiles >= 16 * cus ? GemmPlan{8, 1} : GemmPlan{0, 1};
+        if (pack || tiles <= 2 * cus) return {0, 1};
+        return {8, tiles >= 4 * cus ? 1 : shared_gemm_slices(N, K, 8, cus)};
+    }
     if (epi == EPI_RESID) {
         if (K < (q4 || pack ? 8192 : 4097) || (q4 && pack)) return {0, 1};
         return {4, q4 ? 8 : shared_gemm_slices(N, K, 4, cus)};
@@ -168,19 +181,20 @@ inline GemmPlan gemm_plan_16(int epi, int N, int K, bool q4, bool pack, int cus)
     if (rounds <= 2 || (pack && (q4 || tiles * 20 >= rounds * cus * 17))) return {0, 1};
     const int w = q4 ? 8 : 4, row_blocks = (tiles + w - 1) / w;
     GemmPlan best{w, 1};
-    if (row_blocks >= 2 * cus) return best;
+    if (row_blocks >= 2 * cus || (!q4 && K <= 2048)) return best;
     double best_fill = 0.0;
     for (int s = 2; s <= std::min(5, K / 512); s++) {
         const int blocks = row_blocks * s;
         const double fill = (double)blocks / ((double)cus * ((blocks + cus - 1) / cus));
-        if (fill > best_fill) { best_fill = fill; best.slices = s; }
+        if (fill > 1.15 * best_fill) { best_fill = fill; best.slices = s; }
     }
     return best;
 }
 
 // Waves per block a plan runs with.  Gate/up pairs of more than 16 rows that are planned with eight take six where the
 // busiest compute unit then gets fewer row tiles: the 8B shape's 768 tiles in two slices are 192 blocks of eight, three
-// quarters of the chip, or 256 of six (64 rows 61.0 -> 54.8 us; 688 tiles 58.0 -> 52.2; the 3B shape's 512 tiles in four
+// quarters of the chip, or 256 of six (64 rows 61.0 -> 54.8 us; 688 tiles 58.0 -> 52.2; 1088 tiles in four slices, three
+// rounds of blocks either way, whole step of layers of 5120 x 17408 1639 -> 1581; the 3B shape's 512 tiles in four
 // slices fill the chip with eight: 30.8, with six 40.4).  Sums and their order are the same.
 inline int shared_waves(int epi, int N, int mt, const GemmPlan &p, int cus)
 {

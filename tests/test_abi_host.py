@@ -315,3 +315,20 @@ def test_gemm_plan_follows_the_cost_model():
     for bad in ((3, 64, 128, 16), (0, 0, 128, 16), (0, 64, 128, 4), (0, 64, 128, 65)):
         with pytest.raises(dk.DecodeKitError):
             dk.gemm_plan_query(*bad)
+
+
+def test_gemm_plan_rules_up_to_16_rows():
+    """Both sides of the rules of at most 16 rows, for 256 compute units."""
+    STORE, RESID, SWIGLU = 0, 1, 2
+    # plain stores by row tiles: three and four to a compute unit in slices
+    for tiles, want in ((512, (0, 1)), (513, (8, 3)), (640, (8, 3)), (1000, (8, 2)), (1023, (8, 2)), (1024, (8, 1)), (8016, (8, 1))):
+        assert dk.gemm_plan_query(STORE, tiles * 16, 4096, 9, False, 256)[:2] == want
+        assert dk.gemm_plan_query(STORE, tiles * 16, 4096, 8, False, 256)[:2] == (0, 1)      # terms packed
+    # gate/up: fewer slices unless more fill the units better by a good part
+    for tiles, K, want in ((512, 3072, (0, 1)), (576, 3072, (4, 3)), (592, 3584, (4, 3)), (608, 2560, (4, 3)), (688, 4096, (4, 4)),
+                           (688, 2048, (4, 1)), (688, 2176, (4, 4)),
+                           (768, 4096, (4, 4)), (864, 5120, (4, 2)), (1376, 8192, (4, 2))):
+        assert dk.gemm_plan_query(SWIGLU, tiles * 16, K, 16, False, 256)[:2] == want, tiles
+    # the down projection of six thousand columns: sliced with terms apart, not with terms packed
+    assert dk.gemm_plan_query(RESID, 1000, 6144, 9, False, 256)[:2] == (4, 8)
+    assert dk.gemm_plan_query(RESID, 1000, 6144, 8, False, 256)[:2] == (0, 1)

@@ -1,7 +1,8 @@
-"""The matrix-core GEMMs at the edges of their steps over K and of their tables of partial sums."""
+"""The matrix-core GEMMs at the edges of their steps over K, of their tables of partial sums and of the rules that choose them."""
 import pytest
 
 import workloads as W
+import paper_2601_19139_amd as dk
 from workloads.blocktable import build_block_tables
 from workloads.quant import quantize_weights
 from gpu_common import run_both, run_sampled, check_parity, check_pool, check_pool_sampled
@@ -46,7 +47,8 @@ def test_rotated_steps_and_partials(orc, hidden, ffn, batch):
     ("dense", 1024, 2048, False),     # 4 MB a matrix: the smallest that four rows take so, three stay on the vector kernel
     ("dense", 1024, 1920, False),     # below: four rows stay there too
     ("dense", 384, 8192, False),      # the down projection in K slices across blocks
-    ("dense", 256, 9728, False),      # gate/up of 608 row tiles: K slices where terms are packed too
+    ("dense", 256, 9728, False),      # gate/up of 608 row tiles: the shared-activation kernel, one slice of two steps
+    ("dense", 2560, 9728, False),     # ... three, of seven and six steps
     ("dense", 392, 1032, False),      # sizes off the 128 grid: terms stay apart
     ("dense", 1024, 2048, True),
     ("moe", 1024, 768, False),
@@ -55,6 +57,8 @@ def test_packed_terms(orc, model, hidden, ffn, q4, batch):
     """Up to eight rows the terms of an activation lie side by side in one matrix-core operand: both sides of the row
     counts and sizes at which that begins and ends.  Bound: that of the other parity tests."""
     kw = dict(n_experts=8, top_k=2, expert_ffn=ffn, ffn=0) if model == "moe" else dict(ffn=ffn)
+    if ffn == 9728 and batch >= 5:
+        assert dk.gemm_plan_query(2, ffn, hidden, batch)[:2] == (4, {256: 1, 2560: 3}[hidden])
     shape = variant("tiny_moe" if model == "moe" else "tiny", n_layers=1, hidden=hidden, vocab=2003, n_q_heads=8,
                     n_kv_heads=4, head_dim=64 if hidden != 4096 else 128, qk_norm=True, **kw)
     lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 2, seed=21)
@@ -87,4 +91,30 @@ def test_gate_up_in_blocks_of_six_waves(orc, hidden, ffn, batch, q4):
     out = run_sampled(orc, shape, weights, lay, pool, W.initial_tokens(shape, batch, 34), 1, rows)
     worst, agree = check_parity(out)
     check_pool_sampled(out, pool, shape, lay, 1, rows)
+    assert worst < 2e-4 and agree == 1.0
+
+
+@pytest.mark.parametrize("batch", [4, 5, 9, 16])
+@pytest.mark.parametrize("hidden,ffn,vocab,q4", [
+    (1024, 2048, 4112, False),    # lm_head of 257 row tiles: two per wave, the last block has one
+    (1024, 2048, 4112, True),
+    (1536, 2048, 8200, False),    # 513: blocks of eight waves in three slices of four steps; terms packed: two per wave
+    (2048, 2048, 10007, False),   # 626: three slices of five and six steps
+    (2048, 2048, 16381, False),   # 1024: the smallest without slices
+])
+def test_rules_of_plain_stores(orc, hidden, ffn, vocab, q4, batch):
+    """Plain stores up to 16 rows at both ends of their rules on row tiles.  Bound: that of the other dense parity tests.
+    (Weights without ties: in the oracle the two largest logits of any row lie 3e-4 of the row's rms apart or more, thirty
+    times what the sides differ by; with the seed before, two of them lay 6e-6 apart.)"""
+    if batch > 8 and not q4 and vocab > 8192:
+        assert dk.gemm_plan_query(0, vocab, hidden, batch)[:2] == (8, 1 if vocab == 16381 else 3)
+    shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=vocab, n_q_heads=8, n_kv_heads=4, head_dim=64, qk_norm=True)
+    lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 2, seed=41)
+    weights = W.make_weights(shape, 43)
+    if q4:
+        weights = quantize_weights(weights)
+    pool = W.fill_kv_pool(shape, lay, 43)
+    out = run_both(orc, shape, weights, lay, pool, W.initial_tokens(shape, batch, 44), 2)
+    worst, agree = check_parity(out)
+    check_pool(out, pool, shape, lay, 2)
     assert worst < 2e-4 and agree == 1.0
