@@ -251,8 +251,14 @@ void gemm_plan_needs(int epi, int N, int K, int Bp, bool q4, int pack, size_t &t
 // 0.6B shape 1114 -> 1010 us, 3B 2180 -> 1998, 8B 4434 -> 4019; 4 bit 3B 1651 -> 1375).
 // Three or four rows of a dense model take three terms, all of float32's bits, instead of the vector-ALU products, which
 // re-read float32 activations per two to four weight rows: 4 rows, 0.6B shape 1072 -> 985 us, 3B 2484 -> 1996, 8B 5208 ->
-// 3809.  Three rows gain from the 3B shape on (50 MB a matrix; 2021 -> 1975, 8B 4108 -> 3740) and lose 2 % at the 0.6B shape,
-// two lose on all but the 8B shape (equal there): the vector kernel's work grows with the rows, this one's does not.
+// 3809 (contexts of 512).  The vector kernel's work grows with the rows, this one's does not, so three rows gain less and
+// two lose on all but the 8B shape (equal there).  Lines, by the gate matrix's bytes, whole steps, vector -> three terms:
+//   * four rows from 4 MB on: 4 MB 1024 x 2048 1449 -> 1442, 2048 x 1024 1585 -> 1499, 512 x 4096 1822 -> 1833 (heads of 128)
+//     and 1532 -> 1413 (of 64); 6 MB 1024 x 2816 1529 -> 1508.  Narrower layers below it gain as well (768 x 2048 1855 -> 1454).
+//   * three rows from 32 MB to 256 MB: 32 MB 2048 x 8192 490 -> 477, 33 MB 3072 x 5632 452 -> 457, 34 MB 2560 x 6912 499 ->
+//     495, 40 MB 2304 x 9216 472 -> 449, 50 MB (3B shape) 829 -> 815, 192 MB 6144 x 16384 596 -> 588.  Below: 22 MB 2048 x 5632
+//     640 -> 646, 18 MB 1536 x 6144 740 -> 796, 6 MB (0.6B shape) 2 % slower, though 28 MB 3584 x 4096 469 -> 430.  Above: 344 MB
+//     8192 x 22016 919 -> 987, 448 MB 8192 x 28672 1076 -> 1100.
 constexpr int kPackRows2 = dk::kPackCols(2);
 static_assert(kMaxGemvBatch <= dk::kPackCols(3), "three terms of the few-row batches fit one operand");
 int pack_terms(const dk_model_config &c, int B, bool q4)
@@ -261,7 +267,7 @@ int pack_terms(const dk_model_config &c, int B, bool q4)
     if (H % 128 || qd % 128 || (c.n_experts == 0 && c.ffn % 128) || B > kPackRows2) return 0;
     if (B > kMaxGemvBatch || c.n_experts > 0 || q4) return 2;
     const size_t mb = (H * c.ffn * 2) >> 20;   // of the gate matrix
-    return mb >= (B == 4 ? 4u : 32u) && B >= 3 ? 3 : 0;
+    return B == 4 ? (mb >= 4 ? 3 : 0) : B == 3 && mb >= 32 && mb < 256 ? 3 : 0;
 }
 
 // q4: the model's matrices are 4-bit; every batch size then takes the matrix-core kernels

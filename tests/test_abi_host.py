@@ -332,3 +332,17 @@ def test_gemm_plan_rules_up_to_16_rows():
     # the down projection of six thousand columns: sliced with terms apart, not with terms packed
     assert dk.gemm_plan_query(RESID, 1000, 6144, 9, False, 256)[:2] == (4, 8)
     assert dk.gemm_plan_query(RESID, 1000, 6144, 8, False, 256)[:2] == (0, 1)
+
+
+def test_three_rows_leave_the_vector_kernel_between_two_sizes():
+    """Three rows keep three terms of every activation (and the table of their partial sums) where the gate matrix has 32 MB
+    up to 256 MB: the workspace shrinks where the next larger layer goes back to the vector kernel."""
+    def nbytes(ffn, rows):
+        cfg, ptrs, _keep = fake_model(W.ModelConfig(**{**W.CONFIGS["qwen3_8b"].as_dict(), "n_layers": 1, "hidden": 8192, "ffn": ffn}))
+        m = dk.create_model(cfg, ptrs)
+        n = dk.workspace_bytes(m, rows, 4)
+        dk.destroy_model(m)
+        return n
+    below, at = nbytes(16256, 3), nbytes(16384, 3)      # 254 and 256 MB
+    assert below > at and nbytes(2048, 3) > nbytes(1920, 3) + 8192 * 4 * 3      # 32 and 30 MB
+    assert nbytes(16384, 4) > nbytes(16256, 4)          # four rows: no upper line
