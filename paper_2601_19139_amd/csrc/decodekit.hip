@@ -175,7 +175,7 @@ struct Workspace {
     bool fused;
     int Bp;             // batch rows padded to a multiple of 16
     bool batched;
-    int pack;           // batched path: the terms of an activation share one 16-column operand (2 or 3 terms; 0: hi and lo apart)
+    int pack_x, pack_a, pack_f;   // batched path, inputs of K = hidden, q width and ffn: 2 or 3 terms share one 16-column operand (0: hi and lo apart)
     int chunk_tokens, max_chunks, lm_blocks;
     int pf_chunk_tokens, pf_max_chunks;   // the same split for the kernel that takes a prefill chunk's rows in groups
     bool defer_merge;   // small problems: the output projection merges the attention chunks
@@ -183,7 +183,7 @@ struct Workspace {
     bool attn_light;    // ... without the register double buffer (short chunks)
 };
 
-constexpr int kMaxGemvBatch = 4;  // up to here the vector-ALU GEMV; above, the matrix-core GEMM
+constexpr int kMaxGemvBatch = 4;  // the most rows the vector-ALU GEMV takes (fewer where pack_terms, 4-bit weights or experts ask for the matrix cores)
 constexpr int kLmRB = 8;     // rows per tile of the lm_head GEMV
 constexpr int kLmTiles = 1;  // tiles per block of the lm_head GEMV
 
@@ -261,11 +261,14 @@ void gemm_plan_needs(int epi, int N, int K, int Bp, bool q4, int pack, size_t &t
 //     8192 x 22016 919 -> 987, 448 MB 8192 x 28672 1076 -> 1100.
 constexpr int kPackRows2 = dk::kPackCols(2);
 static_assert(kMaxGemvBatch <= dk::kPackCols(3), "three terms of the few-row batches fit one operand");
-int pack_terms(const dk_model_config &c, int B, bool q4)
+// Two terms go by the operand's own length K: a GEMM then takes the kernel that dk_gemm_plan_query names for its matrix,
+// whatever the model's other sizes are.
+int pack_terms(const dk_model_config &c, int B, bool q4, size_t K)
 {
-    const size_t H = (size_t)c.hidden, qd = (size_t)c.n_q_heads * c.head_dim;
-    if (H % 128 || qd % 128 || (c.n_experts == 0 && c.ffn % 128) || B > kPackRows2) return 0;
+    if (K % 128 || B > kPackRows2) return 0;
     if (B > kMaxGemvBatch || c.n_experts > 0 || q4) return 2;
+    const size_t H = (size_t)c.hidden, qd = (size_t)c.n_q_heads * c.head_dim;
+    if (H % 128 || qd % 128 || c.ffn % 128) return 0;   // three terms: all operands or none
     const size_t mb = (H * c.ffn * 2) >> 20;   // of the gate matrix
     return B == 4 ? (mb >= 4 ? 3 : 0) : B == 3 && mb >= 32 && mb < 256 ? 3 : 0;
 }
@@ -291,7 +294,9 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     //    25.4 -> 22.5 us per launch; 0.6B shape, 16 rows of context 512: 15.1 -> 12.9 us); with 4 k
     //    contexts or groups of 8 it is slower and is not taken.
     const bool batched_attn = B > kMaxGemvBatch || c.n_experts > 0 || q4;   // (three terms: the vector-ALU kernel's float32 probabilities)
-    w.pack = pack_terms(c, B, q4);
+    w.pack_x = pack_terms(c, B, q4, c.hidden);
+    w.pack_a = pack_terms(c, B, q4, (size_t)c.n_q_heads * d);
+    w.pack_f = c.n_experts > 0 ? 0 : pack_terms(c, B, q4, c.ffn);
     const int pairs = B * c.n_kv_heads;
     auto round64 = [](int v) { v = (v + 63) / 64 * 64; return v < 64 ? 64 : v; };
     auto chunk_for = [&](int want_blocks) {
@@ -318,7 +323,7 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     // the output projection then merges them as it loads its input (at most 8
     // chunks, one round of loads), which saves the attention kernel a round of
     // device-wide synchronisation.
-    if (B <= kMaxGemvBatch && c.n_experts == 0 && !q4 && w.pack == 0) {   // the vector-ALU path only
+    if (B <= kMaxGemvBatch && c.n_experts == 0 && !q4 && w.pack_x != 3) {   // the vector-ALU path only
         int chunk8 = ((ctx_max + 7) / 8 + 63) / 64 * 64;
         if (chunk8 < chunk) chunk8 = chunk;
         const int n8 = (ctx_max + chunk8 - 1) / chunk8;
@@ -353,17 +358,17 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     w.part = take(part_floats * 4);
     w.Bp = (B + 15) / 16 * 16;
     // expert layers and 4-bit weights use the matrix-core kernels
-    w.batched = B > kMaxGemvBatch || c.n_experts > 0 || q4 || w.pack == 3;
+    w.batched = B > kMaxGemvBatch || c.n_experts > 0 || q4 || w.pack_x == 3;
     size_t gemm_tickets = 0, gemm_part = 0;
     if (w.batched) {
         const int H = c.hidden, qd = c.n_q_heads * d;
-        gemm_plan_needs(dk::GEPI_STORE, (int)qkv_dim, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
-        gemm_plan_needs(dk::GEPI_RESID, H, qd, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_STORE, (int)qkv_dim, H, w.Bp, q4, w.pack_x, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_RESID, H, qd, w.Bp, q4, w.pack_a, gemm_tickets, gemm_part);
         if (c.n_experts == 0) {
-            gemm_plan_needs(dk::GEPI_SWIGLU, c.ffn, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
-            gemm_plan_needs(dk::GEPI_RESID, H, c.ffn, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
+            gemm_plan_needs(dk::GEPI_SWIGLU, c.ffn, H, w.Bp, q4, w.pack_x, gemm_tickets, gemm_part);
+            gemm_plan_needs(dk::GEPI_RESID, H, c.ffn, w.Bp, q4, w.pack_f, gemm_tickets, gemm_part);
         }
-        gemm_plan_needs(dk::GEPI_STORE, c.vocab, H, w.Bp, q4, w.pack, gemm_tickets, gemm_part);
+        gemm_plan_needs(dk::GEPI_STORE, c.vocab, H, w.Bp, q4, w.pack_x, gemm_tickets, gemm_part);
     }
     w.n_tickets = B * c.n_kv_heads + (int)gemm_tickets;
     w.tickets = take((size_t)w.n_tickets * 4);
@@ -1399,13 +1404,12 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
     uint16_t *ahi = reinterpret_cast<uint16_t *>(ws + w.ahi), *alo = reinterpret_cast<uint16_t *>(ws + w.alo);
     uint16_t *fhi = reinterpret_cast<uint16_t *>(ws + w.fhi), *flo = reinterpret_cast<uint16_t *>(ws + w.flo);
     uint16_t *x3 = nullptr, *a3 = nullptr, *f3 = nullptr;
-    if (w.pack) {   // the other terms lie in further columns of the first one's operand
-        const int next = dk::kPackCols(w.pack) * 8;
-        xlo = xhi + next;
-        alo = ahi + next;
-        if (c.n_experts == 0) flo = fhi + next;
-        if (w.pack == 3) { x3 = xlo + next; a3 = alo + next; f3 = flo + next; }
-    }
+    // packed: the other terms lie in further columns of the first one's operand
+    auto next = [](int terms) { return dk::kPackCols(terms) * 8; };
+    if (w.pack_x) xlo = xhi + next(w.pack_x);
+    if (w.pack_a) alo = ahi + next(w.pack_a);
+    if (w.pack_f) flo = fhi + next(w.pack_f);
+    if (w.pack_x == 3) { x3 = xlo + next(3); a3 = alo + next(3); f3 = flo + next(3); }
     float *ssq = reinterpret_cast<float *>(ws + w.ssq);
 
     const int H = c.hidden, d = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads;
@@ -1450,7 +1454,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = H;
             g.B = B;
             g.q4 = model->q4;
-            g.pack = w.pack;
+            g.pack = w.pack_x;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = xhi;
@@ -1523,7 +1527,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             a.scale = (float)(1.0 / std::sqrt((double)d));
             a.eps = eps;
             a.n_rows = B;
-            if (prefill && batched && w.pack != 3) {
+            if (prefill && batched && w.pack_x != 3) {
                 // rows of one sequence: 16 / G of them share every K/V tile
                 const int G = nq / nkv;
                 a.chunk_tokens = w.pf_chunk_tokens;
@@ -1547,7 +1551,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = nq * d;
             g.B = B;
             g.q4 = model->q4;
-            g.pack = w.pack;
+            g.pack = w.pack_a;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = ahi;
@@ -1687,7 +1691,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = H;
             g.B = B;
             g.q4 = model->q4;
-            g.pack = w.pack;
+            g.pack = w.pack_x;
             g.kpart = kpart;
             g.ktickets = ktickets;
             g.xhi = xhi;
@@ -1705,7 +1709,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             h.K = c.ffn;
             h.B = B;
             h.q4 = model->q4;
-            h.pack = w.pack;
+            h.pack = w.pack_f;
             h.kpart = kpart;
             h.ktickets = ktickets;
             h.xhi = fhi;
@@ -1750,7 +1754,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
         g.K = H;
         g.B = B;
         g.q4 = model->q4;
-        g.pack = w.pack;
+        g.pack = w.pack_x;
         g.kpart = kpart;
         g.ktickets = ktickets;
         g.xhi = xhi;
@@ -1916,9 +1920,9 @@ dk_status dk_gemm_plan_query(int32_t epilogue, int32_t N, int32_t K, int32_t B, 
     if (epilogue < 0 || epilogue > 2 || N < 1 || K < 1 || B <= kMaxGemvBatch || B > DK_MAX_BATCH || compute_units < 0)
         return fail(DK_E_INVALID_ARG, "epilogue %d, N %d, K %d, B %d, compute units %d", epilogue, N, K, B, compute_units);
     const int Bp = (B + 15) / 16 * 16;
-    const GemmPlan p = dkplan::gemm_plan(epilogue, N, K, Bp, four_bit != 0, B <= kPackRows2 && K % 128 == 0, compute_units ? compute_units : device_cus(),
-                                         out_estimate_us);
-    *out_waves = p.w;
+    const int cus = compute_units ? compute_units : device_cus();
+    const GemmPlan p = dkplan::gemm_plan(epilogue, N, K, Bp, four_bit != 0, B <= kPackRows2 && K % 128 == 0, cus, out_estimate_us);
+    *out_waves = dkplan::shared_waves(epilogue, N, Bp / 16, p, cus);
     *out_slices = p.slices;
     return DK_OK;
 }

@@ -277,8 +277,8 @@ def test_shared_prefix_counts_once_in_algorithmic_bytes():
 
 
 def test_gemm_plan_follows_the_cost_model():
-    """The batched-GEMM dispatch is the argmin of a cost estimate, not a table of shapes: properties
-    that any shape must meet, checked on layer matrices of model shapes the calibration never saw
+    """The batched-GEMM dispatch follows rules on sizes up to 16 rows and the argmin of a cost estimate above, not a table
+    of shapes: properties that any shape must meet, checked on layer matrices of model shapes the calibration never saw
     (hidden 2560 / ffn 9728, hidden 5120 / ffn 17408) beside the ones it did."""
     STORE, RESID, SWIGLU = 0, 1, 2
     shapes = []
@@ -291,12 +291,13 @@ def test_gemm_plan_follows_the_cost_model():
             for B in (5, 16, 17, 32, 48, 64):
                 w, s, us = dk.gemm_plan_query(epi, N, K, B, False, cus)
                 tiles = (N + 15) // 16
-                assert w in (0, 4, 8) and 1 <= s <= 8 and us > 0
+                # instantiated block widths: 4 waves for residual projections and for the gate/up pair up to 16 rows,
+                # 8 for plain stores, 8 or 6 for the gate/up pair above
+                assert w in {STORE: (0, 8), RESID: (0, 4), SWIGLU: (0, 4) if B <= 16 else (0, 6, 8)}[epi]
+                assert 1 <= s <= 8 and us > 0
                 if w == 0:
                     assert s == 1
                     continue
-                # instantiated block widths: 4 waves for residual projections (and the gate/up pair at 16 rows)
-                assert (w == 4) == (epi == RESID or (epi == SWIGLU and B <= 16 and w == 4))
                 row_blocks = (tiles + w - 1) // w
                 assert s <= max(1, K // 512)                     # at least four K-steps per slice
                 if row_blocks <= cus // 2:
@@ -346,3 +347,16 @@ def test_three_rows_leave_the_vector_kernel_between_two_sizes():
     below, at = nbytes(16256, 3), nbytes(16384, 3)      # 254 and 256 MB
     assert below > at and nbytes(2048, 3) > nbytes(1920, 3) + 8192 * 4 * 3      # 32 and 30 MB
     assert nbytes(16384, 4) > nbytes(16256, 4)          # four rows: no upper line
+
+
+def test_gemm_plan_query_says_what_runs():
+    """The wave count is the launch's own: six where eight would leave the busiest compute unit more row tiles."""
+    SWIGLU = 2
+    for N, K, B, waves in ((12288, 4096, 17, 6), (12288, 4096, 64, 6), (11008, 4096, 64, 6), (17408, 5120, 32, 6), (8192, 3072, 64, 8),
+                           (9728, 2560, 64, 8)):
+        w, s, us = dk.gemm_plan_query(SWIGLU, N, K, B, False, 256)
+        assert w == waves and us > 0, (N, K, B, w)
+        tiles = (N + 15) // 16
+        busiest = {v: -(--(-tiles // v) * s // 256) * v for v in (6, 8)}
+        assert (w == 6) == (busiest[6] < busiest[8])
+    assert dk.gemm_plan_query(SWIGLU, 10368, 4096, 64, True, 256)[0] == 6

@@ -50,6 +50,8 @@ def test_rotated_steps_and_partials(orc, hidden, ffn, batch):
     ("dense", 256, 9728, False),      # gate/up of 608 row tiles: the shared-activation kernel, one slice of two steps
     ("dense", 2560, 9728, False),     # ... three, of seven and six steps
     ("dense", 392, 1032, False),      # sizes off the 128 grid: terms stay apart
+    ("dense", 392, 1024, False),      # ... of the normed rows alone
+    ("dense", 1024, 1032, False),     # ... of the MLP's inner rows alone
     ("dense", 1024, 2048, True),
     ("moe", 1024, 768, False),
 ])
@@ -82,6 +84,7 @@ def test_packed_terms(orc, model, hidden, ffn, q4, batch):
 def test_gate_up_in_blocks_of_six_waves(orc, hidden, ffn, batch, q4):
     """Six waves share an activation tile that does not divide among them, and sum the partials of eight.  Bound: that
     of the other dense parity tests."""
+    assert dk.gemm_plan_query(2, ffn, hidden, batch, q4)[0] == 6
     shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=1003, qk_norm=True)
     lay = build_block_tables([30 + (29 * i) % 70 for i in range(batch)], 16, 1, seed=31)
     weights, pool = W.make_weights(shape, 32), W.fill_kv_pool(shape, lay, 33)
