@@ -1,4 +1,5 @@
 """The matrix-core GEMMs at the edges of their steps over K, of their tables of partial sums and of the rules that choose them."""
+import numpy as np
 import pytest
 
 import workloads as W
@@ -121,3 +122,102 @@ def test_rules_of_plain_stores(orc, hidden, ffn, vocab, q4, batch):
     worst, agree = check_parity(out)
     check_pool(out, pool, shape, lay, 2)
     assert worst < 2e-4 and agree == 1.0
+
+
+def bf16_terms(x, n):
+    """x as the sum of n bf16 numbers, each rounding what the ones before it leave."""
+    out = np.zeros_like(x)
+    for _ in range(n):
+        out += W.f32_from_bf16_bits(W.bf16_bits_from_f32((x - out).astype(np.float32))).astype(np.float64)
+    return out
+
+
+@pytest.mark.parametrize("hidden,ffn,batch", [(1024, 2048, 4), (2048, 8192, 3)])
+def test_three_terms_keep_float32(orc, hidden, ffn, batch):
+    """Three and four rows on the matrix cores keep every activation as three bf16 terms.  Every matrix selects: the
+    output projection, the down projection and the lm_head pass their input on, gate and up rows pick one element each,
+    so the logits are the residual stream itself behind attention (a mean of cached v, as the embeddings are zero), the
+    output projection, SwiGLU and the down projection, in turn, and an element that lost its third term anywhere shows.
+
+    Bound: the third term of x is what two leave of it, 2^-17 of its binade at most and 2.2e-6 of x in the mean square;
+    float32 itself rounds to 2^-24 = 6e-8 some ten times on the way (mean, norm twice, silu, the terms' sums).  8e-7 lies
+    between, and the two-term value of each of the four activations alone is checked to lie beyond it."""
+    one = W.bf16_bits_from_f32(np.float32(1.0))
+    shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=hidden, n_q_heads=hidden // 128, n_kv_heads=hidden // 256,
+                    head_dim=128, qk_norm=False)
+    rows = np.arange(ffn)
+    pick_a, pick_b = rows % hidden, (7 * rows + 3) % hidden
+
+    def selector(n, k, cols):
+        m = np.zeros((n, k), np.uint16)
+        m[np.arange(len(cols)), cols] = one
+        return m
+
+    eye = selector(hidden, hidden, np.arange(hidden))
+    gain = np.full(hidden, one, np.uint16)
+    zero = lambda n: np.zeros((n, hidden), np.uint16)
+    layer = dict(g_attn=gain, g_mlp=gain, wq=zero(shape.q_dim), wk=zero(shape.kv_dim), wv=zero(shape.kv_dim), wo=eye,
+                 w_gate=selector(ffn, hidden, pick_a), w_up=selector(ffn, hidden, pick_b), w_down=selector(hidden, ffn, np.arange(hidden)))
+    weights = dict(embed=zero(shape.vocab), lm_head=eye, g_final=gain, layers=[layer])
+    lay = build_block_tables([37 + 11 * i for i in range(batch)], 16, 1, seed=51)
+    pool = W.fill_kv_pool(shape, lay, 52)
+
+    def reference(**terms):
+        t = lambda name, x: bf16_terms(x, 2) if name in terms else x
+        norm = lambda x, stored: stored / np.sqrt((x * x).mean(-1, keepdims=True) + shape.rms_eps)
+        att = np.empty((batch, shape.n_q_heads, 128))
+        for b, n in enumerate(lay.contexts):
+            v = np.stack([pool[0, lay.tables[b, p // 16], 1, :, p % 16] for p in range(n)])
+            att[b] = np.repeat(W.f32_from_bf16_bits(v).astype(np.float64).sum(0) / (n + 1), 2, axis=0)
+        x = t("attention", att.reshape(batch, hidden))
+        h = norm(x, t("o", x))
+        g, u = h[:, pick_a], h[:, pick_b]
+        f = t("swiglu", g / (1 + np.exp(-g)) * u)
+        x = x + f[:, :hidden]
+        return norm(x, t("down", x))
+
+    want = reference()
+    err = lambda got: float((np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)).max())
+    for name in ("attention", "o", "swiglu", "down"):
+        assert err(reference(**{name: True})) > 8e-7, name
+    dm = dk.DeviceModel(shape, weights)
+    dkv = dk.DeviceKV(dm, lay, pool)
+    dec = dk.Decoder(dm, dkv, lay.contexts.copy().astype(np.int32), np.zeros(batch, np.int32))
+    dec.ws.fill_(0x3f)      # a term that nobody writes is 0.75, not the zero that fresh memory may hold
+    dec.step()
+    got = dec.logits.cpu().numpy().astype(np.float64)
+    dkv.close()
+    dm.close()
+    print(f"hidden {hidden}, {batch} rows: {err(got):.2e}")
+    assert err(got) < 8e-7
+
+
+@pytest.mark.parametrize("hidden,ffn", [(1024, 2048), (4096, 512), (12288, 256)])
+def test_sums_of_three_terms(orc, hidden, ffn):
+    """A long sum of four rows against float64, the matrix cores (three terms) and the vector kernel (two rows of the same):
+    one layer that adds nothing, so the logits are the lm_head's products with normalised embeddings.
+
+    Bound: the matrix cores add a K-step of 128 on their own and the steps in float32, K / 512 of them per wave; with every
+    partial sum rounded to 2^-24 of its size a walk of n steps is off by 2^-24 * sqrt(n / 3) of the result in the mean
+    square, 1.7e-7 for the 24 of K = 12288.  2.5e-7 leaves the norm's own rounding its share; a single chain through the
+    matrix cores measured 3.3e-7 there."""
+    shape = variant("tiny", n_layers=1, hidden=hidden, ffn=ffn, vocab=2003, n_q_heads=8, n_kv_heads=4, head_dim=64)
+    weights = W.make_weights(shape, 61)
+    layer = weights["layers"][0]
+    layer["wo"], layer["w_down"] = np.zeros_like(layer["wo"]), np.zeros_like(layer["w_down"])
+    f64 = lambda bits: W.f32_from_bf16_bits(bits).astype(np.float64)
+    for batch in (4, 2):
+        lay = build_block_tables([20 + i for i in range(batch)], 16, 1, seed=62)
+        tokens = W.initial_tokens(shape, 4, 63)[:batch]
+        x = f64(weights["embed"][tokens])
+        want = (x / np.sqrt((x * x).mean(-1, keepdims=True) + shape.rms_eps) * f64(weights["g_final"])) @ f64(weights["lm_head"]).T
+        dm = dk.DeviceModel(shape, weights)
+        dkv = dk.DeviceKV(dm, lay, W.fill_kv_pool(shape, lay, 64))
+        dec = dk.Decoder(dm, dkv, lay.contexts.copy().astype(np.int32), tokens)
+        dec.step()
+        got = dec.logits.cpu().numpy().astype(np.float64)
+        dkv.close()
+        dm.close()
+        err = float((np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)).max())
+        print(f"K {hidden}, {batch} rows: {err:.2e}")
+        assert err < 2.5e-7

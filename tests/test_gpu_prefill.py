@@ -84,6 +84,9 @@ CASES = [
     ("tiny_one_chunk", variant("tiny"), 23, 64, 3),
     ("tiny_chunks_of_5", variant("tiny", qk_norm=True), 37, 5, 2),        # chunks of 5 rows: matrix-core path
     ("tiny_chunks_of_3", variant("tiny", qk_norm=True), 20, 3, 2),        # chunks of 3 rows: vector path
+    # three terms of an activation on the matrix cores, the vector-ALU attention over rows of one sequence
+    ("chunks_of_4_three_terms", variant("tiny", n_layers=1, hidden=1024, ffn=2048, n_q_heads=8, n_kv_heads=4, qk_norm=True), 290, 4, 1),
+    ("chunks_of_3_three_terms", variant("tiny", n_layers=1, hidden=2048, ffn=8192, n_q_heads=16, n_kv_heads=4, head_dim=128), 23, 3, 1),
     ("tiny_single_tokens", variant("tiny"), 6, 1, 2),
     ("tiny_long_64", variant("tiny", qk_norm=True), 150, 64, 2),
     ("d128_g4", variant("tiny", head_dim=128, n_q_heads=8, n_kv_heads=2, qk_norm=True), 70, 32, 2),
