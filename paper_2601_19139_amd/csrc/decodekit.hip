@@ -426,7 +426,8 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
 // "before" is two rows and 256 threads below 64 MB, eight rows - gate/up four - and 256 threads above). Whole steps
 // at 2 / 3 / 4 rows, before -> after: 3B shape (19..50 MB a matrix) 1934 / 2502 / 3011 -> 1809 / 2038 / 2520 us, 8B
 // shape (33 MB and up) 3678 / 4262 / 5627 -> 3612 / 4163 / 5262; the 0.6B shape (4..6 MB) lies below the lines.
-// (Those steps of 3 and 4 rows have since left this kernel, see pack_terms; sizes off the 128 grid have not.)
+// (Those steps of 3 and 4 rows have since left this kernel, see pack_terms.  What it still has of them: sizes off the 128
+// grid, three rows of layers below 32 MB and from 256 MB a gate matrix on, four rows below 4 MB.)
 inline size_t gemv_bytes(const dk::GemvArgs &a) { return (size_t)a.N * a.K * 2; }
 inline bool gemv_small(const dk::GemvArgs &a) { return gemv_bytes(a) < (64u << 20); }
 

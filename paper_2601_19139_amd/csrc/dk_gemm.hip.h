@@ -1,4 +1,5 @@
-// Weight-streaming skinny GEMM on the matrix cores for batches of 5..64 rows.
+// Weight-streaming skinny GEMM on the matrix cores: 5..64 rows, three and four of the larger dense models, and every
+// count of expert and 4-bit models.
 //
 //   D[r][n] = sum_k W[r][k] * X[n][k]          r: weight row, n: batch row
 //
@@ -7,9 +8,10 @@
 // load straight into the MFMA with no vector-ALU work at all, and each weight
 // byte is still read from HBM exactly once.  The activations stay accurate:
 // they are kept as two bf16 numbers hi + lo (hi = bf16(x), lo = bf16(x - hi),
-// about 16 significant bits) and each weight tile is multiplied by both - the
+// about 16 significant bits; three or four rows as three numbers, all 24 bits)
+// and each weight tile is multiplied by every one - the
 // matrix cores have an order of magnitude more throughput than the HBM stream
-// needs, so the second product is free.
+// needs, so the second product is free; up to eight rows one product does for all (kPackCols).
 //
 // A block owns a group of 16*RT weight rows (SWIGLU: of each of the two
 // matrices); its KS waves split K in interleaved 128-element steps (a lane loads 64
@@ -480,8 +482,8 @@ __global__ __launch_bounds__(KS * 64) void skinny_gemm_kernel(GemmArgs a)
         }
         if constexpr (PACK == 3) {
             // A step's sum on its own, then onto the total: half the rounding error of one long chain in the matrix
-            // cores, and below that of the vector kernel (relative error against float64, K = 1024 / 4096 / 12288:
-            // 0.8 / 0.9 / 1.2e-7; one chain 1.0 / 1.9 / 3.3e-7, vector kernel 0.9 / 1.1 / 1.4e-7).
+            // cores, and below that of the vector kernel (relative error of logits against float64, K = 1024 / 4096 / 12288:
+            // 0.9 / 1.1 / 1.3e-7; vector kernel 0.9 / 1.2 / 1.5e-7; one chain of products alone 1.0 / 1.9 / 3.3e-7).
 #pragma unroll
             for (int m = 0; m < NA; m++) {
                 f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};

@@ -1,19 +1,20 @@
-// Skinny GEMM whose waves share one activation tile (batches of 17..64 rows).
+// Skinny GEMM whose waves share one activation tile.
 //
 // Same contract and epilogues as skinny_gemm_kernel (dk_gemm.hip.h).  There every wave of a block
 // takes other K-steps, so every wave fetches its own activation operands: 8 KB of bf16 hi/lo
-// per 128-column step and 16 batch rows, against 4 KB of weights per row tile.  At 16 batch rows
-// that is affordable (and that kernel is the faster one); at 32..64 rows the activation traffic
-// is 4..8 times the weight stream and bounds the kernel.  Here all W waves of a block walk the SAME
+// per 128-column step and 16 batch rows, against 4 KB of weights per row tile.  At 32..64 rows that
+// is 4..8 times the weight stream and bounds the kernel; up to 16 rows it matters where a wave has
+// one row tile or the stream is long.  Here all W waves of a block walk the SAME
 // K-steps and own different row tiles: the block fetches each step's activation tile once,
 // 16 bytes per thread, puts it into LDS, and every wave reads its matrix-core operands from
 // there.  A wave then carries only weights (and its 16-byte share of the activations) in
 // flight, so the software pipeline can be deeper for the same registers, and a tile's sum over
 // K is complete in one wave - no reduction across waves.
 //
-// The price is a barrier per K-step, which couples the waves of a block to its slowest load;
-// measured on the 8B / 3B / 0.6B shapes this pays for the lm_head from 17 rows on (2-3.5x) and for
-// the large layer matrices from 33 rows on (1.2-1.6x), and loses elsewhere - the host picks.
+// The price is a barrier per K-step, which couples the waves of a block to its slowest load.  Measured
+// on the 8B / 3B / 0.6B shapes this pays above 16 rows for the lm_head (2-3.5x) and for the large layer
+// matrices from 33 rows on (1.2-1.6x); up to 16 rows for the lm_head, long residual projections and the
+// gate/up pairs of more than two row tiles per compute unit (both sides at gemm_plan_16) - the host picks.
 //
 // A matrix with few row tiles would leave compute units idle, so K can be cut into gridDim.y
 // slices.  Each block then stores its partial tiles (device-coherent stores: the dies' L2s
