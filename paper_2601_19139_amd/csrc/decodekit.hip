@@ -1224,7 +1224,7 @@ dk_status dk_prefill_chunk(dk_model *model, dk_kv_pool *pool, const int32_t *d_b
 }
 
 namespace {
-struct SampleScratch { size_t p, pmax, part_a, part_b, st_a, st_b, item_val, item_cnt, total; };
+struct SampleScratch { size_t p, pmax, part, tickets, hist, st_a, st_b, item_val, item_cnt, total; };
 SampleScratch sample_scratch(int B, int V)
 {
     SampleScratch L{};
@@ -1232,13 +1232,15 @@ SampleScratch sample_scratch(int B, int V)
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
     L.p = take((size_t)B * V * 4);
     L.pmax = take((size_t)B * dk::kSampleBlocks * 4);
-    L.part_a = take((size_t)B * dk::kSampleBlocks * 16 * 4);
-    L.part_b = take((size_t)B * dk::kSampleBlocks * 16 * 4);
+    L.part = take((size_t)B * dk::kSampleBlocks * 16 * 4);   // (the searches use 64 floats a row of these two)
+    L.tickets = take((size_t)B * dk::kSampleBlocks * 16 * 4);
     L.st_a = take((size_t)B * sizeof(dk::SampleState));
     L.st_b = take((size_t)B * sizeof(dk::SampleState));
     L.item_val = take((size_t)B * dk::kSampleItems * 4);
     L.item_cnt = take((size_t)B * dk::kSampleItems * 4);
     L.total = off;
+    L.hist = L.item_val;   // the searches' histograms, where the selection path has its items
+    static_assert(3 * dk::kSampleBins * sizeof(unsigned long long) <= 2 * dk::kSampleItems * 4, "three histograms a row");
     return L;
 }
 }  // namespace
@@ -1279,22 +1281,33 @@ dk_status dk_sample_tokens(const float *d_logits, int32_t B, int32_t V, const dk
     a.seed_hi = (uint32_t)(params->seed >> 32);
     a.step_lo = (uint32_t)step;
     a.step_hi = (uint32_t)(step >> 32);
-    float *part[2] = {reinterpret_cast<float *>(base + L.part_a), reinterpret_cast<float *>(base + L.part_b)};
+    a.part = reinterpret_cast<float *>(base + L.part);
+    a.tickets = reinterpret_cast<int *>(base + L.tickets);
+    // totals of V weights of at most 1 are at most 2^63
+    a.mass_bits = 63;
+    for (int n = V; n > 1; n = (n + 1) / 2) a.mass_bits--;
     dk::SampleState *state[2] = {reinterpret_cast<dk::SampleState *>(base + L.st_a),
                                  reinterpret_cast<dk::SampleState *>(base + L.st_b)};
-    int cur = 0;   // the buffers the last launch wrote
-    auto launch = [&](int stage, int grid_x) {
-        a.stage = stage;
-        a.part_in = part[cur];
-        a.st_in = state[cur];
-        a.part_out = part[cur ^ 1];
-        a.st_out = state[cur ^ 1];
-        hipLaunchKernelGGL(dk::sample_kernel, dim3(grid_x, B), dim3(dk::kSampleThreads), 0, st, a);
-        cur ^= 1;
+    // three histograms in turn: the one the last launch added to, the one this launch adds to, the one it clears
+    unsigned long long *hist = reinterpret_cast<unsigned long long *>(base + L.hist);
+    const size_t hist_words = (size_t)B * dk::kSampleBins;
+    int n_launch = 0;
+    auto launch = [&](void (*kernel)(dk::SampleArgs), int grid_x) {
+        a.st_in = state[n_launch & 1];
+        a.st_out = state[(n_launch & 1) ^ 1];
+        a.hist_in = hist + (size_t)((n_launch + 2) % 3) * hist_words;
+        a.hist_out = hist + (size_t)(n_launch % 3) * hist_words;
+        a.hist_clear = hist + (size_t)((n_launch + 1) % 3) * hist_words;
+        hipLaunchKernelGGL(kernel, dim3(grid_x, B), dim3(dk::kSampleThreads), 0, st, a);
+        n_launch++;
     };
     const bool use_k = params->top_k > 0 && params->top_k < V, use_p = params->top_p < 1.f;
-    launch(dk::SAMPLE_MAX, dk::kSampleBlocks);
-    if (use_k && params->top_k <= dk::kSampleFastK && V <= dk::kSampleBlocks * dk::kSampleSliceMax) {
+    const bool select = use_k && params->top_k <= dk::kSampleFastK && V <= dk::kSampleBlocks * dk::kSampleSliceMax;
+    a.search = (use_k || use_p) && !select;
+    a.count = use_k;
+    a.negligible = use_k ? 0.f : (1.f - params->top_p) / (2.f * (float)V);
+    launch(dk::sample_max_kernel, dk::kSampleBlocks);
+    if (select) {
         // few candidates: the weights and the slices' top k, then one block per row for thresholds and draw
         dk::SampleSelectArgs s{};
         s.logits = d_logits;
@@ -1316,33 +1329,33 @@ dk_status dk_sample_tokens(const float *d_logits, int32_t B, int32_t V, const dk
         DK_HIP(hipGetLastError());
         return DK_OK;
     }
-    launch(dk::SAMPLE_EXP, dk::kSampleBlocks);
-    if (use_k) {
-        a.count = 1;
-        a.need_from_mass = 0;
-        for (int shift = 28; shift >= 0; shift -= 4) {
+    // a search: a launch per digit makes its histogram (the first: the launch that makes the weights, or the one that
+    // settles the top-k threshold), the next one settles it
+    auto later_digits = [&](bool count) {
+        a.count = a.count_in = count;
+        for (int shift = dk::kSampleTopShift - dk::kSampleDigitBits; shift >= 0; shift -= dk::kSampleDigitBits) {
             a.shift = shift;
-            a.first = (shift == 28);
-            launch(dk::SAMPLE_PASS, dk::kSampleBlocks);
+            a.first = shift == dk::kSampleTopShift - dk::kSampleDigitBits;
+            launch(dk::sample_kernel<dk::SAMPLE_PASS>, dk::kSampleBlocks);
         }
-        a.settle = 1;
-        launch(dk::SAMPLE_MASS, dk::kSampleBlocks);
+        a.first = 0;
+    };
+    launch(a.search ? dk::sample_kernel<dk::SAMPLE_EXP_DIGIT> : dk::sample_kernel<dk::SAMPLE_EXP>, dk::kSampleBlocks);
+    if (!a.search) {
+        launch(dk::sample_kernel<dk::SAMPLE_DRAW>, 1);
+        DK_HIP(hipGetLastError());
+        return DK_OK;
     }
-    if (use_p) {
+    if (use_k) later_digits(true);
+    if (use_k && use_p) {
+        a.second = 1;
         a.count = 0;
-        for (int shift = 28; shift >= 0; shift -= 4) {
-            a.shift = shift;
-            a.first = (shift == 28);
-            a.need_from_mass = a.first;
-            launch(dk::SAMPLE_PASS, dk::kSampleBlocks);
-        }
-        a.settle = 1;
-    } else {
-        a.settle = 0;
+        a.shift = dk::kSampleTopShift;
+        launch(dk::sample_kernel<dk::SAMPLE_PASS>, dk::kSampleBlocks);
+        a.second = 0;
     }
-    // with neither threshold every weight is kept: the slices' totals are already there
-    if (use_k || use_p) launch(dk::SAMPLE_KEEP, dk::kSampleBlocks);
-    launch(dk::SAMPLE_DRAW, 1);
+    if (use_p) later_digits(false);
+    launch(dk::sample_kernel<dk::SAMPLE_KEEP>, dk::kSampleBlocks);
     DK_HIP(hipGetLastError());
     return DK_OK;
 }

@@ -13,14 +13,21 @@
 //
 // A vocabulary of 150 000 entries is too much for one compute unit per row, so a row is
 // spread over kSampleBlocks blocks (slice g of the row belongs to block g).  In general the
-// work is a chain of launches of one kernel (its `stage` argument says which step):
-// thresholds are found by a radix search on the bit pattern of the (non-negative) float
-// threshold - count / mass above a threshold is monotone, so a pass tries the 15 next-digit
-// candidates at once and settles four bits; eight passes settle all of them.  A pass leaves
-// per-block partial totals; the next launch adds them in block order (every block does,
-// redundantly) and decides the digit.  With a small top_k (the usual serving setting) the
-// candidates are selected slice by slice instead and a call is three launches (below).
-// Float sums have a fixed order everywhere and counts are integers: a call is repeatable
+// work is a chain of launches (the stages of sample_kernel):
+// thresholds are found by a radix search on the bit pattern of the threshold, ten bits at a
+// time.  A weight lies in [0, 1], so its pattern has 30 bits and three digits settle it.  Every
+// launch of a search leaves the row's histogram of one digit - how much weights of each digit
+// count (top-k) or weigh (top-p) - and the next launch settles the digit from it.  Masses are
+// whole numbers of 2^-mass_bits there, truncated: V weights lose less than V * 2^-mass_bits of a
+// total of at least 1, 2^-27 for 2^18 of them.  So the blocks add to a histogram in any order and
+// the totals are still the same bits.  What bounds the chain is the number of
+// dependent launches, 5 to 7 us each: digits of four bits with the candidates' float totals
+// took 12 launches for top-p alone and 21 with both thresholds, now 5 and 8.
+// us a call, then and now: 16 rows of 151936, top-p 0.9 79.5 -> 43.9 (flat rows 79.8 -> 48.3), top-k 100 82.0 -> 46.1,
+// both 141.1 -> 63.5; one row 60.4 -> 25.8; 64 rows 200.6 -> 107.4; 1 x 1000 41.3 -> 19.9, 64 x 32000 112.5 -> 72.1.
+// With a small top_k (the usual serving setting) the candidates are selected slice by slice
+// instead and a call is three launches (below).
+// Other float sums have a fixed order and counts are integers: a call is repeatable
 // bit for bit.
 #pragma once
 #include "dk_common.hip.h"
@@ -45,66 +52,100 @@ __device__ __forceinline__ uint32_t philox4x32_10_first(uint32_t c0, uint32_t c1
 constexpr int kSampleBlocks = 64;    // blocks per row
 constexpr int kSampleThreads = 256;
 
+constexpr int kSampleDigitBits = 10;
+constexpr int kSampleBins = 1 << kSampleDigitBits;
+constexpr int kSampleTopShift = 20;  // of the first of three digits: weights are at most 1, 30 bits
+
 // per-row search state handed from one launch to the next
 struct SampleState {
-    uint32_t prefix;      // threshold bits settled so far
-    float need;           // total the threshold has to reach
-    uint32_t floor_bits;  // only weights >= this (the top-k threshold) take part
-    uint32_t pad;
+    unsigned long long need;   // what the weights of the settled prefix still have to reach
+    uint32_t prefix;           // threshold bits settled so far
+    uint32_t floor_bits;       // only weights >= this (the top-k threshold) take part
 };
 
 enum {
-    SAMPLE_MAX = 0,       // per-block maximum of logit / T
-    SAMPLE_EXP,           // weights p, per-block total
-    SAMPLE_PASS,          // settle the previous digit (unless first), partial totals of the next digit's candidates
-    SAMPLE_MASS,          // settle the last digit of the top-k search; per-block candidate mass
-    SAMPLE_KEEP,          // settle the last digit; per-block kept mass
-    SAMPLE_DRAW           // one block per row: the draw
+    SAMPLE_EXP = 0,       // no search follows: weights p, per-block total
+    SAMPLE_EXP_DIGIT,     // weights p, the first digit's histogram
+    SAMPLE_PASS,          // settle the previous digit, histogram of the next one (of this search or of the second)
+    SAMPLE_KEEP,          // settle the last digit; per-block kept mass; the row's last block draws
+    SAMPLE_DRAW           // no thresholds: one block per row draws
 };
 
 struct SampleArgs {
     const float *logits;   // [B][V]
     float *p;              // [B][V] weights
     float *pmax;           // [B][kSampleBlocks]
-    float *part_in, *part_out;      // [B][kSampleBlocks][16] partial totals (ping-pong)
+    float *part;           // [B][kSampleBlocks] the slices' masses for the draw
     SampleState *st_in, *st_out;    // [B] (ping-pong)
+    // [B][kSampleBins] each: settled, added to (zero before the launch), cleared for the next launch
+    unsigned long long *hist_in, *hist_out, *hist_clear;
+    int *tickets;          // [B]: blocks of a row that have left their kept mass
     int *out;              // [B]
-    int V, stage;
-    int shift;             // SAMPLE_PASS: bit position of the digit whose candidates are totalled
-    int first;             // SAMPLE_PASS: no previous digit to settle; start a new search
-    int count;             // SAMPLE_PASS: totals are counts (top-k) instead of masses (top-p)
-    int settle;            // SAMPLE_MASS / SAMPLE_KEEP: a search precedes, its last digit is settled here
-    int need_from_mass;    // SAMPLE_PASS with first: need = top_p * (sum of the blocks' masses in part_in)
+    int V;
+    int search;            // a search follows: sample_max_kernel clears what it starts from
+    int shift;             // SAMPLE_PASS: bit position of the digit whose histogram is made
+    int first;             // SAMPLE_PASS, SAMPLE_KEEP: hist_in is a search's first digit
+    int count_in, count;   // hist_in / hist_out hold counts (top-k) instead of masses (top-p)
+    int second;            // SAMPLE_PASS: hist_in was the top-k search's last digit, the top-p search begins
+    int mass_bits;
+    float negligible;      // SAMPLE_EXP_DIGIT: weights below this go to digit 0 (see there)
     float temperature, top_p;
     int top_k;
     uint32_t seed_lo, seed_hi, step_lo, step_hi;
 };
 
-// The digit (0..15) of a finished pass: the largest candidate whose total over all blocks,
-// added in block order, still reaches `need`.  Called by every thread of the block.  A candidate's
-// 64 partial totals are requested together and then added: with the requests inside the adding loop
-// a settle is a few round trips instead of one.  Top-p alone, a call of 12 launches, adding loop -> this, together
-// with the same change where the mass and the kept mass are added up: one row of 1000 weights 50.0 -> 42.0 us,
-// 64 rows of 1000 111.9 -> 101.6, 64 rows of 151936 217.6 -> 201.1.  Bringing the totals in by all threads and
-// adding them from LDS costs two more barriers and an LDS pass: 43.0, 110.0 and 206.4 us.
-__device__ __forceinline__ uint32_t settle_digit(const float *part, float need, float *sm /*[16]*/)
+// The weight with bit pattern `bits` in [0, 1] as a whole number of 2^-mass_bits, truncated.
+__device__ __forceinline__ unsigned long long sample_fixed(uint32_t bits, int mass_bits)
 {
-    const int tid = threadIdx.x;
-    __syncthreads();
-    if (tid < 15) {
-        float v[kSampleBlocks], t = 0.f;
+    const int sh = (int)(bits >> 23) - 150 + mass_bits;
+    const unsigned long long m = (bits & 0x7fffffu) | 0x800000u;
+    return sh >= 0 ? m << sh : m >> min(-sh, 63);
+}
+
+// Settles a digit from the row's histogram: the largest one whose total together with those above it
+// reaches `need` (first: need is made of the histogram's own total).  Called by every thread of the block.
+__device__ __forceinline__ SampleState sample_settle(const SampleArgs &a, SampleState st, int b, int digit_shift,
+                                                     unsigned long long *sm_w /*[4]*/, unsigned long long *sm_r /*[2]*/)
+{
+    constexpr int PER = kSampleBins / kSampleThreads;
+    static_assert(PER == 4, "two 16-byte loads a thread");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // thread t holds the digits from the top: bins kSampleBins-1-4t down
+    const ulonglong2 *hp = reinterpret_cast<const ulonglong2 *>(a.hist_in + (int64_t)b * kSampleBins + kSampleBins - 4 - PER * tid);
+    const ulonglong2 h10 = hp[0], h32 = hp[1];
+    const unsigned long long h[PER] = {h32.y, h32.x, h10.y, h10.x};
+    const unsigned long long own = h[0] + h[1] + h[2] + h[3];
+    unsigned long long inc = own;
 #pragma unroll
-        for (int g = 0; g < kSampleBlocks; g++) v[g] = part[g * 16 + tid];
-#pragma unroll
-        for (int g = 0; g < kSampleBlocks; g++) t += v[g];
-        sm[tid] = t;
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long o = __shfl_up(inc, d, 64);
+        inc += lane >= d ? o : 0ull;
     }
     __syncthreads();
-    uint32_t digit = 0;
+    if (lane == 63) sm_w[wave] = inc;
+    if (tid == 0) sm_r[0] = sm_r[1] = 0ull;   // nothing reaches it: digit 0
+    __syncthreads();
+    unsigned long long total = 0ull, over = inc - own;
 #pragma unroll
-    for (int d = 0; d < 15; d++)
-        if (sm[d] >= need) digit = (uint32_t)(d + 1);     // totals fall as d grows: the last hit is the largest
-    return digit;
+    for (int w = 0; w < 4; w++) {
+        over += w < wave ? sm_w[w] : 0ull;
+        total += sm_w[w];
+    }
+    if (a.first) st.need = a.count_in ? (unsigned long long)a.top_k : (unsigned long long)ceil((double)a.top_p * (double)total);
+    // at most one thread's four digits hold it (the topmost digit where nothing is needed: a row without a mass)
+    if (over + own >= st.need && (over < st.need || (tid == 0 && st.need == 0ull))) {
+        unsigned long long run = over;
+        int i = 0;
+#pragma unroll
+        for (int k = 0; k < PER - 1; k++)
+            if (i == k && run + h[k] < st.need) { run += h[k]; i++; }
+        sm_r[0] = (unsigned long long)(kSampleBins - 1 - PER * tid - i);
+        sm_r[1] = run;
+    }
+    __syncthreads();
+    st.prefix |= (uint32_t)sm_r[0] << digit_shift;
+    st.need -= sm_r[1];
+    return st;
 }
 
 // Sum over the block in a fixed order; every thread gets it.
@@ -552,38 +593,73 @@ __global__ __launch_bounds__(kSampleThreads) void sample_merge_draw_kernel(Sampl
                     sm_i);
 }
 
+// grid (kSampleBlocks, B): the slices' maxima of logit / T.  A search's first histogram and its ticket are cleared here.
+__global__ __launch_bounds__(kSampleThreads) void sample_max_kernel(SampleArgs a)
+{
+    __shared__ float sm[4];
+    const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
+    const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
+    const int i0 = min(g * slice, V), i1 = min(i0 + slice, V);
+    const float *l = a.logits + (int64_t)b * V;
+    // four loads in flight; an address past the slice is clamped (a value twice does not change a maximum)
+    float mx = -INFINITY;
+    for (int i = i0 + tid; i < i1; i += 4 * kSampleThreads) {
+        const float x0 = l[i], x1 = l[min(i + kSampleThreads, i1 - 1)], x2 = l[min(i + 2 * kSampleThreads, i1 - 1)],
+                    x3 = l[min(i + 3 * kSampleThreads, i1 - 1)];
+        mx = fmaxf(fmaxf(fmaxf(mx, x0 / a.temperature), fmaxf(x1 / a.temperature, x2 / a.temperature)), x3 / a.temperature);
+    }
+    mx = max64(mx);
+    if ((tid & 63) == 0) sm[tid >> 6] = mx;
+    __syncthreads();
+    if (tid == 0) a.pmax[b * kSampleBlocks + g] = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+    constexpr int CLEAR = kSampleBins / kSampleBlocks;
+    if (a.search) {
+        if (tid < CLEAR) a.hist_clear[(int64_t)b * kSampleBins + g * CLEAR + tid] = 0ull;
+        if (g == 0 && tid == 0) a.tickets[b] = 0;
+    }
+}
+
+// A kernel per stage: with all of them in one the shorter ones carry the searches' LDS and registers (16 rows of 151936
+// without thresholds 14.0 -> 14.5 us).
+template <int STAGE>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
 {
-    __shared__ float sm[16];
-    __shared__ float red[4 * 15];
-    __shared__ __align__(16) float scan[kSampleThreads];
-    __shared__ float tot[kSampleBlocks];
+    __shared__ unsigned long long hist[kSampleBins];
+    __shared__ unsigned long long sm_w[4], sm_r[2];
+    __shared__ float sm[8];
+    __shared__ float mass[kSampleBlocks];
     __shared__ int sm_i[12];
     const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
     const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
     const int i0 = min(g * slice, V), i1 = min(i0 + slice, V);
     const float *l = a.logits + (int64_t)b * V;
     float *p = a.p + (int64_t)b * V;
-    float *part_out = a.part_out + ((int64_t)b * kSampleBlocks + g) * 16;
-    const float *part_in = a.part_in + (int64_t)b * kSampleBlocks * 16;
 
-    if (a.stage == SAMPLE_MAX) {
-        // four loads in flight; an address past the slice is clamped (a value twice does not change a maximum)
-        float mx = -INFINITY;
-        for (int i = i0 + tid; i < i1; i += 4 * kSampleThreads) {
-            const float x0 = l[i], x1 = l[min(i + kSampleThreads, i1 - 1)], x2 = l[min(i + 2 * kSampleThreads, i1 - 1)],
-                        x3 = l[min(i + 3 * kSampleThreads, i1 - 1)];
-            mx = fmaxf(fmaxf(fmaxf(mx, x0 / a.temperature), fmaxf(x1 / a.temperature, x2 / a.temperature)), x3 / a.temperature);
-        }
-        mx = max64(mx);
-        if ((tid & 63) == 0) sm[tid >> 6] = mx;
+    // this block's share of the histogram that the next launch adds to
+    constexpr int CLEAR = kSampleBins / kSampleBlocks;
+    if ((STAGE == SAMPLE_EXP_DIGIT || STAGE == SAMPLE_PASS) && tid < CLEAR) a.hist_clear[(int64_t)b * kSampleBins + g * CLEAR + tid] = 0ull;
+    // the block's histogram onto the row's
+    auto add_hist = [&]() {
         __syncthreads();
-        if (tid == 0) a.pmax[b * kSampleBlocks + g] = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-        return;
-    }
-    if (a.stage == SAMPLE_EXP) {
+#pragma unroll
+        for (int k = tid; k < kSampleBins; k += kSampleThreads)
+            if (hist[k])
+                __hip_atomic_fetch_add(a.hist_out + (int64_t)b * kSampleBins + k, hist[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+
+    if constexpr (STAGE == SAMPLE_EXP || STAGE == SAMPLE_EXP_DIGIT) {
+        constexpr bool DIGIT = STAGE == SAMPLE_EXP_DIGIT;
         const float mx = max64(a.pmax[b * kSampleBlocks + (tid & 63)]);
+        if constexpr (DIGIT) {
+#pragma unroll
+            for (int k = tid; k < kSampleBins; k += kSampleThreads) hist[k] = 0ull;
+            __syncthreads();
+        }
         float z = 0.f;
+        // Top-p: weights below (1 - top_p) / 2V weigh less than half of what may stay outside the nucleus, all of them
+        // together, so its threshold lies above them and only their sum matters.  They are most of a trained model's
+        // row; in their own digits they would be hundreds of atomics per block on the row's histogram.
+        unsigned long long rest = 0ull;
         for (int i = i0 + tid; i < i1; i += 4 * kSampleThreads) {     // four loads in flight
             float x[4];
 #pragma unroll
@@ -594,105 +670,70 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
                     const float v = expf(x[j] / a.temperature - mx);
                     p[i + j * kSampleThreads] = v;
                     z += v;
+                    const uint32_t bits = __float_as_uint(v);
+                    if (DIGIT && v >= 0.f) {   // (not a NaN: a row whose maximum is infinite)
+                        const unsigned long long w = a.count ? 1ull : sample_fixed(bits, a.mass_bits);
+                        if (v < a.negligible) rest += w;
+                        else atomicAdd(&hist[min(bits >> kSampleTopShift, (uint32_t)kSampleBins - 1)], w);
+                    }
                 }
         }
-        z = sample_block_sum(z, sm);
-        if (tid == 0) part_out[0] = z;
-        if (g == 0 && tid == 0) a.st_out[b] = SampleState{0u, 0.f, 0u, 0u};
+        if constexpr (DIGIT) {
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) rest += __shfl_xor(rest, d, 64);
+            if ((tid & 63) == 0 && rest) atomicAdd(&hist[0], rest);
+            add_hist();
+            if (g == 0 && tid == 0) a.st_out[b] = SampleState{0ull, 0u, 0u};
+        } else {
+            z = sample_block_sum(z, sm);
+            if (tid == 0) a.part[b * kSampleBlocks + g] = z;
+        }
         return;
     }
-    if (a.stage == SAMPLE_DRAW) {
-        // g == 0 only (grid.x = 1)
-        sample_draw_row(p, part_in, 16, __uint_as_float(a.st_in[b].prefix), V, b, a.seed_lo, a.seed_hi, a.step_lo,
-                        a.step_hi, a.out, sm, sm_i);
+    if constexpr (STAGE == SAMPLE_DRAW) {
+        // g == 0 only (grid.x = 1): without thresholds every weight is kept, the slices' totals are already there
+        sample_draw_row(p, a.part + b * kSampleBlocks, 1, 0.f, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
         return;
     }
 
     // ---- the threshold searches ------------------------------------------------------------
-    // What bounds a launch here is its chain of round trips (state, totals of the pass before, slice), not its
-    // bytes.  The slice is walked after the digit is settled, by a plain loop: holding it in registers, requested
-    // ahead of the settle, saves a round trip (one row of 151936: 61.8 -> 61.2 us a call) but unrolls the
-    // candidates' sums sixteen times, which costs every launch more than that on short slices (one row of 1000:
-    // 42.0 -> 49.2) and on many rows (64 rows of 32000: 113.7 -> 164.9).
-    SampleState st = a.st_in[b];
-    if (a.stage == SAMPLE_PASS && a.first) {
-        // a new search: top-k counts every weight; top-p only the candidates of top-k (the
-        // settled threshold of the search before, which SAMPLE_MASS left in floor_bits)
-        st.prefix = 0;
-        if (a.count) {
-            st.need = (float)a.top_k;
-            st.floor_bits = 0;
-        }
-        if (a.need_from_mass) {
-            if (tid < kSampleBlocks) tot[tid] = part_in[tid * 16];
-            __syncthreads();
-            float z = 0.f;
+    if constexpr (STAGE == SAMPLE_PASS) {
+        SampleState st = a.st_in[b];
 #pragma unroll
-            for (int k = 0; k < kSampleBlocks; k++) z += tot[k];
-            st.need = a.top_p * z;
-        }
-    } else if (a.stage == SAMPLE_PASS || a.settle) {
-        // the digit of the pass before (its position: 4 bits above this pass's, or bit 0)
-        const int prev_shift = (a.stage == SAMPLE_PASS) ? a.shift + 4 : 0;
-        st.prefix |= settle_digit(part_in, st.need, sm) << prev_shift;
-    }
-    const float floor_t = __uint_as_float(st.floor_bits);
-
-    if (a.stage == SAMPLE_PASS) {
-        float acc[15];
-#pragma unroll
-        for (int d = 0; d < 15; d++) acc[d] = 0.f;
+        for (int k = tid; k < kSampleBins; k += kSampleThreads) hist[k] = 0ull;
+        st = sample_settle(a, st, b, a.second ? 0 : a.shift + kSampleDigitBits, sm_w, sm_r);   // (its barriers also order the clearing)
+        if (a.second) st = SampleState{0ull, 0u, st.prefix};   // the top-k threshold: the floor of the second search
+        const float floor_t = __uint_as_float(st.floor_bits);
+        const int above = a.shift + kSampleDigitBits;          // the bits of the prefix: 30 - none - for a search's first digit
         for (int i = i0 + tid; i < i1; i += kSampleThreads) {
             const float v = p[i];
-            const float w = (v >= floor_t) ? (a.count ? 1.f : v) : 0.f;
             const uint32_t bits = __float_as_uint(v);
-#pragma unroll
-            for (int d = 0; d < 15; d++)
-                acc[d] += (bits >= (st.prefix | ((uint32_t)(d + 1) << a.shift))) ? w : 0.f;
+            if (v >= floor_t && bits >> above == st.prefix >> above)
+                atomicAdd(&hist[(bits >> a.shift) & (kSampleBins - 1)], a.count ? 1ull : sample_fixed(bits, a.mass_bits));
         }
-#pragma unroll
-        for (int d = 0; d < 15; d++) acc[d] = sum64(acc[d]);
-        __syncthreads();
-        if ((tid & 63) == 0) {
-#pragma unroll
-            for (int d = 0; d < 15; d++) red[(tid >> 6) * 15 + d] = acc[d];
-        }
-        __syncthreads();
-        if (tid < 15) part_out[tid] = red[tid] + red[15 + tid] + red[30 + tid] + red[45 + tid];
+        add_hist();
         if (g == 0 && tid == 0) a.st_out[b] = st;
         return;
     }
-    if (a.stage == SAMPLE_MASS) {
-        // st.prefix is now the top-k threshold: it becomes the floor of what follows
-        const float tau_k = __uint_as_float(st.prefix);
-        float z = 0.f;
-        for (int i = i0 + tid; i < i1; i += kSampleThreads) z += (p[i] >= tau_k) ? p[i] : 0.f;
-        z = sample_block_sum(z, sm);
-        if (tid == 0) part_out[0] = z;
-        if (g == 0 && tid == 0) a.st_out[b] = SampleState{st.prefix, 0.f, st.prefix, 0u};
-        return;
-    }
-    // SAMPLE_KEEP: the final threshold is the larger of the two searches'; kept mass of the
-    // slice in index order (thread pieces in thread order)
-    const uint32_t tau_bits = max(st.prefix, st.floor_bits);
-    const float tau = __uint_as_float(tau_bits);
-    {
-        const int piece = (slice + kSampleThreads - 1) / kSampleThreads;
-        const int j0 = min(i0 + tid * piece, i1), j1 = min(j0 + piece, i1);
-        float mine = 0.f;
-        for (int i = j0; i < j1; i++) mine += (p[i] >= tau) ? p[i] : 0.f;
-        scan[tid] = mine;
-        __syncthreads();
+    if constexpr (STAGE == SAMPLE_KEEP) {
+        // SAMPLE_KEEP: the final threshold is the larger of the two searches'; kept mass of the slice, in a fixed order
+        const SampleState st = sample_settle(a, a.st_in[b], b, 0, sm_w, sm_r);
+        const uint32_t tau_bits = max(st.prefix, st.floor_bits);
+        const float tau = __uint_as_float(tau_bits);
+        float kept = 0.f;
+        for (int i = i0 + tid; i < i1; i += kSampleThreads) kept += (p[i] >= tau) ? p[i] : 0.f;
+        kept = sample_block_sum(kept, sm);
         if (tid == 0) {
-            float t = 0.f;
-#pragma unroll 16
-            for (int k = 0; k < kSampleThreads; k += 4) {
-                const float4 v = ldf4(scan + k);
-                t += v.x; t += v.y; t += v.z; t += v.w;
-            }
-            part_out[0] = t;
-            if (g == 0) a.st_out[b] = SampleState{tau_bits, 0.f, 0u, 0u};
+            // device-coherent: the row's last block may run on another die
+            __hip_atomic_store(&a.part[b * kSampleBlocks + g], kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            drain_stores();
+            sm_i[0] = __hip_atomic_fetch_add(&a.tickets[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        __syncthreads();
+        if (sm_i[0] != kSampleBlocks - 1) return;
+        if (tid < kSampleBlocks)
+            mass[tid] = __hip_atomic_load(&a.part[b * kSampleBlocks + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sample_draw_row(p, mass, 1, tau, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
     }
 }
 

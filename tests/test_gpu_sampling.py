@@ -118,6 +118,50 @@ def test_sampler_matches_oracle(dk, orc, V, B, T, top_k, top_p):
     assert same >= 6 * B, f"only {same} of {12 * B} draws equal the oracle's"
 
 
+@pytest.mark.parametrize("row,V,top_k,top_p", [
+    ("flat", 4096, 0, 0.37),          # every weight the same: all of them in one digit, all tied at the threshold
+    ("flat", 1, 0, 0.5),
+    ("two_levels", 5000, 0, 0.9),     # the threshold on the upper of two values, the lower ones negligible or not
+    ("two_levels", 5000, 700, 0.9),
+    ("half_excluded", 3001, 0, 0.8),  # logits of minus infinity: weight zero
+    ("half_excluded", 3001, 2000, 0.8),   # ... and fewer others than top_k
+    ("ties", 5000, 300, 1.0),         # the 300th largest is one of 500 equal ones
+    ("wide", 20000, 0, 0.999),        # weights down to 1e-30: most of them negligible
+])
+def test_threshold_searches(dk, orc, row, V, top_k, top_p):
+    """The searches over whole rows (no small top_k) where digits, ties and negligible weights meet: the kept set must
+    be the oracle's, seen through draws at many u."""
+    import torch
+    rng = np.random.default_rng(V)
+    l = rng.normal(size=V).astype(np.float32)
+    if row == "flat":
+        l[:] = 1.5
+    elif row == "two_levels":
+        l[:] = np.where(np.arange(V) % 50 == 3, 9.0, -4.0)
+    elif row == "half_excluded":
+        l[::2] = -np.inf
+    elif row == "ties":
+        l[100:600] = 2.0
+    else:
+        l *= 20.0
+    B = 16
+    d_logits = torch.from_numpy(np.tile(l, (B, 1))).cuda()
+    scratch = torch.full((dk.sample_scratch_bytes(B, V),), 255, dtype=torch.uint8, device="cuda")   # nothing cleared before
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    exact = 0
+    for step in range(6):
+        dk.sample_tokens(d_logits, 1.0, top_k, top_p, 77, step, scratch, out)
+        got = out.cpu().numpy()
+        for b in range(B):
+            u = orc.sample_uniform(77, step, b)
+            m_u, m_p, kept = oracle_margins(l, 1.0, top_k, top_p, u)
+            assert m_p < 1e-6 or got[b] in kept, (step, b, got[b])
+            if m_u > 1e-5 and m_p > 1e-6:
+                assert got[b] == orc.sample(l, 1.0, top_k, top_p, u), (step, b, got[b])
+                exact += 1
+    assert exact >= 4 * B
+
+
 def test_sampled_distribution_on_device(dk):
     """Many independent draws (one per row and step) follow the softmax probabilities."""
     import torch
