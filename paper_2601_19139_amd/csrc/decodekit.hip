@@ -181,6 +181,7 @@ struct Workspace {
     bool defer_merge;   // small problems: the output projection merges the attention chunks
     bool attn_mfma;     // the matrix-core attention kernel (otherwise the vector-ALU one)
     bool attn_light;    // ... without the register double buffer (short chunks)
+    bool attn_plan;     // contexts split on the device, from the rows' lengths (make_attn_plan)
 };
 
 constexpr int kMaxGemvBatch = 4;  // the most rows the vector-ALU GEMV takes (fewer where pack_terms, 4-bit weights or experts ask for the matrix cores)
@@ -411,6 +412,10 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
         w.fused_sets = take((size_t)2 * w.fused_set_floats * 4);
         w.fused_status = take(64);
     }
+    // The plan is worth its look-up where a chunk can get shorter than the tables' width gives it, and lies in the
+    // float32 attention output, which the batched path does not write.
+    w.attn_plan = w.batched && !w.defer_merge && w.chunk_tokens >= 256 && B * w.max_chunks <= dk::kPlanMaxItems &&
+                  (B * w.max_chunks + 1) * dk::kPlanWords <= B * c.n_q_heads * d;
     w.total = off;
     return w;
 }
@@ -669,26 +674,26 @@ dk_status launch_gemm(const dk::GemmArgs &a, int Bp, hipStream_t st)
 }
 
 // light: without the register double buffer (short chunks, query groups of up to 4: the host's choice)
-template <int D, int G>
+template <int D, int G, bool PLAN>
 void launch_attention_mfma(const dk::AttnArgs &a, dim3 grid, bool light, hipStream_t st)
 {
     if constexpr (G <= 4) {
         if (light) {
-            DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, false>), grid, dim3(256), 0, st, a);
+            DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, false, PLAN>), grid, dim3(256), 0, st, a);
             return;
         }
     }
-    DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, true>), grid, dim3(256), 0, st, a);
+    DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, true, PLAN>), grid, dim3(256), 0, st, a);
 }
 
 // mfma: the matrix-core inner loop (batched path); otherwise the vector-ALU one
-template <int D>
+template <int D, bool PLAN>
 dk_status launch_attention_d(const dk::AttnArgs &a, int G, dim3 grid, bool mfma, bool light, hipStream_t st)
 {
 #define DK_ATTN_CASE(g)                                                                              \
     case g:                                                                                          \
-        if (mfma) launch_attention_mfma<D, g>(a, grid, light, st);                                     \
-        else DK_LAUNCH(DK_K_ATTENTION, (dk::attention_kernel<D, g>), grid, dim3(256), 0, st, a);     \
+        if (mfma) launch_attention_mfma<D, g, PLAN>(a, grid, light, st);                                     \
+        else DK_LAUNCH(DK_K_ATTENTION, (dk::attention_kernel<D, g, PLAN>), grid, dim3(256), 0, st, a);     \
         break;
     switch (G) {
         DK_ATTN_CASE(1)
@@ -1434,6 +1439,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
     dk_status s;
     auto u16 = [](const void *p) { return static_cast<const uint16_t *>(p); };
 
+    uint32_t *plan = w.attn_plan && !prefill ? reinterpret_cast<uint32_t *>(attn) : nullptr;
     {   // embedding rows, rotary angles, cleared tickets
         dk::EmbedArgs e{};
         e.embed = u16(model->embed);
@@ -1443,6 +1449,16 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
         e.cs = cs;
         e.tickets = tickets;
         e.n_tickets = w.n_tickets;
+        e.B = B;
+        if (plan) {
+            e.plan = plan;
+            e.plan_items = B * w.max_chunks;
+            e.plan_unit = w.attn_light ? 128 : 64;
+            e.static_chunk = w.chunk_tokens;
+            e.plan_units_max = (w.chunk_tokens + e.plan_unit - 1) / e.plan_unit;
+            e.block_tables = d_block_tables;
+            e.max_blocks = max_blocks;
+        }
         e.H = H;
         e.half = d / 2;
         e.V = c.vocab;
@@ -1454,7 +1470,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             e.ssq_out = ssq;
         }
         std::memcpy(e.inv_freq, model->inv_freq, sizeof e.inv_freq);
-        DK_LAUNCH(DK_K_EMBED, dk::embed_kernel, dim3(B), dim3(256), 0, st, e);
+        DK_LAUNCH(DK_K_EMBED, dk::embed_kernel, dim3(plan ? B + 1 : B), dim3(256), 0, st, e);
         DK_HIP(hipGetLastError());
     }
 
@@ -1550,10 +1566,16 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
                 s = (d == 128) ? launch_prefill_attention_d<128>(a, G, grid, st)
                                : launch_prefill_attention_d<64>(a, G, grid, st);
             } else {
-                const dim3 grid(w.max_chunks, nkv, B);
+                a.plan = plan;
+                const dim3 grid = plan ? dim3(nkv, B * w.max_chunks) : dim3(w.max_chunks, nkv, B);
                 const bool use_mfma = w.attn_mfma;
-                s = (d == 128) ? launch_attention_d<128>(a, nq / nkv, grid, use_mfma, w.attn_light, st)
-                               : launch_attention_d<64>(a, nq / nkv, grid, use_mfma, w.attn_light, st);
+                const int G = nq / nkv;
+                if (plan)
+                    s = (d == 128) ? launch_attention_d<128, true>(a, G, grid, use_mfma, w.attn_light, st)
+                                   : launch_attention_d<64, true>(a, G, grid, use_mfma, w.attn_light, st);
+                else
+                    s = (d == 128) ? launch_attention_d<128, false>(a, G, grid, use_mfma, w.attn_light, st)
+                                   : launch_attention_d<64, false>(a, G, grid, use_mfma, w.attn_light, st);
             }
             if (s != DK_OK) return s;
         }

@@ -16,7 +16,10 @@ struct EmbedArgs {
     float2 *cs;             // [B][d/2]
     int *tickets;           // [n_tickets]
     int n_tickets;
-    int H, half, V;
+    int B, H, half, V;
+    uint32_t *plan;         // the step's attention plan (make_attn_plan), or null
+    const int *block_tables;  // [B][max_blocks]
+    int plan_items, plan_unit, plan_units_max, max_blocks, static_chunk;
     // batched path (null otherwise): (x * gain) as bf16 hi/lo in act_offset() order and the
     // row's sum of x^2 in ssq_out[b], for the first matrix-core GEMM
     const uint16_t *gain;
@@ -25,9 +28,100 @@ struct EmbedArgs {
     double inv_freq[64];    // theta^(-2i/d), i < d/2
 };
 
+// The split of a step's contexts over the blocks of decode attention, made from the lengths on the device.
+// The host sizes the grid by the longest context the block table can hold; with one chunk length for that, ragged
+// rows leave short ones on a block each while the long ones' blocks are the last to finish, and table columns that
+// no row has reached yet are blocks without work.  The plan takes the shortest chunk - a multiple of plan_unit
+// tokens - with which all rows together make at most plan_items chunks, the number of blocks launched per kv head.
+// Whole chunks come first, then what is left of every row, the longest first: blocks go round the compute units in
+// that order, so all of them get about the same.  64 rows of 37 to 900 tokens (0.6B shape) 40.4 -> 32.2 us a launch, 2136 ->
+// 1910 a step; 16 of 128 to 2048 (3B, 4 bit) 1905 -> 1859 a step; 16 of 4096 (8B) 5588 -> 5569, the same split.
+// Record 0 of the plan: word 0, tokens of a chunk, or 0 where the host's split does as well (equal rows that fill their
+// tables: then blocks, which request their inputs by the host's split before they have read this word, save the round
+// trip).  Record 1 + i: row | chunk << 8, or kPlanNone; the row's length; the
+// partial slot of its chunk 0 (a row's slots lie side by side); the block table's entries of the chunk's first kPlanBlocks
+// blocks, so that a block of attention requests its K/V as soon as it has read the record.
+// Called by the 256 threads of a block; 64 rows at most.
+constexpr uint32_t kPlanNone = 0xffffffffu;
+constexpr int kPlanMaxItems = 65535, kPlanWords = 16, kPlanBlocks = 8;
+__device__ __forceinline__ void make_attn_plan(const EmbedArgs &a, int tid)
+{
+    __shared__ int sm_whole[64], sm_slot[64], sm_len[64], sm_left[64], sm_row[64], sm_units;
+    if (tid < 64) {
+        const int T = tid < a.B ? min(max(a.seq_lens[tid], 0), a.max_blocks * 16 - 1) : -1;
+        auto chunks = [&](int units) { return (T + units * a.plan_unit) / (units * a.plan_unit); };
+        auto total = [&](int units) {
+            int n = chunks(units);
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) n += __shfl_xor(n, off);
+            return n;
+        };
+        int lo = 1, hi = a.plan_units_max;   // plan_units_max fits: the host counted it for full tables
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (total(mid) <= a.plan_items) hi = mid;
+            else lo = mid + 1;
+        }
+        const int n = chunks(lo), left = T + 1 - (n - 1) * lo * a.plan_unit;
+        int end = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(end, off);
+            end += tid >= off ? o : 0;
+        }
+        sm_slot[tid] = end - n;
+        sm_whole[tid] = end - min(tid + 1, a.B);   // whole chunks of the rows up to this one
+        sm_len[tid] = T;
+        sm_left[tid] = tid < a.B ? left : -1;
+        if (tid == 0) {
+            sm_units = lo;
+            a.plan[0] = a.static_chunk * 8 <= lo * a.plan_unit * 9 ? 0u : (uint32_t)(lo * a.plan_unit);
+        }
+    }
+    __syncthreads();
+    if (tid < a.B) {
+        const int left = sm_left[tid];
+        int rank = 0;
+        for (int q = 0; q < a.B; q++) rank += sm_left[q] > left || (sm_left[q] == left && q < tid) ? 1 : 0;
+        sm_row[rank] = tid;
+    }
+    __syncthreads();
+    // eight threads to a record
+    const int blocks_per_chunk = sm_units * (a.plan_unit / 16), whole = sm_whole[a.B - 1], e = tid & 7;
+    for (int i = tid >> 3; i < a.plan_items; i += 32) {
+        int row, c;
+        if (i < whole) {
+            int lo = 0, hi = a.B - 1;            // the first row whose whole chunks end behind i
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (sm_whole[mid] > i) hi = mid;
+                else lo = mid + 1;
+            }
+            row = lo;
+            c = i - (lo ? sm_whole[lo - 1] : 0);
+        } else {
+            row = sm_row[min(i - whole, a.B - 1)];
+            c = sm_whole[row] - (row ? sm_whole[row - 1] : 0);
+        }
+        uint32_t *rec = a.plan + (int64_t)(1 + i) * kPlanWords;
+        const bool none = i >= whole + a.B;
+        if (e == 0) {
+            rec[0] = none ? kPlanNone : (uint32_t)row | (uint32_t)c << 8;
+            rec[1] = (uint32_t)sm_len[row];
+            rec[2] = (uint32_t)sm_slot[row];
+        }
+        if (!none)
+            rec[3 + e] = (uint32_t)a.block_tables[(int64_t)row * a.max_blocks + min(c * blocks_per_chunk + e, a.max_blocks - 1)];
+    }
+}
+
 __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a)
 {
     const int b = blockIdx.x, tid = threadIdx.x;
+    if (b == a.B) {   // (one block more where a plan is wanted)
+        make_attn_plan(a, tid);
+        return;
+    }
     // an out-of-range token id is clamped (reads a valid row) rather than faulting
     const int tok = min(max(a.tokens[b], 0), a.V - 1);
     const uint16_t *row = a.embed + (int64_t)tok * a.H;
@@ -155,6 +249,9 @@ struct AttnArgs {
     int max_blocks, num_blocks, layer, nq, nkv;
     int chunk_tokens;        // multiple of 64
     int max_chunks;
+    // decode kernels: which (row, chunk) a block takes (make_attn_plan; grid = (kv heads, items), partials
+    // [kv head][slot]), or null: grid = (chunks, kv heads, rows)
+    const uint32_t *plan;
     int defer_merge;         // 1: leave the chunk partials for the consumer to merge
     int table_stride;        // ints between the rows' block tables (0: all rows share one table)
     int no_append;           // 1: the new tokens' K/V are already in the pool (chunked prefill)
@@ -169,6 +266,33 @@ __device__ __forceinline__ void st_coherent(float *p, float v)
 __device__ __forceinline__ float ld_coherent(const float *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The part of decode attention that a block of the two decode kernels takes: row, chunk, kv head, tokens of a chunk,
+// partial record of the row's chunk 0.
+struct AttnItem { int b, c, j, chunk_tokens, part; };
+// ... by the host's split
+template <bool PLAN>
+__device__ __forceinline__ AttnItem attn_item(const AttnArgs &a)
+{
+    AttnItem it;
+    it.b = PLAN ? (int)blockIdx.y / a.max_chunks : (int)blockIdx.z;
+    it.c = PLAN ? (int)blockIdx.y % a.max_chunks : (int)blockIdx.x;
+    it.j = PLAN ? blockIdx.x : blockIdx.y;
+    it.chunk_tokens = a.chunk_tokens;
+    it.part = (it.b * a.nkv + it.j) * a.max_chunks;
+    return it;
+}
+// ... by the plan's record; false: no work
+__device__ __forceinline__ bool attn_planned_item(const AttnArgs &a, int chunk_tokens, const uint32_t *rec, AttnItem &it)
+{
+    const uint32_t e = rec[0];
+    it.b = e & 63;
+    it.c = (int)(e >> 8);
+    it.j = blockIdx.x;
+    it.chunk_tokens = chunk_tokens;
+    it.part = it.j * (int)gridDim.y + (int)rec[2];
+    return e != kPlanNone;
 }
 
 // Online merge, in chunk order, of the chunk partials of one (row, kv head): [chunk][G][d+2] with the
@@ -328,7 +452,7 @@ __global__ void iota_kernel(int *seq, int start, int n)
     if (i < n) seq[i] = start + i;
 }
 
-template <int D, int G>
+template <int D, int G, bool PLAN>
 __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
 {
     constexpr int BS = 16;            // tokens per block
@@ -340,37 +464,44 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
     __shared__ float sm_ml[NWV][G][2];
     __shared__ int sm_ticket;
 
-    const int c = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+    AttnItem item = attn_item<PLAN>(a);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int dl = (lane % TPR) * 8;   // this lane's 8 dims
     const int sub = lane / TPR;        // token within a wave load
     const int q_stride = (a.nq + 2 * a.nkv) * D;
-    const float *row = a.qkv + (int64_t)b * q_stride;
-    const float2 *cs_row = a.cs + (int64_t)b * (D / 2);
-    const int *table = a.block_tables + (int64_t)b * a.table_stride;
+    const bool upper = dl >= D / 2;
 
     // Everything that does not depend on the sequence length is requested
     // before the length is looked at, so the loads overlap: the raw q heads and
     // the first block-table entry this wave will need (always inside the table).
     float q[G][8];
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        const float *qp = row + (int64_t)(j * G + g) * D + dl;
-        const float4 lo = ldf4(qp), hi = ldf4(qp + 4);
-        q[g][0] = lo.x; q[g][1] = lo.y; q[g][2] = lo.z; q[g][3] = lo.w;
-        q[g][4] = hi.x; q[g][5] = hi.y; q[g][6] = hi.z; q[g][7] = hi.w;
-    }
-    const bool upper = dl >= D / 2;
     float2 cs[8];
-    {
-        const float4 *cp = reinterpret_cast<const float4 *>(cs_row + (upper ? dl - D / 2 : dl));
+    float kn[8], vn[8];   // raw k and v of the new token (only the block owning position T uses them)
+    auto request_row = [&](int b, int j) {
+        const float *row = a.qkv + (int64_t)b * q_stride;
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const float *qp = row + (int64_t)(j * G + g) * D + dl;
+            const float4 lo = ldf4(qp), hi = ldf4(qp + 4);
+            q[g][0] = lo.x; q[g][1] = lo.y; q[g][2] = lo.z; q[g][3] = lo.w;
+            q[g][4] = hi.x; q[g][5] = hi.y; q[g][6] = hi.z; q[g][7] = hi.w;
+        }
+        const float4 *cp = reinterpret_cast<const float4 *>(a.cs + (int64_t)b * (D / 2) + (upper ? dl - D / 2 : dl));
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             const float4 t = cp[e];
             cs[2 * e] = make_float2(t.x, t.y);
             cs[2 * e + 1] = make_float2(t.z, t.w);
         }
-    }
+        const float *kp = row + (int64_t)(a.nq + j) * D + dl;
+        const float *vp = row + (int64_t)(a.nq + a.nkv + j) * D + dl;
+        const float4 klo = ldf4(kp), khi = ldf4(kp + 4), vlo = ldf4(vp), vhi = ldf4(vp + 4);
+        kn[0] = klo.x; kn[1] = klo.y; kn[2] = klo.z; kn[3] = klo.w;
+        kn[4] = khi.x; kn[5] = khi.y; kn[6] = khi.z; kn[7] = khi.w;
+        vn[0] = vlo.x; vn[1] = vlo.y; vn[2] = vlo.z; vn[3] = vlo.w;
+        vn[4] = vhi.x; vn[5] = vhi.y; vn[6] = vhi.z; vn[7] = vhi.w;
+    };
+    request_row(item.b, item.j);
     const bool norm = a.g_q != nullptr;
     float gq[8], gk[8];
     if (norm) {
@@ -380,26 +511,30 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
 #pragma unroll
         for (int e = 0; e < 8; e++) gq[e] = gk[e] = 1.f;
     }
-    // raw k and v of the new token (only the block owning position T uses them)
-    float kn[8], vn[8];
-    {
-        const float *kp = row + (int64_t)(a.nq + j) * D + dl;
-        const float *vp = row + (int64_t)(a.nq + a.nkv + j) * D + dl;
-        const float4 klo = ldf4(kp), khi = ldf4(kp + 4), vlo = ldf4(vp), vhi = ldf4(vp + 4);
-        kn[0] = klo.x; kn[1] = klo.y; kn[2] = klo.z; kn[3] = klo.w;
-        kn[4] = khi.x; kn[5] = khi.y; kn[6] = khi.z; kn[7] = khi.w;
-        vn[0] = vlo.x; vn[1] = vlo.y; vn[2] = vlo.z; vn[3] = vlo.w;
-        vn[4] = vhi.x; vn[5] = vhi.y; vn[6] = vhi.z; vn[7] = vhi.w;
-    }
-    const int first_blk = c * (a.chunk_tokens / BS) + wv;
-    int phys_next = table[min(first_blk, a.max_blocks - 1)];
+    const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
+    int phys_next = table[min(item.c * (item.chunk_tokens / BS) + wv, a.max_blocks - 1)];
     // T = cached tokens = position of the new token (clamped to what the table can name)
-    const int T = min(max(a.seq_lens[b], 0), a.max_blocks * BS - 1);
+    int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
+    const uint32_t *rec = a.plan + (PLAN ? (int64_t)(1 + blockIdx.y) * kPlanWords : 0);
+    bool planned = false;
+    if constexpr (PLAN) {
+        const int planned_tokens = (int)a.plan[0];
+        planned = planned_tokens != 0;
+        if (planned) {
+            if (!attn_planned_item(a, planned_tokens, rec, item)) return;
+            request_row(item.b, item.j);
+            table = a.block_tables + (int64_t)item.b * a.table_stride;
+            phys_next = (int)rec[3 + wv];
+            T = (int)rec[1];
+        }
+    }
+    const int b = item.b, c = item.c, j = item.j, chunk_tokens = item.chunk_tokens;
+    const int first_blk = c * (chunk_tokens / BS) + wv;
     const int T1 = T + 1;
-    const int nact = (T1 + a.chunk_tokens - 1) / a.chunk_tokens;
+    const int nact = (T1 + chunk_tokens - 1) / chunk_tokens;
     if (c >= nact) return;
-    const int t0 = c * a.chunk_tokens;
-    const int t1 = min(T, t0 + a.chunk_tokens);   // cached positions [t0, t1) come from the pool
+    const int t0 = c * chunk_tokens;
+    const int t1 = min(T, t0 + chunk_tokens);   // cached positions [t0, t1) come from the pool
     const bool owns_new = (c == nact - 1);        // position T itself
 
     const int blk_end = (t1 + BS - 1) / BS;
@@ -414,7 +549,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
             kw_n[i] = ld16(kt + i * 512 + lane * 8);
             vw_n[i] = ld16(vt + i * 512 + lane * 8);
         }
-        phys_next = table[min(first_blk + NWV, a.max_blocks - 1)];
+        phys_next = planned ? (int)rec[3 + NWV + wv] : table[min(first_blk + NWV, a.max_blocks - 1)];
     }
 
 #pragma unroll
@@ -552,7 +687,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
     __syncthreads();
 
     // merge the waves; thread (g, dim) for g*D + dim = tid, tid + 256, ...
-    float *part = a.part + (((int64_t)b * a.nkv + j) * a.max_chunks) * (G * (D + 2));
+    float *part = a.part + (int64_t)item.part * (G * (D + 2));
     for (int idx = tid; idx < G * D; idx += 256) {
         const int g = idx / D, dim = idx % D;
         float mn = sm_ml[0][g][0];

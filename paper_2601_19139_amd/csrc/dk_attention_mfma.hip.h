@@ -173,7 +173,7 @@ __device__ __forceinline__ void mfma_attend_tile_pair(const uint4 (&kw)[2][D / 3
     }
 }
 
-template <int D, int G, bool PREFETCH>
+template <int D, int G, bool PREFETCH, bool PLAN>
 __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(AttnArgs a)
 {
     constexpr int BS = 16;            // tokens per block tile
@@ -192,16 +192,14 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     __shared__ float sm_ml[NWV + 1][G][2];
     __shared__ int sm_ticket;
 
-    const int c = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+    AttnItem item = attn_item<PLAN>(a);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int dl = (lane % TPR) * 8;   // row-major layout: this lane's 8 dims
     const int sub = lane / TPR;        // row-major layout: token within a wave load
     const int ln = lane & 15, lg = lane >> 4;   // MFMA layout
     const int q_stride = (a.nq + 2 * a.nkv) * D;
-    const float *row = a.qkv + (int64_t)b * q_stride;
-    const float2 *cs_row = a.cs + (int64_t)b * (D / 2);
-    const int *table = a.block_tables + (int64_t)b * a.table_stride;
+    const bool upper = dl >= D / 2;
 
     // ---- requests first, arithmetic later -------------------------------------
     // The q | k | v row, the rotation table and the gains do not depend on the
@@ -210,40 +208,53 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     // has been read) are still on their way.  Loads return in order, so the other
     // way round the prologue would wait for the K/V tiles.
     float4 q_raw[G][2], k_raw[2], v_raw[2], cs_raw[4];
+    auto request_row = [&](int b, int j) {
+        const float *row = a.qkv + (int64_t)b * q_stride;
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        const float *qp = row + (int64_t)(j * G + g) * D + dl;
-        q_raw[g][0] = ldf4(qp);
-        q_raw[g][1] = ldf4(qp + 4);
-    }
-    const bool upper = dl >= D / 2;
-    {
-        const float4 *cp = reinterpret_cast<const float4 *>(cs_row + (upper ? dl - D / 2 : dl));
+        for (int g = 0; g < G; g++) {
+            const float *qp = row + (int64_t)(j * G + g) * D + dl;
+            q_raw[g][0] = ldf4(qp);
+            q_raw[g][1] = ldf4(qp + 4);
+        }
+        const float4 *cp = reinterpret_cast<const float4 *>(a.cs + (int64_t)b * (D / 2) + (upper ? dl - D / 2 : dl));
 #pragma unroll
         for (int e = 0; e < 4; e++) cs_raw[e] = cp[e];
-    }
+        const float *kp = row + (int64_t)(a.nq + j) * D + dl;
+        const float *vp = row + (int64_t)(a.nq + a.nkv + j) * D + dl;
+        k_raw[0] = ldf4(kp); k_raw[1] = ldf4(kp + 4);
+        v_raw[0] = ldf4(vp); v_raw[1] = ldf4(vp + 4);
+    };
+    request_row(item.b, item.j);
     const bool norm = a.g_q != nullptr;
     uint4 gq_raw = make_uint4(0, 0, 0, 0), gk_raw = make_uint4(0, 0, 0, 0);
     if (norm) {
         gq_raw = ld16(a.g_q + dl);
         gk_raw = ld16(a.g_k + dl);
     }
-    {
-        const float *kp = row + (int64_t)(a.nq + j) * D + dl;
-        const float *vp = row + (int64_t)(a.nq + a.nkv + j) * D + dl;
-        k_raw[0] = ldf4(kp); k_raw[1] = ldf4(kp + 4);
-        v_raw[0] = ldf4(vp); v_raw[1] = ldf4(vp + 4);
-    }
     // block-table entries of the wave's first tile pair: they depend on the chunk
     // index only, so they are read together with the sequence length
-    const int blk_first = c * (a.chunk_tokens / BS) + 2 * wv;
-    const int phys_a = table[min(blk_first, a.max_blocks - 1)];
-    const int phys_b = table[min(blk_first + 1, a.max_blocks - 1)];
-    const int T = min(max(a.seq_lens[b], 0), a.max_blocks * BS - 1);
-    const int nact = (T + 1 + a.chunk_tokens - 1) / a.chunk_tokens;
+    const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
+    int blk_first = item.c * (item.chunk_tokens / BS) + 2 * wv;
+    int phys_a = table[min(blk_first, a.max_blocks - 1)], phys_b = table[min(blk_first + 1, a.max_blocks - 1)];
+    int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
+    if constexpr (PLAN) {
+        const int planned_tokens = (int)a.plan[0];
+        if (planned_tokens != 0) {
+            const uint32_t *rec = a.plan + (int64_t)(1 + blockIdx.y) * kPlanWords;
+            if (!attn_planned_item(a, planned_tokens, rec, item)) return;
+            request_row(item.b, item.j);
+            table = a.block_tables + (int64_t)item.b * a.table_stride;
+            blk_first = item.c * (item.chunk_tokens / BS) + 2 * wv;
+            phys_a = (int)rec[3 + 2 * wv];
+            phys_b = (int)rec[4 + 2 * wv];
+            T = (int)rec[1];
+        }
+    }
+    const int b = item.b, c = item.c, j = item.j, chunk_tokens = item.chunk_tokens;
+    const int nact = (T + 1 + chunk_tokens - 1) / chunk_tokens;
     if (c >= nact) return;
-    const int t0 = c * a.chunk_tokens;
-    const int t1 = min(T, t0 + a.chunk_tokens);   // cached positions [t0, t1) come from the pool
+    const int t0 = c * chunk_tokens;
+    const int t1 = min(T, t0 + chunk_tokens);   // cached positions [t0, t1) come from the pool
     const bool owns_new = (c == nact - 1);        // position T itself
     const int blk_end = (t1 + BS - 1) / BS;
     // The K and V tiles of the next iteration are requested before this one is
@@ -400,7 +411,7 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     __syncthreads();
 
     // ---- merge the waves and the new token; chunks as in attention_kernel ------
-    float *part = a.part + (((int64_t)b * a.nkv + j) * a.max_chunks) * (G * (D + 2));
+    float *part = a.part + (int64_t)item.part * (G * (D + 2));
     for (int idx = tid; idx < G * D; idx += 256) {
         const int g = idx / D, dim = idx % D;
         float mn = sm_ml[0][g][0];
