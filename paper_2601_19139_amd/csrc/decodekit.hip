@@ -1727,6 +1727,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.K = H;
             g.B = B;
             g.q4 = model->q4;
+            g.spread = !prefill;
             g.pack = w.pack_x;
             g.kpart = kpart;
             g.ktickets = ktickets;

@@ -49,6 +49,7 @@ struct GemmArgs {
     const uint16_t *W2;      // GEPI_SWIGLU: the "up" matrix, same format as W
     int N, K, B;             // B valid batch rows (<= 16*MT)
     int q4;                  // host side only: W / W2 are packed 4-bit matrices (selects the Q4 kernels)
+    int spread;              // shared_gemm_kernel, more than 16 rows: blocks may begin at columns of their own
     int pack;                // host side only: the terms of an activation share one operand (2 or 3, see kPackCols)
     const uint16_t *xhi;     // hi part of the input, bf16 in act_offset() order
     const uint16_t *xlo;     // lo part

@@ -93,7 +93,15 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
     struct Stage {
         uint4 wa[NA][Q4 ? 3 : 4], act[PPT];   // Q4: codes of the whole step, (scale, bias) of its two groups
     };
-    const int rot = MT == 1 && (!Q4 || K % 8192 == 0) ? (int)blockIdx.x % max(niter, 1) : 0;   // each block begins at another column (see skinny_gemm_kernel)
+    // Where a block begins in its slice.  Up to 16 rows every block at another column (see skinny_gemm_kernel).  Above, in
+    // the gate/up pair of a decode step (a.spread), the blocks of a compute die together, since they share the activation
+    // tiles of a step through its L2, and the dies an eighth of the slice apart: with all blocks at one column of rows
+    // 8 KB apart their weights come from a few memory channels (12288 x 4096: 64 rows 55.2 -> 51.7 us, 32 rows 50.3 ->
+    // 40.7; 8192 x 3072 30.9 -> 30.1; the other matrices and 4-bit rows the same as before).  Not for prompts: their K/V,
+    // rounded to bf16, feed all that follows, so there another order of sums shows as 1e-3 of the logits.
+    int rot = 0;
+    if (MT == 1) rot = !Q4 || K % 8192 == 0 ? (int)blockIdx.x % max(niter, 1) : 0;
+    else if (EPI == GEPI_SWIGLU && !Q4 && a.spread) rot = (int)((blockIdx.x + blockIdx.y * gridDim.x) & 7) * niter / 8;
     int it_i = 0;
     auto issue = [&](Stage &st) {
         // (a step past the slice, or an empty slice - more slices than steps: a valid step, unused)
@@ -261,6 +269,8 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
         // device-coherent loads of a slice - 16 bytes per lane and 16 x 16 tile, as the matrix cores
         // leave it - are independent and are all issued before the first is used; the next slice is
         // requested before this one is added, so a round trip is paid per slice, not per element.
+        // The block's own slice is still in its registers (with two slices half of the bytes that the last
+        // blocks, a part of the chip, read alone: gate/up of 12288 x 4096, 64 rows, begun at columns apart, 51.7 -> 47.9 us).
         const float *pbase[NA];
 #pragma unroll
         for (int m = 0; m < NA; m++) {
@@ -275,22 +285,32 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
                 for (int t = 0; t < MT; t++)
                     v[m][t] = ld_coherent16(pbase[m] + off, MT * 1024, (uint32_t)(t * 1024 + lane * 16));
         };
-        f32x4_t cur[NA][MT], nxt[NA][MT];
-        fetch(0, cur);
+        f32x4_t own[NA][MT], cur[NA][MT], nxt[NA][MT];
+        auto other = [&](int i) { return i + (i >= y ? 1 : 0); };   // the i-th of the other slices
+        fetch(other(0), cur);
 #pragma unroll
         for (int m = 0; m < NA; m++)
 #pragma unroll
-            for (int t = 0; t < MT; t++) acc[m][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        for (int q = 0; q < S; q++) {
-            fetch(q + 1, nxt);       // (past the last slice: the last one again, unused)
+            for (int t = 0; t < MT; t++) {
+                own[m][t] = acc[m][t];
+                acc[m][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            }
+        auto add = [&](const f32x4_t (&v)[NA][MT]) {
 #pragma unroll
             for (int m = 0; m < NA; m++)
 #pragma unroll
-                for (int t = 0; t < MT; t++) {
-                    acc[m][t] += cur[m][t];
-                    cur[m][t] = nxt[m][t];
-                }
+                for (int t = 0; t < MT; t++) acc[m][t] += v[m][t];
+        };
+        for (int i = 0; i < S - 1; i++) {
+            fetch(other(i + 1), nxt);       // (past the last slice: the last one again, unused)
+            if (i == y) add(own);
+            add(cur);
+#pragma unroll
+            for (int m = 0; m < NA; m++)
+#pragma unroll
+                for (int t = 0; t < MT; t++) cur[m][t] = nxt[m][t];
         }
+        if (y == S - 1) add(own);
     } else {
         __syncthreads();   // sm_ssq
     }
