@@ -1439,6 +1439,10 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
     dk_status s;
     auto u16 = [](const void *p) { return static_cast<const uint16_t *>(p); };
 
+    // The chunk's k and v reach the pool from the projection itself where its blocks hold a head each.
+    const bool grouped = prefill && batched && w.pack_x != 3;   // attention takes 16 / G rows of the sequence together
+    const bool qkv_appends = grouped && d == 128 && H % 128 == 0 &&
+                             gemm_plan(dk::GEPI_STORE, qkv_dim, H, w.Bp, model->q4, w.pack_x).w == 8;
     // A prefill chunk whose predictions nobody wants (all but the last of a prompt) leaves K/V and, in a model with
     // experts, the routing: it ends with the last layer's (501 tokens of the 8B shape: 7 of 8 chunks, 2 % of the call).
     const bool kv_only = prefill && d_next_tokens == nullptr && d_logits == nullptr;
@@ -1497,6 +1501,18 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             g.n_part = (l == 0) ? 1 : (c.n_experts > 0) ? (H + 1023) / 1024 : ssq_tiles;
             g.eps = eps;
             g.y = qkv;
+            if (qkv_appends) {
+                g.q_heads = nq;
+                g.kv_heads = nkv;
+                g.cs = cs;
+                g.g_k = c.qk_norm ? u16(L.g_k) : nullptr;
+                g.pool = pool->mem;
+                g.block_table = d_block_tables;
+                g.seq_lens = d_seq_lens;
+                g.max_blocks = max_blocks;
+                g.num_blocks = pool->num_blocks;
+                g.layer = l;
+            }
             if ((s = launch_gemm<dk::GEPI_STORE, true>(g, w.Bp, st)) != DK_OK) return s;
         } else {
             dk::GemvArgs g{};
@@ -1537,7 +1553,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             a.table_stride = prefill ? 0 : max_blocks;
             a.no_append = prefill ? 1 : 0;
             const bool append_only = l + 1 == c.n_layers && kv_only && c.n_experts == 0;
-            if (prefill) {
+            if (prefill && !qkv_appends) {
                 dk::PrefillAppendArgs pa{};
                 pa.qkv = qkv;
                 pa.cs = cs;
@@ -1562,8 +1578,7 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
             a.scale = (float)(1.0 / std::sqrt((double)d));
             a.eps = eps;
             a.n_rows = B;
-            if (prefill && batched && w.pack_x != 3) {
-                // rows of one sequence: 16 / G of them share every K/V tile
+            if (grouped) {
                 const int G = nq / nkv;
                 a.chunk_tokens = w.pf_chunk_tokens;
                 a.max_chunks = w.pf_max_chunks;

@@ -196,8 +196,8 @@ __global__ __launch_bounds__(128) void append_kv_kernel(AppendArgs a)
 // Chunked prefill: the rows of a step are consecutive positions of ONE sequence
 // (row b sits at position seq_lens[b]; one shared block table).  Row b's
 // attention reads the positions of rows < b from the pool, so every row's new k
-// (head norm, rotation) and v are stored by prefill_append_kernel before
-// attention starts, with exactly the arithmetic the attention kernel applies to
+// (head norm, rotation) and v are stored before attention starts - by the projection where its
+// blocks hold a head each (append_head, dk_gemm_shared.hip.h), else by prefill_append_kernel - with exactly the arithmetic the attention kernel applies to
 // its own new token.  grid = (rows), 256 threads: aligned groups of D/8 lanes
 // take the kv heads in turn.
 struct PrefillAppendArgs {

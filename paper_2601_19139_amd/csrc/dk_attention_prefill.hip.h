@@ -7,8 +7,8 @@
 // RPB = 16 / G consecutive rows: a K/V tile is read (and multiplied) once for
 // RPB rows instead of once per row.  Column col = (row in group) * G + head.
 //
-// Every row's own k and v are already in the pool (prefill_append_kernel runs
-// first), so there is no "new token" special case: column col attends to the
+// Every row's own k and v are already in the pool (stored by the projection, append_head in
+// dk_gemm_shared.hip.h, or by prefill_append_kernel in front), so there is no "new token" special case: column col attends to the
 // positions 0..T(col) of the pool, and the causal mask inside the group is the
 // per-column limit.  The inner loop is the decode kernel's (mfma_attend_tile_pair:
 // scores = K q with q as three bf16 terms, online softmax per column, output = P V

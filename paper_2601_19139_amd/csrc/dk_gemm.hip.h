@@ -74,6 +74,14 @@ struct GemmArgs {
     // (zero before the launch, zero after)
     float *kpart;
     int *ktickets;
+    // shared_gemm_kernel, q | k | v of a prompt chunk whose blocks hold a head each (heads of 128, eight waves): q_heads > 0,
+    // and the k and v heads go to the pool instead of y
+    int q_heads, kv_heads;
+    const float2 *cs;        // [B][64]
+    const uint16_t *g_k;     // [128] or null
+    uint16_t *pool;
+    const int *block_table, *seq_lens;
+    int max_blocks, num_blocks, layer;
 };
 
 __device__ __forceinline__ void split_bf16(float x, uint16_t &hi, uint16_t &lo)

@@ -22,6 +22,7 @@
 // arrives last adds the slices in slice order and runs the epilogue: the result does not
 // depend on arrival order.
 #pragma once
+#include "dk_attention.hip.h"
 #include "dk_gemm.hip.h"
 
 namespace dk {
@@ -50,6 +51,51 @@ __device__ __forceinline__ f32x4_t ld_coherent16(const float *base, int bytes, u
 
 // Dynamic LDS bytes of a shared_gemm_kernel instance.
 constexpr size_t shared_gemm_lds_bytes(int MT) { return (size_t)2 * 512 * MT * 16; }
+
+// A block's 128 output rows are one head of k or v of a prompt chunk: head norm and rotation (k), rounding, and into the
+// pool, as prefill_append_kernel does it (same arithmetic).  That kernel is a launch of its own, 4.9 us per layer, for
+// values that this block has in its registers; here the head takes one trip through the LDS of the activation tiles and
+// the projection 0.3 us more (8B shape, 64 rows, 23.9 -> 24.2; 3B with 4-bit weights 19.4 -> 20.3).  buf: [rows][132] floats.  Called by all threads, which have left the activation tiles.
+template <int MT, int W>
+__device__ __forceinline__ void append_head(const GemmArgs &a, int head, const float (&v)[MT][4], float *buf)
+{
+    constexpr int D = 128, BS = 16, LD = D + 4;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, ln = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < MT; t++)
+        *reinterpret_cast<float4 *>(buf + (t * 16 + ln) * LD + wv * 16 + 4 * lg) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
+    __syncthreads();
+    const bool is_v = head >= a.kv_heads;
+    const int j = is_v ? head - a.kv_heads : head, dl = (tid & 15) * 8;
+    const bool upper = dl >= D / 2, norm = a.g_k != nullptr;
+    float gk[8];
+    if (norm) {
+        unpack8(ld16(a.g_k + dl), gk);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; e++) gk[e] = 1.f;
+    }
+    for (int n = tid >> 4; n < a.B; n += W * 4) {   // sixteen lanes to a row
+        const int T = min(max(a.seq_lens[n], 0), a.max_blocks * BS - 1);
+        const int phys = min(max(a.block_table[T / BS], 0), a.num_blocks - 1);
+        const float4 lo = ldf4(buf + n * LD + dl), hi = ldf4(buf + n * LD + dl + 4);
+        float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        if (!is_v) {
+            float2 cs[8];
+            const float4 *cp = reinterpret_cast<const float4 *>(a.cs + (int64_t)n * (D / 2) + (upper ? dl - D / 2 : dl));
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const float4 t = cp[e];
+                cs[2 * e] = make_float2(t.x, t.y);
+                cs[2 * e + 1] = make_float2(t.z, t.w);
+            }
+            head_norm_rope<D>(x, norm, gk, a.eps, cs, upper);
+        }
+        uint16_t *dst = a.pool + kv_tile_offset(a.layer, a.num_blocks, phys, is_v ? 1 : 0, a.kv_heads, j, BS, D) + (T % BS) * D + dl;
+        *reinterpret_cast<uint4 *>(dst) = make_uint4(f32x2_to_bf16x2_rne(x[0], x[1]), f32x2_to_bf16x2_rne(x[2], x[3]),
+                                                     f32x2_to_bf16x2_rne(x[4], x[5]), f32x2_to_bf16x2_rne(x[6], x[7]));
+    }
+}
 
 // W waves per block, RT row tiles per wave (GEPI_SWIGLU: of each of the two matrices), PD K-steps
 // in flight per wave.  K must be a multiple of 128.  grid = (ceil(tiles / (W*RT)), slices).
@@ -324,6 +370,17 @@ __global__ __launch_bounds__(W * 64) void shared_gemm_kernel(GemmArgs a)
 #pragma unroll
             for (int w = 0; w < NC; w++) s += sm_ssq[w][t * 16 + ln];
             inv[t] = rsqrtf(s / (float)K + a.eps);
+        }
+    }
+    if constexpr (EPI == GEPI_STORE && W == 8 && RT == 1) {
+        if (a.q_heads > 0 && (int)blockIdx.x >= a.q_heads) {
+            float v[MT][4];
+#pragma unroll
+            for (int t = 0; t < MT; t++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) v[t][i] = pack_sum<PACK>(acc[0][t][i], lane) * inv[t];
+            append_head<MT, W>(a, (int)blockIdx.x - a.q_heads, v, reinterpret_cast<float *>(sm_act_dyn));
+            return;
         }
     }
 #pragma unroll

@@ -150,6 +150,22 @@ def test_prefill_matches_token_by_token_oracle(dk, orc, name, shape, plen, chunk
     dm.close()
 
 
+# the chunk's k and v leave the projection's blocks, a head each: (q heads, kv heads, hidden, chunk, slices of K, head norm)
+HEAD_BLOCKS = [
+    (24, 8, 512, 23, 1, True),       # two row tiles, one slice
+    (32, 8, 1024, 41, 2, False),     # three; no head norm
+    (24, 8, 1024, 64, 2, True),      # four, all rows in use; the second chunk is short and takes the kernel of its own
+    (8, 8, 2048, 60, 4, True),
+]
+
+
+@pytest.mark.parametrize("nq,nkv,hidden,chunk,slices,norm", HEAD_BLOCKS)
+def test_heads_stored_by_the_projection(dk, orc, nq, nkv, hidden, chunk, slices, norm):
+    assert dk.gemm_plan_query(0, (nq + 2 * nkv) * 128, hidden, chunk, False)[:2] == (8, slices)
+    shape = variant("tiny", n_layers=2, hidden=hidden, ffn=512, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, qk_norm=norm)
+    test_prefill_matches_token_by_token_oracle(dk, orc, "heads", shape, chunk + 9, chunk, 1)
+
+
 def test_prefill_behind_a_shared_prefix(dk, orc):
     """Prefix reuse: the shared prefix is fed once; two sequences whose tables start with the
     same blocks feed only their own suffixes from the start position the prefix ends at.  Each

@@ -201,11 +201,16 @@ def test_q4_distinct_scales_and_biases_per_group(dk, orc):
     assert worst < TIGHT and agree == 1.0, (worst, agree)
 
 
-def test_q4_prefill_chunk_matches_token_by_token(dk, orc):
+@pytest.mark.parametrize("chunk,kw", [
+    (16, {}),
+    (32, dict(hidden=2048, n_q_heads=16, n_kv_heads=8, head_dim=128)),   # k and v stored by the projection, a head a block
+], ids=["", "heads_stored_by_the_projection"])
+def test_q4_prefill_chunk_matches_token_by_token(dk, orc, chunk, kw):
     """A prompt written by chunked prefill with 4-bit weights gives the logits of the oracle's
     token-by-token run."""
     import torch
-    shape = W.CONFIGS["tiny_q4"]
+    shape = variant("tiny_q4", **kw)
+    assert dk.gemm_plan_query(0, (shape.n_q_heads + 2 * shape.n_kv_heads) * shape.head_dim, shape.hidden, chunk, True)[0] == (8 if kw else 0)
     weights = quantize_weights(W.make_weights(shape, 9))
     P = 45
     lay = build_block_tables([0], 16, P + 1, seed=5)
@@ -218,7 +223,7 @@ def test_q4_prefill_chunk_matches_token_by_token(dk, orc):
     dm = dk.DeviceModel(shape, weights)
     dkv = dk.DeviceKV(dm, lay, pool)
     pf = dk.Prefiller(dm, dkv)
-    nxt, logits = pf.prefill(0, 0, prompt, chunk=16)
+    nxt, logits = pf.prefill(0, 0, prompt, chunk=chunk)
     torch.cuda.synchronize()
     got = logits[-1].astype(np.float64)
     rel = np.linalg.norm(got - ref["logits"][0]) / np.linalg.norm(ref["logits"][0])
