@@ -1229,7 +1229,7 @@ dk_status dk_prefill_chunk(dk_model *model, dk_kv_pool *pool, const int32_t *d_b
 }
 
 namespace {
-struct SampleScratch { size_t p, pmax, part, tickets, hist, st_a, st_b, item_val, item_cnt, total; };
+struct SampleScratch { size_t p, pmax, part, hist, st_a, st_b, item_val, item_cnt, total; };
 SampleScratch sample_scratch(int B, int V)
 {
     SampleScratch L{};
@@ -1237,8 +1237,8 @@ SampleScratch sample_scratch(int B, int V)
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
     L.p = take((size_t)B * V * 4);
     L.pmax = take((size_t)B * dk::kSampleBlocks * 4);
-    L.part = take((size_t)B * dk::kSampleBlocks * 16 * 4);   // (the searches use 64 floats a row of these two)
-    L.tickets = take((size_t)B * dk::kSampleBlocks * 16 * 4);
+    L.part = take((size_t)B * dk::kSampleBlocks * 16 * 4);   // (64 floats a row in use; callers keep scratch of this size)
+    take((size_t)B * dk::kSampleBlocks * 16 * 4);
     L.st_a = take((size_t)B * sizeof(dk::SampleState));
     L.st_b = take((size_t)B * sizeof(dk::SampleState));
     L.item_val = take((size_t)B * dk::kSampleItems * 4);
@@ -1287,7 +1287,6 @@ dk_status dk_sample_tokens(const float *d_logits, int32_t B, int32_t V, const dk
     a.step_lo = (uint32_t)step;
     a.step_hi = (uint32_t)(step >> 32);
     a.part = reinterpret_cast<float *>(base + L.part);
-    a.tickets = reinterpret_cast<int *>(base + L.tickets);
     // totals of V weights of at most 1 are at most 2^63
     a.mass_bits = 63;
     for (int n = V; n > 1; n = (n + 1) / 2) a.mass_bits--;
@@ -1361,6 +1360,7 @@ dk_status dk_sample_tokens(const float *d_logits, int32_t B, int32_t V, const dk
     }
     if (use_p) later_digits(false);
     launch(dk::sample_kernel<dk::SAMPLE_KEEP>, dk::kSampleBlocks);
+    launch(dk::sample_kernel<dk::SAMPLE_DRAW>, 1);
     DK_HIP(hipGetLastError());
     return DK_OK;
 }

@@ -22,9 +22,10 @@
 // total of at least 1, 2^-27 for 2^18 of them.  So the blocks add to a histogram in any order and
 // the totals are still the same bits.  What bounds the chain is the number of
 // dependent launches, 5 to 7 us each: digits of four bits with the candidates' float totals
-// took 12 launches for top-p alone and 21 with both thresholds, now 5 and 8.
-// us a call, then and now: 16 rows of 151936, top-p 0.9 79.5 -> 43.9 (flat rows 79.8 -> 48.3), top-k 100 82.0 -> 46.1,
-// both 141.1 -> 63.5; one row 60.4 -> 25.8; 64 rows 200.6 -> 107.4; 1 x 1000 41.3 -> 19.9, 64 x 32000 112.5 -> 72.1.
+// took 12 launches for top-p alone and 21 with both thresholds, now 6 and 9.  (The draw by the
+// row's last block of the kept-mass launch, a ticket each, saves a launch and cost more: that launch took 19.3 us.)
+// us a call, then and now: 16 rows of 151936, top-p 0.9 79.5 -> 30.6 (flat rows 79.8 -> 35.0), top-k 100 82.0 -> 32.8,
+// both 141.1 -> 47.0; one row 60.4 -> 23.4; 64 rows 200.6 -> 61.7; 1 x 1000 41.3 -> 20.0, 64 x 32000 112.5 -> 41.1.
 // With a small top_k (the usual serving setting) the candidates are selected slice by slice
 // instead and a call is three launches (below).
 // Other float sums have a fixed order and counts are integers: a call is repeatable
@@ -67,8 +68,8 @@ enum {
     SAMPLE_EXP = 0,       // no search follows: weights p, per-block total
     SAMPLE_EXP_DIGIT,     // weights p, the first digit's histogram
     SAMPLE_PASS,          // settle the previous digit, histogram of the next one (of this search or of the second)
-    SAMPLE_KEEP,          // settle the last digit; per-block kept mass; the row's last block draws
-    SAMPLE_DRAW           // no thresholds: one block per row draws
+    SAMPLE_KEEP,          // settle the last digit; per-block kept mass
+    SAMPLE_DRAW           // one block per row: the draw
 };
 
 struct SampleArgs {
@@ -79,10 +80,9 @@ struct SampleArgs {
     SampleState *st_in, *st_out;    // [B] (ping-pong)
     // [B][kSampleBins] each: settled, added to (zero before the launch), cleared for the next launch
     unsigned long long *hist_in, *hist_out, *hist_clear;
-    int *tickets;          // [B]: blocks of a row that have left their kept mass
     int *out;              // [B]
     int V;
-    int search;            // a search follows: sample_max_kernel clears what it starts from
+    int search;            // there are thresholds: sample_max_kernel clears what the search starts from
     int shift;             // SAMPLE_PASS: bit position of the digit whose histogram is made
     int first;             // SAMPLE_PASS, SAMPLE_KEEP: hist_in is a search's first digit
     int count_in, count;   // hist_in / hist_out hold counts (top-k) instead of masses (top-p)
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_merge_draw_kernel(Sampl
                     sm_i);
 }
 
-// grid (kSampleBlocks, B): the slices' maxima of logit / T.  A search's first histogram and its ticket are cleared here.
+// grid (kSampleBlocks, B): the slices' maxima of logit / T.  A search's first histogram is cleared here.
 __global__ __launch_bounds__(kSampleThreads) void sample_max_kernel(SampleArgs a)
 {
     __shared__ float sm[4];
@@ -613,11 +613,41 @@ __global__ __launch_bounds__(kSampleThreads) void sample_max_kernel(SampleArgs a
     __syncthreads();
     if (tid == 0) a.pmax[b * kSampleBlocks + g] = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
     constexpr int CLEAR = kSampleBins / kSampleBlocks;
-    if (a.search) {
-        if (tid < CLEAR) a.hist_clear[(int64_t)b * kSampleBins + g * CLEAR + tid] = 0ull;
-        if (g == 0 && tid == 0) a.tickets[b] = 0;
-    }
+    if (a.search && tid < CLEAR) a.hist_clear[(int64_t)b * kSampleBins + g * CLEAR + tid] = 0ull;
 }
+
+// What a thread sees of its block's slice p[i0..i1): elements i0 + tid, i0 + tid + kSampleThreads, ... in that order, four
+// or eight loads in flight.  The first eight - all of a slice of 2048 - are requested by begin(), which does not wait, so
+// that they come in while a digit is settled.
+struct SampleSlice {
+    static constexpr int PRE = 8;
+    const float *p;
+    int i0, i1;
+    float pre[PRE];
+    __device__ __forceinline__ void begin(const float *row, int first, int end)
+    {
+        p = row;
+        i0 = first + (int)threadIdx.x;
+        i1 = end;
+#pragma unroll
+        for (int j = 0; j < PRE; j++) pre[j] = p[max(min(i0 + j * kSampleThreads, i1 - 1), 0)];
+    }
+    template <class F>
+    __device__ __forceinline__ void each(F &&f) const
+    {
+#pragma unroll
+        for (int j = 0; j < PRE; j++)
+            if (i0 + j * kSampleThreads < i1) f(pre[j]);
+        for (int i = i0 + PRE * kSampleThreads; i < i1; i += 4 * kSampleThreads) {
+            float x[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) x[j] = p[min(i + j * kSampleThreads, i1 - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (i + j * kSampleThreads < i1) f(x[j]);
+        }
+    }
+};
 
 // A kernel per stage: with all of them in one the shorter ones carry the searches' LDS and registers (16 rows of 151936
 // without thresholds 14.0 -> 14.5 us).
@@ -627,7 +657,6 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     __shared__ unsigned long long hist[kSampleBins];
     __shared__ unsigned long long sm_w[4], sm_r[2];
     __shared__ float sm[8];
-    __shared__ float mass[kSampleBlocks];
     __shared__ int sm_i[12];
     const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
     const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
@@ -691,49 +720,46 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
         return;
     }
     if constexpr (STAGE == SAMPLE_DRAW) {
-        // g == 0 only (grid.x = 1): without thresholds every weight is kept, the slices' totals are already there
-        sample_draw_row(p, a.part + b * kSampleBlocks, 1, 0.f, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
+        // g == 0 only (grid.x = 1); without thresholds every weight is kept, the slices' totals are already there
+        const float tau = a.search ? __uint_as_float(a.st_in[b].prefix) : 0.f;
+        sample_draw_row(p, a.part + b * kSampleBlocks, 1, tau, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
         return;
     }
 
     // ---- the threshold searches ------------------------------------------------------------
     if constexpr (STAGE == SAMPLE_PASS) {
         SampleState st = a.st_in[b];
+        SampleSlice slice_p;
+        slice_p.begin(p, i0, i1);
 #pragma unroll
         for (int k = tid; k < kSampleBins; k += kSampleThreads) hist[k] = 0ull;
         st = sample_settle(a, st, b, a.second ? 0 : a.shift + kSampleDigitBits, sm_w, sm_r);   // (its barriers also order the clearing)
         if (a.second) st = SampleState{0ull, 0u, st.prefix};   // the top-k threshold: the floor of the second search
         const float floor_t = __uint_as_float(st.floor_bits);
         const int above = a.shift + kSampleDigitBits;          // the bits of the prefix: 30 - none - for a search's first digit
-        for (int i = i0 + tid; i < i1; i += kSampleThreads) {
-            const float v = p[i];
+        slice_p.each([&](float v) {
             const uint32_t bits = __float_as_uint(v);
             if (v >= floor_t && bits >> above == st.prefix >> above)
                 atomicAdd(&hist[(bits >> a.shift) & (kSampleBins - 1)], a.count ? 1ull : sample_fixed(bits, a.mass_bits));
-        }
+        });
         add_hist();
         if (g == 0 && tid == 0) a.st_out[b] = st;
         return;
     }
     if constexpr (STAGE == SAMPLE_KEEP) {
         // SAMPLE_KEEP: the final threshold is the larger of the two searches'; kept mass of the slice, in a fixed order
+        SampleSlice slice_p;
+        slice_p.begin(p, i0, i1);
         const SampleState st = sample_settle(a, a.st_in[b], b, 0, sm_w, sm_r);
         const uint32_t tau_bits = max(st.prefix, st.floor_bits);
         const float tau = __uint_as_float(tau_bits);
         float kept = 0.f;
-        for (int i = i0 + tid; i < i1; i += kSampleThreads) kept += (p[i] >= tau) ? p[i] : 0.f;
+        slice_p.each([&](float v) { kept += v >= tau ? v : 0.f; });
         kept = sample_block_sum(kept, sm);
         if (tid == 0) {
-            // device-coherent: the row's last block may run on another die
-            __hip_atomic_store(&a.part[b * kSampleBlocks + g], kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            drain_stores();
-            sm_i[0] = __hip_atomic_fetch_add(&a.tickets[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            a.part[b * kSampleBlocks + g] = kept;
+            if (g == 0) a.st_out[b] = SampleState{0ull, tau_bits, 0u};
         }
-        __syncthreads();
-        if (sm_i[0] != kSampleBlocks - 1) return;
-        if (tid < kSampleBlocks)
-            mass[tid] = __hip_atomic_load(&a.part[b * kSampleBlocks + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sample_draw_row(p, mass, 1, tau, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
     }
 }
 
