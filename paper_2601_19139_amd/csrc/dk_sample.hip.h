@@ -56,6 +56,9 @@ constexpr int kSampleThreads = 256;
 constexpr int kSampleDigitBits = 10;
 constexpr int kSampleBins = 1 << kSampleDigitBits;
 constexpr int kSampleTopShift = 20;  // of the first of three digits: weights are at most 1, 30 bits
+// The first digit of 1 is 1016, so the topmost one has no weights and counts the row's NaNs.  A NaN makes the total that
+// top-p takes its share of a NaN, which no candidate reaches: everything but the NaNs stays, as the definition has it.
+constexpr int kSampleNanBin = kSampleBins - 1;
 
 // per-row search state handed from one launch to the next
 struct SampleState {
@@ -105,7 +108,7 @@ __device__ __forceinline__ unsigned long long sample_fixed(uint32_t bits, int ma
 // Settles a digit from the row's histogram: the largest one whose total together with those above it
 // reaches `need` (first: need is made of the histogram's own total).  Called by every thread of the block.
 __device__ __forceinline__ SampleState sample_settle(const SampleArgs &a, SampleState st, int b, int digit_shift,
-                                                     unsigned long long *sm_w /*[4]*/, unsigned long long *sm_r /*[2]*/)
+                                                     unsigned long long *sm_w /*[5]*/, unsigned long long *sm_r /*[2]*/)
 {
     constexpr int PER = kSampleBins / kSampleThreads;
     static_assert(PER == 4, "two 16-byte loads a thread");
@@ -123,7 +126,10 @@ __device__ __forceinline__ SampleState sample_settle(const SampleArgs &a, Sample
     }
     __syncthreads();
     if (lane == 63) sm_w[wave] = inc;
-    if (tid == 0) sm_r[0] = sm_r[1] = 0ull;   // nothing reaches it: digit 0
+    if (tid == 0) {
+        sm_r[0] = sm_r[1] = 0ull;   // nothing reaches it: digit 0
+        sm_w[4] = h[0];             // kSampleNanBin
+    }
     __syncthreads();
     unsigned long long total = 0ull, over = inc - own;
 #pragma unroll
@@ -131,7 +137,10 @@ __device__ __forceinline__ SampleState sample_settle(const SampleArgs &a, Sample
         over += w < wave ? sm_w[w] : 0ull;
         total += sm_w[w];
     }
-    if (a.first) st.need = a.count_in ? (unsigned long long)a.top_k : (unsigned long long)ceil((double)a.top_p * (double)total);
+    if (a.first) {
+        st.need = a.count_in ? (unsigned long long)a.top_k : (unsigned long long)ceil((double)a.top_p * (double)total);
+        if (!a.count_in && sm_w[4] != 0ull) st.need = ~0ull;   // a total that is not a number: nothing reaches a share of it
+    }
     // at most one thread's four digits hold it (the topmost digit where nothing is needed: a row without a mass)
     if (over + own >= st.need && (over < st.need || (tid == 0 && st.need == 0ull))) {
         unsigned long long run = over;
@@ -655,7 +664,7 @@ template <int STAGE>
 __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
 {
     __shared__ unsigned long long hist[kSampleBins];
-    __shared__ unsigned long long sm_w[4], sm_r[2];
+    __shared__ unsigned long long sm_w[5], sm_r[2];
     __shared__ float sm[8];
     __shared__ int sm_i[12];
     const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V;
@@ -700,10 +709,12 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
                     p[i + j * kSampleThreads] = v;
                     z += v;
                     const uint32_t bits = __float_as_uint(v);
-                    if (DIGIT && v >= 0.f) {   // (not a NaN: a row whose maximum is infinite)
+                    if (DIGIT && v >= 0.f) {
                         const unsigned long long w = a.count ? 1ull : sample_fixed(bits, a.mass_bits);
                         if (v < a.negligible) rest += w;
-                        else atomicAdd(&hist[min(bits >> kSampleTopShift, (uint32_t)kSampleBins - 1)], w);
+                        else atomicAdd(&hist[min(bits >> kSampleTopShift, (uint32_t)kSampleNanBin - 1)], w);
+                    } else if (DIGIT && !a.count) {   // a NaN among the logits, or a row whose maximum is infinite
+                        atomicAdd(&hist[kSampleNanBin], 1ull);
                     }
                 }
         }

@@ -162,6 +162,29 @@ def test_threshold_searches(dk, orc, row, V, top_k, top_p):
     assert exact >= 4 * B
 
 
+def test_nan_among_the_logits(dk, orc):
+    """A NaN makes the total that the nucleus is a share of a NaN: no threshold reaches it, and every other token stays
+    a candidate (the oracle's sums come to the same)."""
+    import torch
+    V, B, top_p = 5000, 16, 0.3
+    l = (np.random.default_rng(8).normal(size=V) * 2.0).astype(np.float32)
+    l[[17, 1234, V - 1]] = np.nan
+    d_logits = torch.from_numpy(np.tile(l, (B, 1))).cuda()
+    scratch = torch.empty(dk.sample_scratch_bytes(B, V), dtype=torch.uint8, device="cuda")
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    cum = np.cumsum(np.where(np.isnan(l), 0.0, np.exp(l.astype(np.float64) - np.nanmax(l))))
+    exact = 0
+    for step in range(6):
+        dk.sample_tokens(d_logits, 1.0, 0, top_p, 9, step, scratch, out)
+        got = out.cpu().numpy()
+        for b in range(B):
+            u = orc.sample_uniform(9, step, b)
+            if np.min(np.abs(cum - u * cum[-1])) > 1e-5 * cum[-1]:
+                assert got[b] == orc.sample(l, 1.0, 0, top_p, u), (step, b, got[b])
+                exact += 1
+    assert exact >= 4 * B
+
+
 def test_sampled_distribution_on_device(dk):
     """Many independent draws (one per row and step) follow the softmax probabilities."""
     import torch
