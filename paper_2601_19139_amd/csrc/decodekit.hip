@@ -181,7 +181,7 @@ struct Workspace {
     bool defer_merge;   // small problems: the output projection merges the attention chunks
     bool attn_mfma;     // the matrix-core attention kernel (otherwise the vector-ALU one)
     bool attn_light;    // ... without the register double buffer (short chunks)
-    bool attn_plan;     // contexts split on the device, from the rows' lengths (make_attn_plan)
+    bool attn_plan;     // chunks ordered on the device, from the rows' lengths (make_attn_plan)
 };
 
 constexpr int kMaxGemvBatch = 4;  // the most rows the vector-ALU GEMV takes (fewer where pack_terms, 4-bit weights or experts ask for the matrix cores)
@@ -412,8 +412,8 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
         w.fused_sets = take((size_t)2 * w.fused_set_floats * 4);
         w.fused_status = take(64);
     }
-    // The plan is worth its look-up where a chunk can get shorter than the tables' width gives it, and lies in the
-    // float32 attention output, which the batched path does not write.
+    // The plan is worth its look-up where a block's chunk takes long, and lies in the float32 attention output, which the
+    // batched path does not write.
     w.attn_plan = w.batched && !w.defer_merge && w.chunk_tokens >= 256 && B * w.max_chunks <= dk::kPlanMaxItems &&
                   (B * w.max_chunks + 1) * dk::kPlanWords <= B * c.n_q_heads * d;
     w.total = off;
@@ -1460,9 +1460,8 @@ static dk_status decode_step_impl(dk_model *model, dk_kv_pool *pool, const int32
         if (plan) {
             e.plan = plan;
             e.plan_items = B * w.max_chunks;
-            e.plan_unit = w.attn_light ? 128 : 64;
-            e.static_chunk = w.chunk_tokens;
-            e.plan_units_max = (w.chunk_tokens + e.plan_unit - 1) / e.plan_unit;
+            e.plan_chunk = w.chunk_tokens;
+            e.plan_chunks = w.max_chunks;
             e.block_tables = d_block_tables;
             e.max_blocks = max_blocks;
         }

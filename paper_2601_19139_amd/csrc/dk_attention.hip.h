@@ -19,7 +19,7 @@ struct EmbedArgs {
     int B, H, half, V;
     uint32_t *plan;         // the step's attention plan (make_attn_plan), or null
     const int *block_tables;  // [B][max_blocks]
-    int plan_items, plan_unit, plan_units_max, max_blocks, static_chunk;
+    int plan_items, plan_chunk, plan_chunks, max_blocks;
     // batched path (null otherwise): (x * gain) as bf16 hi/lo in act_offset() order and the
     // row's sum of x^2 in ssq_out[b], for the first matrix-core GEMM
     const uint16_t *gain;
@@ -28,57 +28,58 @@ struct EmbedArgs {
     double inv_freq[64];    // theta^(-2i/d), i < d/2
 };
 
-// The split of a step's contexts over the blocks of decode attention, made from the lengths on the device.
-// The host sizes the grid by the longest context the block table can hold; with one chunk length for that, ragged
-// rows leave short ones on a block each while the long ones' blocks are the last to finish, and table columns that
-// no row has reached yet are blocks without work.  The plan takes the shortest chunk - a multiple of plan_unit
-// tokens - with which all rows together make at most plan_items chunks, the number of blocks launched per kv head.
-// Whole chunks come first, then what is left of every row, the longest first: blocks go round the compute units in
-// that order, so all of them get about the same.  64 rows of 37 to 900 tokens (0.6B shape) 40.4 -> 32.2 us a launch, 2136 ->
-// 1910 a step; 16 of 128 to 2048 (3B, 4 bit) 1905 -> 1859 a step; 16 of 4096 (8B) 5588 -> 5569, the same split.
-// Record 0 of the plan: word 0, tokens of a chunk, or 0 where the host's split does as well (equal rows that fill their
-// tables: then blocks, which request their inputs by the host's split before they have read this word, save the round
-// trip).  Record 1 + i: row | chunk << 8, or kPlanNone; the row's length; the
-// partial slot of its chunk 0 (a row's slots lie side by side); the block table's entries of the chunk's first kPlanBlocks
-// blocks, so that a block of attention requests its K/V as soon as it has read the record.
+// The order in which the blocks of decode attention take a step's chunks, made from the lengths on the device.
+// The host sizes the grid by the longest context the block table can hold and cuts every context into chunks of one
+// length, so where a row's chunks begin and end - and the order of its sums - follows from its own length: rows do not
+// interact, bit for bit.  (Chunks made shorter where the lengths of all rows together allow it tie a row's rounding to its
+// neighbours; they take 0 to 2 % off 64 ragged rows and add 1.5 % to 16 ragged rows of the 3B shape, 4 bit.)  In the order
+// of the grid, ragged rows leave short ones on a block each while the long ones' blocks are the last to finish, and table
+// columns that no row has reached yet are blocks without work between the others.  The plan puts whole chunks first, then
+// what is left of every row, the longest first: blocks go round the compute units in that order, so all of them get
+// about the same.  Whole step, us, grid's order -> plan: 64 rows of 37 to 900 tokens (0.6B shape) 2160 -> 1974, 16 of 500
+// to 4000 2115 -> 1898, 16 of 128 to 2048 (3B, 4 bit) 1961 -> 1922, 16 of 500 to 4000 (8B) 5395 -> 5255.
+// Word 0 of the plan: 1, or 0 where the grid's order is as good (then no records are written): rows of equally many
+// chunks and nearly equal remainders that leave few blocks of the grid without work.  Blocks request their inputs by the
+// grid's order before they have read this word, which saves such steps a round trip.  Plan / grid's order, equal rows:
+//   * chunks that do not fill the table keep the plan (0.6B shape, 64 rows of 300 in a table of 1000 1645 / 1744, 16 of
+//     1000 in 4000 1351 / 1849, of 3000 - six chunks of eight - 2018 / 2005; 8B shape, 16 of 2000 in 4000 4956 / 5336);
+//   * four chunks and more do not (0.6B, 16 of 4000 2300 / 2205, of 3500 2140 / 2096; 8B, 16 of 4096 5600 / 5568; 3B, 16
+//     of 2000 2789 / 2752, 4 bit 2200 / 2160; but 0.6B, 32 of 3000 2994 / 3018);
+//   * three and two do (48 of 3000 4119 / 4197, of 2000 3098 / 3170; 64 of 900 2407 / 2516, of 2000 3680 / 3745).
+// Record 1 + i: row | chunk << 8, or kPlanNone; the row's length; the block table's entries of the chunk's first
+// kPlanBlocks blocks, so that a block of attention requests its K/V as soon as it has read the record.
 // Called by the 256 threads of a block; 64 rows at most.
 constexpr uint32_t kPlanNone = 0xffffffffu;
 constexpr int kPlanMaxItems = 65535, kPlanWords = 16, kPlanBlocks = 8;
 __device__ __forceinline__ void make_attn_plan(const EmbedArgs &a, int tid)
 {
-    __shared__ int sm_whole[64], sm_slot[64], sm_len[64], sm_left[64], sm_row[64], sm_units;
+    __shared__ int sm_whole[64], sm_len[64], sm_left[64], sm_row[64], sm_on;
+    const int chunk = a.plan_chunk;
     if (tid < 64) {
-        const int T = tid < a.B ? min(max(a.seq_lens[tid], 0), a.max_blocks * 16 - 1) : -1;
-        auto chunks = [&](int units) { return (T + units * a.plan_unit) / (units * a.plan_unit); };
-        auto total = [&](int units) {
-            int n = chunks(units);
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) n += __shfl_xor(n, off);
-            return n;
-        };
-        int lo = 1, hi = a.plan_units_max;   // plan_units_max fits: the host counted it for full tables
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (total(mid) <= a.plan_items) hi = mid;
-            else lo = mid + 1;
-        }
-        const int n = chunks(lo), left = T + 1 - (n - 1) * lo * a.plan_unit;
-        int end = n;
+        const bool row = tid < a.B;
+        const int T = row ? min(max(a.seq_lens[tid], 0), a.max_blocks * 16 - 1) : -1;
+        const int n = (T + chunk) / chunk, left = T + 1 - (n - 1) * chunk;   // chunks, tokens of the last one
+        int end = n, n_min = row ? n : kPlanMaxItems, n_max = n, left_min = row ? left : chunk, left_max = row ? left : 0;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int o = __shfl_up(end, off);
             end += tid >= off ? o : 0;
+            n_min = min(n_min, __shfl_xor(n_min, off));
+            n_max = max(n_max, __shfl_xor(n_max, off));
+            left_min = min(left_min, __shfl_xor(left_min, off));
+            left_max = max(left_max, __shfl_xor(left_max, off));
         }
-        sm_slot[tid] = end - n;
         sm_whole[tid] = end - min(tid + 1, a.B);   // whole chunks of the rows up to this one
         sm_len[tid] = T;
-        sm_left[tid] = tid < a.B ? left : -1;
+        sm_left[tid] = row ? left : -1;
         if (tid == 0) {
-            sm_units = lo;
-            a.plan[0] = a.static_chunk * 8 <= lo * a.plan_unit * 9 ? 0u : (uint32_t)(lo * a.plan_unit);
+            const bool equal = n_min == n_max && (left_max - left_min) * 4 <= chunk, fill = n_max * 8 >= a.plan_chunks * 7;
+            sm_on = equal && fill && (n_max == 1 || n_max >= 4) ? 0 : 1;
+            a.plan[0] = (uint32_t)sm_on;
         }
     }
     __syncthreads();
+    if (sm_on == 0) return;
     if (tid < a.B) {
         const int left = sm_left[tid];
         int rank = 0;
@@ -87,7 +88,7 @@ __device__ __forceinline__ void make_attn_plan(const EmbedArgs &a, int tid)
     }
     __syncthreads();
     // eight threads to a record
-    const int blocks_per_chunk = sm_units * (a.plan_unit / 16), whole = sm_whole[a.B - 1], e = tid & 7;
+    const int blocks_per_chunk = chunk / 16, whole = sm_whole[a.B - 1], e = tid & 7;
     for (int i = tid >> 3; i < a.plan_items; i += 32) {
         int row, c;
         if (i < whole) {
@@ -108,10 +109,9 @@ __device__ __forceinline__ void make_attn_plan(const EmbedArgs &a, int tid)
         if (e == 0) {
             rec[0] = none ? kPlanNone : (uint32_t)row | (uint32_t)c << 8;
             rec[1] = (uint32_t)sm_len[row];
-            rec[2] = (uint32_t)sm_slot[row];
         }
         if (!none)
-            rec[3 + e] = (uint32_t)a.block_tables[(int64_t)row * a.max_blocks + min(c * blocks_per_chunk + e, a.max_blocks - 1)];
+            rec[2 + e] = (uint32_t)a.block_tables[(int64_t)row * a.max_blocks + min(c * blocks_per_chunk + e, a.max_blocks - 1)];
     }
 }
 
@@ -249,8 +249,8 @@ struct AttnArgs {
     int max_blocks, num_blocks, layer, nq, nkv;
     int chunk_tokens;        // multiple of 64
     int max_chunks;
-    // decode kernels: which (row, chunk) a block takes (make_attn_plan; grid = (kv heads, items), partials
-    // [kv head][slot]), or null: grid = (chunks, kv heads, rows)
+    // decode kernels: which (row, chunk) a block takes (make_attn_plan; grid = (kv heads, items)), or null: grid =
+    // (chunks, kv heads, rows)
     const uint32_t *plan;
     int defer_merge;         // 1: leave the chunk partials for the consumer to merge
     int table_stride;        // ints between the rows' block tables (0: all rows share one table)
@@ -268,30 +268,20 @@ __device__ __forceinline__ float ld_coherent(const float *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The part of decode attention that a block of the two decode kernels takes: row, chunk, kv head, tokens of a chunk,
-// partial record of the row's chunk 0.
-struct AttnItem { int b, c, j, chunk_tokens, part; };
-// ... by the host's split
+// The part of decode attention that a block of the two decode kernels takes: row, chunk, kv head.
+struct AttnItem { int b, c, j; };
+// ... in the order of the grid
 template <bool PLAN>
 __device__ __forceinline__ AttnItem attn_item(const AttnArgs &a)
 {
-    AttnItem it;
-    it.b = PLAN ? (int)blockIdx.y / a.max_chunks : (int)blockIdx.z;
-    it.c = PLAN ? (int)blockIdx.y % a.max_chunks : (int)blockIdx.x;
-    it.j = PLAN ? blockIdx.x : blockIdx.y;
-    it.chunk_tokens = a.chunk_tokens;
-    it.part = (it.b * a.nkv + it.j) * a.max_chunks;
-    return it;
+    if (!PLAN) return {(int)blockIdx.z, (int)blockIdx.x, (int)blockIdx.y};
+    return {(int)blockIdx.y / a.max_chunks, (int)blockIdx.y % a.max_chunks, (int)blockIdx.x};
 }
 // ... by the plan's record; false: no work
-__device__ __forceinline__ bool attn_planned_item(const AttnArgs &a, int chunk_tokens, const uint32_t *rec, AttnItem &it)
+__device__ __forceinline__ bool attn_planned_item(const uint32_t *rec, AttnItem &it)
 {
     const uint32_t e = rec[0];
-    it.b = e & 63;
-    it.c = (int)(e >> 8);
-    it.j = blockIdx.x;
-    it.chunk_tokens = chunk_tokens;
-    it.part = it.j * (int)gridDim.y + (int)rec[2];
+    it = {(int)(e & 63), (int)(e >> 8), (int)blockIdx.x};
     return e != kPlanNone;
 }
 
@@ -512,29 +502,28 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
         for (int e = 0; e < 8; e++) gq[e] = gk[e] = 1.f;
     }
     const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
-    int phys_next = table[min(item.c * (item.chunk_tokens / BS) + wv, a.max_blocks - 1)];
+    int phys_next = table[min(item.c * (a.chunk_tokens / BS) + wv, a.max_blocks - 1)];
     // T = cached tokens = position of the new token (clamped to what the table can name)
     int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
     const uint32_t *rec = a.plan + (PLAN ? (int64_t)(1 + blockIdx.y) * kPlanWords : 0);
     bool planned = false;
     if constexpr (PLAN) {
-        const int planned_tokens = (int)a.plan[0];
-        planned = planned_tokens != 0;
+        planned = a.plan[0] != 0;
         if (planned) {
-            if (!attn_planned_item(a, planned_tokens, rec, item)) return;
+            if (!attn_planned_item(rec, item)) return;
             request_row(item.b, item.j);
             table = a.block_tables + (int64_t)item.b * a.table_stride;
-            phys_next = (int)rec[3 + wv];
+            phys_next = (int)rec[2 + wv];
             T = (int)rec[1];
         }
     }
-    const int b = item.b, c = item.c, j = item.j, chunk_tokens = item.chunk_tokens;
-    const int first_blk = c * (chunk_tokens / BS) + wv;
+    const int b = item.b, c = item.c, j = item.j;
+    const int first_blk = c * (a.chunk_tokens / BS) + wv;
     const int T1 = T + 1;
-    const int nact = (T1 + chunk_tokens - 1) / chunk_tokens;
+    const int nact = (T1 + a.chunk_tokens - 1) / a.chunk_tokens;
     if (c >= nact) return;
-    const int t0 = c * chunk_tokens;
-    const int t1 = min(T, t0 + chunk_tokens);   // cached positions [t0, t1) come from the pool
+    const int t0 = c * a.chunk_tokens;
+    const int t1 = min(T, t0 + a.chunk_tokens);   // cached positions [t0, t1) come from the pool
     const bool owns_new = (c == nact - 1);        // position T itself
 
     const int blk_end = (t1 + BS - 1) / BS;
@@ -549,7 +538,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
             kw_n[i] = ld16(kt + i * 512 + lane * 8);
             vw_n[i] = ld16(vt + i * 512 + lane * 8);
         }
-        phys_next = planned ? (int)rec[3 + NWV + wv] : table[min(first_blk + NWV, a.max_blocks - 1)];
+        phys_next = planned ? (int)rec[2 + NWV + wv] : table[min(first_blk + NWV, a.max_blocks - 1)];
     }
 
 #pragma unroll
@@ -687,7 +676,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
     __syncthreads();
 
     // merge the waves; thread (g, dim) for g*D + dim = tid, tid + 256, ...
-    float *part = a.part + (int64_t)item.part * (G * (D + 2));
+    float *part = a.part + (((int64_t)b * a.nkv + j) * a.max_chunks) * (G * (D + 2));
     for (int idx = tid; idx < G * D; idx += 256) {
         const int g = idx / D, dim = idx % D;
         float mn = sm_ml[0][g][0];

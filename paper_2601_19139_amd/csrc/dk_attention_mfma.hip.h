@@ -234,27 +234,26 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     // block-table entries of the wave's first tile pair: they depend on the chunk
     // index only, so they are read together with the sequence length
     const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
-    int blk_first = item.c * (item.chunk_tokens / BS) + 2 * wv;
+    int blk_first = item.c * (a.chunk_tokens / BS) + 2 * wv;
     int phys_a = table[min(blk_first, a.max_blocks - 1)], phys_b = table[min(blk_first + 1, a.max_blocks - 1)];
     int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
     if constexpr (PLAN) {
-        const int planned_tokens = (int)a.plan[0];
-        if (planned_tokens != 0) {
+        if (a.plan[0] != 0) {
             const uint32_t *rec = a.plan + (int64_t)(1 + blockIdx.y) * kPlanWords;
-            if (!attn_planned_item(a, planned_tokens, rec, item)) return;
+            if (!attn_planned_item(rec, item)) return;
             request_row(item.b, item.j);
             table = a.block_tables + (int64_t)item.b * a.table_stride;
-            blk_first = item.c * (item.chunk_tokens / BS) + 2 * wv;
-            phys_a = (int)rec[3 + 2 * wv];
-            phys_b = (int)rec[4 + 2 * wv];
+            blk_first = item.c * (a.chunk_tokens / BS) + 2 * wv;
+            phys_a = (int)rec[2 + 2 * wv];
+            phys_b = (int)rec[3 + 2 * wv];
             T = (int)rec[1];
         }
     }
-    const int b = item.b, c = item.c, j = item.j, chunk_tokens = item.chunk_tokens;
-    const int nact = (T + 1 + chunk_tokens - 1) / chunk_tokens;
+    const int b = item.b, c = item.c, j = item.j;
+    const int nact = (T + 1 + a.chunk_tokens - 1) / a.chunk_tokens;
     if (c >= nact) return;
-    const int t0 = c * chunk_tokens;
-    const int t1 = min(T, t0 + chunk_tokens);   // cached positions [t0, t1) come from the pool
+    const int t0 = c * a.chunk_tokens;
+    const int t1 = min(T, t0 + a.chunk_tokens);   // cached positions [t0, t1) come from the pool
     const bool owns_new = (c == nact - 1);        // position T itself
     const int blk_end = (t1 + BS - 1) / BS;
     // The K and V tiles of the next iteration are requested before this one is
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     __syncthreads();
 
     // ---- merge the waves and the new token; chunks as in attention_kernel ------
-    float *part = a.part + (int64_t)item.part * (G * (D + 2));
+    float *part = a.part + (((int64_t)b * a.nkv + j) * a.max_chunks) * (G * (D + 2));
     for (int idx = tid; idx < G * D; idx += 256) {
         const int g = idx / D, dim = idx % D;
         float mn = sm_ml[0][g][0];
