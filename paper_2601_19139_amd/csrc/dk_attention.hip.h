@@ -45,7 +45,8 @@ struct EmbedArgs {
 //     1000 in 4000 1351 / 1849, of 3000 - six chunks of eight - 2018 / 2005; 8B shape, 16 of 2000 in 4000 4956 / 5336);
 //   * four chunks and more do not (0.6B, 16 of 4000 2300 / 2205, of 3500 2140 / 2096; 8B, 16 of 4096 5600 / 5568; 3B, 16
 //     of 2000 2789 / 2752, 4 bit 2200 / 2160; but 0.6B, 32 of 3000 2994 / 3018);
-//   * three and two do (48 of 3000 4119 / 4197, of 2000 3098 / 3170; 64 of 900 2407 / 2516, of 2000 3680 / 3745).
+//   * two do where the second is short (0.6B, 64 of 1200 2788 / 2807, of 900 2407 / 2468, of 1600, four fifths, 3268 / 3247,
+//     of 2000 3680 / 3593, of 1000 2514 / 2498), three do (48 of 3000 4119 / 4167, of 2000 3098 / 3170).
 // Record 1 + i: row | chunk << 8, or kPlanNone; the row's length; the block table's entries of the chunk's first
 // kPlanBlocks blocks, so that a block of attention requests its K/V as soon as it has read the record.
 // Called by the 256 threads of a block; 64 rows at most.
@@ -74,7 +75,7 @@ __device__ __forceinline__ void make_attn_plan(const EmbedArgs &a, int tid)
         sm_left[tid] = row ? left : -1;
         if (tid == 0) {
             const bool equal = n_min == n_max && (left_max - left_min) * 4 <= chunk, fill = n_max * 8 >= a.plan_chunks * 7;
-            sm_on = equal && fill && (n_max == 1 || n_max >= 4) ? 0 : 1;
+            sm_on = equal && fill && (n_max == 1 || n_max >= 4 || (n_max == 2 && left_min * 5 >= chunk * 4)) ? 0 : 1;
             a.plan[0] = (uint32_t)sm_on;
         }
     }
@@ -270,11 +271,17 @@ __device__ __forceinline__ float ld_coherent(const float *p)
 
 // The part of decode attention that a block of the two decode kernels takes: row, chunk, kv head.
 struct AttnItem { int b, c, j; };
-// ... in the order of the grid
+// ... in the order of the grid.  Where there can be a plan, kv heads next to each other, then chunks (0.6B shape, 16 rows of
+// 4000 2296 -> 2216 a step, 32 of 2000 2376 -> 2350) - but the two chunks of a row and head next to each other where a row has
+// two (64 rows of 1000 2563 -> 2510, of 2000 3782 -> 3634).
 template <bool PLAN>
 __device__ __forceinline__ AttnItem attn_item(const AttnArgs &a)
 {
     if (!PLAN) return {(int)blockIdx.z, (int)blockIdx.x, (int)blockIdx.y};
+    if (a.max_chunks == 2) {
+        const int pair = (int)(blockIdx.x + blockIdx.y * gridDim.x), row_head = pair >> 1;
+        return {row_head / a.nkv, pair & 1, row_head % a.nkv};
+    }
     return {(int)blockIdx.y / a.max_chunks, (int)blockIdx.y % a.max_chunks, (int)blockIdx.x};
 }
 // ... by the plan's record; false: no work

@@ -27,6 +27,7 @@ EDGES = [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300]
 @pytest.mark.parametrize("lengths", ["ragged", "equal", "one_long"])
 @pytest.mark.parametrize("heads,d,longest", [
     ((4, 4), 64, 1100),      # vector-ALU kernel, a head of its own per kv head
+    ((8, 8), 64, 1100),      # ... two chunks a row, next to each other in the grid's order
     ((8, 4), 64, 1700),      # ... groups of two, chunks too long for the lighter matrix-core variant
     ((8, 4), 128, 1100),     # the lighter variant
     ((12, 4), 128, 1700),    # the matrix-core kernel that requests ahead
@@ -123,17 +124,19 @@ def test_rows_do_not_interact(base, batch, sizes, longest):
             assert np.array_equal(l0, l1) and np.array_equal(kv0, kv1)
 
 
-@pytest.mark.parametrize("length,width,word", [
-    (1100, 1104, 0),     # four chunks of 320, the last one short: the grid's order
-    (500, 1104, 1),      # two of four
-    (1100, 4400, 1),     # one chunk of 1152 in a table of four
+@pytest.mark.parametrize("heads,length,width,word", [
+    (4, 1100, 1104, 0),     # four chunks of 320, the last one short: the grid's order
+    (4, 500, 1104, 1),      # two of four
+    (4, 1100, 4400, 1),     # one chunk of 1152 in a table of four
+    (8, 1100, 1104, 0),     # two chunks of 576, the second nearly whole
+    (8, 900, 1104, 1),      # ... and not
 ])
-def test_equal_rows_take_a_plan_only_where_it_orders_something(length, width, word):
+def test_equal_rows_take_a_plan_only_where_it_orders_something(heads, length, width, word):
     """A plan that is not wanted is not written either: behind its word the workspace is left as it was."""
     import torch
     import paper_2601_19139_amd as dk
     batch = 64
-    shape = variant("tiny", n_layers=1, qk_norm=True, n_q_heads=4, n_kv_heads=4, head_dim=64)
+    shape = variant("tiny", n_layers=1, qk_norm=True, n_q_heads=heads, n_kv_heads=heads, head_dim=64)
     lay = build_block_tables([length] * batch, 16, 1, seed=81)
     wide = np.full((batch, width // 16), -1, dtype=np.int32)
     wide[:, :lay.tables.shape[1]] = lay.tables
