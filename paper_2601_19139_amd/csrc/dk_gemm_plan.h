@@ -49,8 +49,11 @@ struct SkinnyVariant { int mt, ks, rt, groups; };
 //     one block per compute unit (less to add up: K = 2048 6.4 -> 6.3, 4096 11.0 -> 10.8).
 // Above 16 rows: a small matrix whose row tiles x groups of 16 rows still make at most two blocks per compute unit runs
 // the 16-row kernel over all groups at once, residual projections with two-wave blocks; with 4-bit weights
-// and more than 32 rows, residual projections of up to three blocks as well, of four waves (64 rows, 192 row tiles of K =
-// 3072 14.8 -> 12.6 us; a wave's steps and the order of their sums are those of the 64-row block).
+// and more than 48 rows, residual projections of up to three blocks as well, of four waves (a wave's steps and the order of
+// their sums are those of the 64-row block; 64 rows, 192 row tiles of K = 3072 14.8 -> 12.6 us; whole steps of 12 layers
+// with 136, 144, 160, 192 tiles 846 -> 803, 1249 -> 1170, 1449 -> 1409, 1036 -> 978).  Not up to 48 rows, whose own block
+// leaves less to gain (whole steps: 192 tiles, 48 rows 894 / 908 and 2434 / 2437, 40 rows 1201 / 1195; 224 tiles 1730 /
+// 1743; 256 tiles, 48 rows 1140 / 1169, 8B shape 4238 / 4265, 33 rows 1115 / 1141).
 inline SkinnyVariant skinny_variant(int epi, int N, int K, int Bp, bool q4, bool pack, int cus)
 {
     const int tiles = (N + 15) / 16, mt = Bp / 16;
@@ -61,7 +64,7 @@ inline SkinnyVariant skinny_variant(int epi, int N, int K, int Bp, bool q4, bool
         return {1, !pack && (K <= 1024 || K % 2048 == 0) ? 8 : 4, two ? 2 : 1, 1};
     }
     if (tiles * mt <= 2 * cus) return {1, epi == EPI_RESID && !q4 ? 2 : 8, 1, mt};
-    if (mt > 2 && q4 && epi == EPI_RESID && tiles * mt <= 3 * cus) return {1, 4, 1, mt};
+    if (mt == 4 && q4 && epi == EPI_RESID && tiles * mt <= 3 * cus) return {1, 4, 1, mt};
     switch (mt) {
         case 2:
             if (one_matrix && tiles >= 4 * cus) return {2, 8, 2, 1};

@@ -360,3 +360,27 @@ def test_gemm_plan_query_says_what_runs():
         busiest = {v: -(--(-tiles // v) * s // 256) * v for v in (6, 8)}
         assert (w == 6) == (busiest[6] < busiest[8])
     assert dk.gemm_plan_query(SWIGLU, 10368, 4096, 64, True, 256)[0] == 6
+
+
+def test_residual_projections_of_4_bit_weights_in_groups_of_16_rows(tmp_path):
+    """Both ends of the rule, which the query does not show (256 compute units): more than 48 rows, two to three blocks per
+    compute unit; up to 48 rows, above three blocks and with bf16 weights the rows stay together."""
+    import subprocess
+    src, lib = tmp_path / "variant.cpp", tmp_path / "libvariant.so"
+    src.write_text('#include "dk_gemm_plan.h"\n'
+                   'extern "C" int variant(int epi, int N, int K, int Bp, int q4, int cus)\n'
+                   '{ const auto v = dkplan::skinny_variant(epi, N, K, Bp, q4, false, cus);\n'
+                   '  return ((v.mt * 16 + v.ks) * 16 + v.rt) * 16 + v.groups; }\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2601_19139_amd", "csrc"),
+                    str(src), "-o", str(lib)], check=True)
+    f = C.CDLL(str(lib)).variant
+
+    def variant(epi, tiles, rows, q4=1):
+        v = f(epi, tiles * 16, 3072, (rows + 15) // 16 * 16, q4, 256)
+        return v >> 12, v >> 8 & 15, v >> 4 & 15, v & 15
+    STORE, RESID = 0, 1
+    assert variant(RESID, 128, 64) == (1, 8, 1, 4)         # two blocks per compute unit: as with bf16
+    assert variant(RESID, 129, 64) == variant(RESID, 192, 49) == (1, 4, 1, 4)
+    assert variant(RESID, 193, 64) == variant(RESID, 192, 64, q4=0) == variant(STORE, 192, 64) == (4, 4, 1, 1)
+    assert variant(RESID, 170, 48) == (1, 8, 1, 3)
+    assert variant(RESID, 171, 48) == variant(RESID, 192, 40) == variant(RESID, 256, 33) == (3, 4, 1, 1)

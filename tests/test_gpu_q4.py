@@ -233,6 +233,37 @@ def test_q4_prefill_chunk_matches_token_by_token(dk, orc, chunk, kw):
     dm.close()
 
 
+@pytest.mark.parametrize("rows", [40, 50, 64])
+def test_q4_residual_projections_of_many_rows(dk, orc, rows):
+    """192 row tiles: above 48 rows groups of 16 rows, the last one partly filled, or all rows in a block; as a decode step
+    and as a prompt chunk of as many tokens."""
+    import torch
+    shape = variant("tiny_q4", n_layers=1, hidden=3072, n_q_heads=24, n_kv_heads=8, head_dim=128)
+    weights = quantize_weights(W.make_weights(shape, 19))
+    lay = build_block_tables([3 + 2 * i for i in range(rows)], 16, 1, seed=6)
+    pool = W.fill_kv_pool(shape, lay, 5)
+    some = [0, 15, 16, 33, rows - 1]
+    out = run_sampled(orc, shape, weights, lay, pool, W.initial_tokens(shape, rows, 7), 1, some)
+    worst, agree = check_parity(out)
+    # (rows of few tokens, heads of 128: a new v on a rounding boundary moves such a row by up to 2^-8 / sqrt(128))
+    assert worst < 4e-4 and agree == 1.0, worst
+    check_pool_sampled(out, pool, shape, lay, 1, some)
+    lay = build_block_tables([0], 16, rows, seed=8)
+    pool = W.fill_kv_pool(shape, lay, 9)
+    prompt = np.random.default_rng(10).integers(0, shape.vocab, size=rows).astype(np.int32)
+    opool = pool.copy()
+    for t in range(rows):
+        ref = orc.decode_step_q4(shape, weights, opool, 16, lay.tables, np.array([t], np.int32), prompt[t:t + 1])
+    dm = dk.DeviceModel(shape, weights)
+    dkv = dk.DeviceKV(dm, lay, pool)
+    nxt, logits = dk.Prefiller(dm, dkv).prefill(0, 0, prompt, chunk=rows)
+    torch.cuda.synchronize()
+    rel = np.linalg.norm(logits[-1] - ref["logits"][0]) / np.linalg.norm(ref["logits"][0])
+    assert rel < 2e-3 and int(nxt[-1]) == int(ref["next"][0]), rel      # the bound of the prefill path
+    dkv.close()
+    dm.close()
+
+
 def test_cfg1_shape_q4_full_size(dk, orc):
     """The benchmark model shape (28 layers, hidden 1024, vocabulary 151936, context 512) with
     4-bit weights, every logit of the first steps."""
