@@ -673,17 +673,18 @@ dk_status launch_gemm(const dk::GemmArgs &a, int Bp, hipStream_t st)
     return fail(DK_E_INVALID_ARG, "no GEMM kernel for %d rows (at most %d)", Bp, DK_MAX_BATCH);
 }
 
-// light: without the register double buffer (short chunks, query groups of up to 4: the host's choice)
+// light: without the register double buffer (short chunks).  carve() takes the matrix cores for query groups of 2 to 4
+// where the chunks are that short and for groups of 3 and more otherwise.
 template <int D, int G, bool PLAN>
 void launch_attention_mfma(const dk::AttnArgs &a, dim3 grid, bool light, hipStream_t st)
 {
-    if constexpr (G <= 4) {
+    if constexpr (G >= 2 && G <= 4) {
         if (light) {
             DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, false, PLAN>), grid, dim3(256), 0, st, a);
             return;
         }
     }
-    DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, true, PLAN>), grid, dim3(256), 0, st, a);
+    if constexpr (G >= 3) DK_LAUNCH(DK_K_ATTENTION, (dk::attention_mfma_kernel<D, G, true, PLAN>), grid, dim3(256), 0, st, a);
 }
 
 // mfma: the matrix-core inner loop (batched path); otherwise the vector-ALU one
@@ -692,8 +693,8 @@ dk_status launch_attention_d(const dk::AttnArgs &a, int G, dim3 grid, bool mfma,
 {
 #define DK_ATTN_CASE(g)                                                                              \
     case g:                                                                                          \
-        if (mfma) launch_attention_mfma<D, g, PLAN>(a, grid, light, st);                                     \
-        else DK_LAUNCH(DK_K_ATTENTION, (dk::attention_kernel<D, g, PLAN>), grid, dim3(256), 0, st, a);     \
+        if (mfma) launch_attention_mfma<D, g, PLAN>(a, grid, light, st);                             \
+        else DK_LAUNCH(DK_K_ATTENTION, (dk::attention_kernel<D, g, PLAN>), grid, dim3(256), 0, st, a); \
         break;
     switch (G) {
         DK_ATTN_CASE(1)
@@ -1237,8 +1238,7 @@ SampleScratch sample_scratch(int B, int V)
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
     L.p = take((size_t)B * V * 4);
     L.pmax = take((size_t)B * dk::kSampleBlocks * 4);
-    L.part = take((size_t)B * dk::kSampleBlocks * 16 * 4);   // (64 floats a row in use; callers keep scratch of this size)
-    take((size_t)B * dk::kSampleBlocks * 16 * 4);
+    L.part = take((size_t)B * dk::kSampleBlocks * 4);
     L.st_a = take((size_t)B * sizeof(dk::SampleState));
     L.st_b = take((size_t)B * sizeof(dk::SampleState));
     L.item_val = take((size_t)B * dk::kSampleItems * 4);

@@ -169,14 +169,14 @@ __device__ __forceinline__ float sample_block_sum(float v, float *sm /*[4]*/)
 
 // ---- small top_k: candidates by selection instead of a search over the whole row -------------
 // With 0 < top_k <= kSampleFastK a call is three launches (maximum; weights and the slices' top k;
-// thresholds and draw) instead of up to 21.  The block that computes a slice's weights also selects
+// thresholds and draw) instead of 6 or 9.  The block that computes a slice's weights also selects
 // the k-th largest of them (tau_g) and hands on the weights above it (fewer than k values, in index
 // order) plus (tau_g, how many equal it): an element of the row's top k is in its slice's top k, so
 // the row's k-th largest weight - and every weight at or above it - is among those items, ties
 // counted.  One block per row then selects the k-th largest of that multiset (tau_k), gathers the
 // candidates (items >= tau_k; a few dozen unless many weights are equal), finds the nucleus
 // threshold among them (a candidate per thread adds up the mass at or above its own value; beyond a
-// block's worth of candidates, the four-bit search of the general path), adds up each slice's kept
+// block's worth of candidates, a search of four bits per pass), adds up each slice's kept
 // mass from its items and draws: the slice that holds r by those masses, then the index inside it
 // from the weights themselves.  Selections are radix selections on the bit pattern (weights are
 // non-negative floats), eight bits per pass through an integer LDS histogram, on items held in
@@ -282,14 +282,14 @@ __device__ __forceinline__ float sample_wave_scan(float v)
     return v;
 }
 
-// The draw for row b: r = u * (sum of mass[k * stride], k in slice order); the slice that holds r, then
+// The draw for row b: r = u * (sum of mass[k], k in slice order); the slice that holds r, then
 // the index inside it by a running sum of the kept weights (p >= tau) in index order.  Two levels of
 // prefix sums (the slices' masses across a wave; inside the slice a contiguous piece per thread, the
 // pieces' sums across the block) name the thread whose piece holds r; that thread walks its piece.  Where
 // rounding leaves r beyond the last prefix, the last kept weight is taken.  Called by all threads of a
 // block; sm: LDS [8], sm_i: LDS [12].
 constexpr int kSampleDrawPiece = 16;     // weights of a piece held in registers (slices up to 4096)
-__device__ __forceinline__ void sample_draw_row(const float *p, const float *mass, int stride, float tau, int V, int b,
+__device__ __forceinline__ void sample_draw_row(const float *p, const float *mass, float tau, int V, int b,
                                                 uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
                                                 int *out, float *sm, int *sm_i)
 {
@@ -298,7 +298,7 @@ __device__ __forceinline__ void sample_draw_row(const float *p, const float *mas
     const int slice = (V + kSampleBlocks - 1) / kSampleBlocks;
     __syncthreads();
     if (wave == 0) {
-        const float m = mass[lane * stride];
+        const float m = mass[lane];
         const float inc = sample_wave_scan(m);
         const float total = __shfl(inc, 63, 64);
         const uint32_t x0 = philox4x32_10_first(step_lo, step_hi, (uint32_t)b, 0u, seed_lo, seed_hi);
@@ -551,8 +551,8 @@ __global__ __launch_bounds__(kSampleThreads) void sample_merge_draw_kernel(Sampl
         }
         tau = max(tau_k, sample_block_max((tid < nc && ge >= a.top_p * z) ? __float_as_uint(vi) : 0u, sm_w));
     } else if (a.top_p < 1.f) {
-        // many equal weights: the search of the general path (four bits per pass; the 15 candidates of a digit
-        // in registers, added over the block in a fixed order) on the candidates' values
+        // many equal weights: a search on the candidates' values, four bits per pass (the 15 candidates of a digit
+        // in registers, added over the block in a fixed order)
         float z = 0.f;
         for (int i = tid; i < nc; i += kSampleThreads) z += wgt[i];
         z = sample_block_sum(z, sm);
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_merge_draw_kernel(Sampl
         for (uint32_t i = inc - c; i < inc; i++) m += (val[i] >= tau_f) ? wgt[i] : 0.f;
         mass[tid] = m;
     }
-    sample_draw_row(a.p + (int64_t)b * a.V, mass, 1, tau_f, a.V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm,
+    sample_draw_row(a.p + (int64_t)b * a.V, mass, tau_f, a.V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm,
                     sm_i);
 }
 
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_kernel(SampleArgs a)
     if constexpr (STAGE == SAMPLE_DRAW) {
         // g == 0 only (grid.x = 1); without thresholds every weight is kept, the slices' totals are already there
         const float tau = a.search ? __uint_as_float(a.st_in[b].prefix) : 0.f;
-        sample_draw_row(p, a.part + b * kSampleBlocks, 1, tau, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
+        sample_draw_row(p, a.part + b * kSampleBlocks, tau, V, b, a.seed_lo, a.seed_hi, a.step_lo, a.step_hi, a.out, sm, sm_i);
         return;
     }
 

@@ -384,3 +384,11 @@ def test_residual_projections_of_4_bit_weights_in_groups_of_16_rows(tmp_path):
     assert variant(RESID, 193, 64) == variant(RESID, 192, 64, q4=0) == variant(STORE, 192, 64) == (4, 4, 1, 1)
     assert variant(RESID, 170, 48) == (1, 8, 1, 3)
     assert variant(RESID, 171, 48) == variant(RESID, 192, 40) == variant(RESID, 256, 33) == (3, 4, 1, 1)
+
+
+def test_sampler_scratch_holds_what_the_kernels_use():
+    """Per row: the weights, a maximum and a mass of each of 64 slices, two search states, 64 x 65 items of a value and a
+    count; every part rounded up to 256 bytes."""
+    for B, V in ((1, 1), (16, 151936), (64, 1000)):
+        parts = (B * V * 4, B * 256, B * 256, B * 16, B * 16, B * 64 * 65 * 4, B * 64 * 65 * 4)
+        assert dk.sample_scratch_bytes(B, V) == sum((n + 255) // 256 * 256 for n in parts)
