@@ -278,16 +278,13 @@ template <bool PLAN>
 __device__ __forceinline__ AttnItem attn_item(const AttnArgs &a)
 {
     if (!PLAN) return {(int)blockIdx.z, (int)blockIdx.x, (int)blockIdx.y};
-    if (a.max_chunks == 2) {
-        const int pair = (int)(blockIdx.x + blockIdx.y * gridDim.x), row_head = pair >> 1;
-        return {row_head / a.nkv, pair & 1, row_head % a.nkv};
-    }
-    return {(int)blockIdx.y / a.max_chunks, (int)blockIdx.y % a.max_chunks, (int)blockIdx.x};
+    const int b = (int)blockIdx.y / a.max_chunks, r = (int)blockIdx.y - b * a.max_chunks, i = (int)blockIdx.x + r * a.nkv;
+    const bool pairs = a.max_chunks == 2;
+    return {b, pairs ? i & 1 : r, pairs ? i >> 1 : (int)blockIdx.x};
 }
-// ... by the plan's record; false: no work
-__device__ __forceinline__ bool attn_planned_item(const uint32_t *rec, AttnItem &it)
+// ... by the first word of the plan's record; false: no work
+__device__ __forceinline__ bool attn_planned_item(uint32_t e, AttnItem &it)
 {
-    const uint32_t e = rec[0];
     it = {(int)(e & 63), (int)(e >> 8), (int)blockIdx.x};
     return e != kPlanNone;
 }
@@ -510,20 +507,26 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
     }
     const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
     int phys_next = table[min(item.c * (a.chunk_tokens / BS) + wv, a.max_blocks - 1)];
-    // T = cached tokens = position of the new token (clamped to what the table can name)
-    int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
-    const uint32_t *rec = a.plan + (PLAN ? (int64_t)(1 + blockIdx.y) * kPlanWords : 0);
+    int len = a.seq_lens[item.b], phys_then = 0;
     bool planned = false;
     if constexpr (PLAN) {
-        planned = a.plan[0] != 0;
+        const uint32_t *rec = a.plan + (int64_t)(1 + blockIdx.y) * kPlanWords;
+        const uint32_t on = a.plan[0], what = rec[0], rec_len = rec[1], rec_phys = rec[2 + wv], rec_then = rec[2 + NWV + wv];
+        // (what either side needs is requested here, together with the word: left to the compiler, the length and the
+        // first block wait for the word, one after the other, 1.5 us a launch)
+        asm volatile("" ::"s"(on), "s"(what), "s"(rec_len), "s"(len), "v"(phys_next), "v"(rec_phys), "v"(rec_then));
+        planned = on != 0;
         if (planned) {
-            if (!attn_planned_item(rec, item)) return;
+            if (!attn_planned_item(what, item)) return;
             request_row(item.b, item.j);
             table = a.block_tables + (int64_t)item.b * a.table_stride;
-            phys_next = (int)rec[2 + wv];
-            T = (int)rec[1];
+            phys_next = (int)rec_phys;
+            phys_then = (int)rec_then;
+            len = (int)rec_len;
         }
     }
+    // T = cached tokens = position of the new token (clamped to what the table can name)
+    const int T = min(max(len, 0), a.max_blocks * BS - 1);
     const int b = item.b, c = item.c, j = item.j;
     const int first_blk = c * (a.chunk_tokens / BS) + wv;
     const int T1 = T + 1;
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnArgs a)
             kw_n[i] = ld16(kt + i * 512 + lane * 8);
             vw_n[i] = ld16(vt + i * 512 + lane * 8);
         }
-        phys_next = planned ? (int)rec[2 + NWV + wv] : table[min(first_blk + NWV, a.max_blocks - 1)];
+        phys_next = planned ? phys_then : table[min(first_blk + NWV, a.max_blocks - 1)];
     }
 
 #pragma unroll

@@ -236,19 +236,23 @@ __global__ __launch_bounds__(256, PREFETCH ? 2 : 3) void attention_mfma_kernel(A
     const int *table = a.block_tables + (int64_t)item.b * a.table_stride;
     int blk_first = item.c * (a.chunk_tokens / BS) + 2 * wv;
     int phys_a = table[min(blk_first, a.max_blocks - 1)], phys_b = table[min(blk_first + 1, a.max_blocks - 1)];
-    int T = min(max(a.seq_lens[item.b], 0), a.max_blocks * BS - 1);
+    int len = a.seq_lens[item.b];
     if constexpr (PLAN) {
-        if (a.plan[0] != 0) {
-            const uint32_t *rec = a.plan + (int64_t)(1 + blockIdx.y) * kPlanWords;
-            if (!attn_planned_item(rec, item)) return;
+        const uint32_t *rec = a.plan + (int64_t)(1 + blockIdx.y) * kPlanWords;
+        const uint32_t on = a.plan[0], what = rec[0], rec_len = rec[1], rec_a = rec[2 + 2 * wv], rec_b = rec[3 + 2 * wv];
+        // (requested together with the word, see attention_kernel)
+        asm volatile("" ::"s"(on), "s"(what), "s"(rec_len), "s"(rec_a), "s"(rec_b), "s"(len), "s"(phys_a), "s"(phys_b));
+        if (on != 0) {
+            if (!attn_planned_item(what, item)) return;
             request_row(item.b, item.j);
             table = a.block_tables + (int64_t)item.b * a.table_stride;
             blk_first = item.c * (a.chunk_tokens / BS) + 2 * wv;
-            phys_a = (int)rec[2 + 2 * wv];
-            phys_b = (int)rec[3 + 2 * wv];
-            T = (int)rec[1];
+            phys_a = (int)rec_a;
+            phys_b = (int)rec_b;
+            len = (int)rec_len;
         }
     }
+    const int T = min(max(len, 0), a.max_blocks * BS - 1);
     const int b = item.b, c = item.c, j = item.j;
     const int nact = (T + 1 + a.chunk_tokens - 1) / a.chunk_tokens;
     if (c >= nact) return;
