@@ -151,3 +151,39 @@ def test_equal_rows_take_a_plan_only_where_it_orders_something(heads, length, wi
     assert got == word and (record == int(np.uint32(0xabababab).view(np.int32))) == (word == 0), (got, hex(record))
     dkv.close()
     dm.close()
+
+
+def test_plan_is_made_anew_by_every_replay_of_a_graph():
+    """Equal rows that reach their last chunk while a captured step is replayed: the plan of the first replays gives way to
+    the grid's order, and tokens and logits are those of eager steps bit for bit."""
+    import torch
+    import paper_2601_19139_amd as dk
+    batch, length, steps = 64, 955, 8                          # chunks of 320: the fourth begins at 960
+    shape = variant("tiny", n_layers=2, qk_norm=True, n_q_heads=4, n_kv_heads=4, head_dim=64)
+    lay = build_block_tables([length] * batch, 16, 149, seed=91)       # tables of 1104 tokens
+    dm = dk.DeviceModel(shape, W.make_weights(shape, 93))
+    pool = W.fill_kv_pool(shape, lay, 92)
+    flags = dk.STEP_ADVANCE | dk.STEP_NO_FUSED
+    seen = []
+    for replayed in (False, True):
+        dkv = dk.DeviceKV(dm, lay, pool)
+        dec = dk.Decoder(dm, dkv, lay.contexts, W.initial_tokens(shape, batch, 94))
+        stream, graph, got = torch.cuda.Stream(), torch.cuda.CUDAGraph(), []
+        with torch.cuda.stream(stream):
+            for step in range(steps):
+                if replayed and step == 1:
+                    graph.capture_begin()
+                    dec.step(flags=flags, stream=stream.cuda_stream)
+                    graph.capture_end()
+                if replayed and step:
+                    graph.replay()
+                else:
+                    dec.step(flags=flags, stream=stream.cuda_stream)
+                stream.synchronize()
+                got.append((plan_words(dec)[0], dec.next.cpu().numpy(), dec.logits.cpu().numpy()))
+        assert [w for w, _, _ in got] == [1] * 5 + [0] * 3     # lengths 955 to 962
+        seen.append(got)
+        dkv.close()
+    for (_, n0, l0), (_, n1, l1) in zip(*seen):
+        assert np.array_equal(n0, n1) and np.array_equal(l0, l1)
+    dm.close()
