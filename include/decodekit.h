@@ -226,7 +226,9 @@ enum {
 
 /*
  * One decode step for B sequences (Algorithm 1's per-iteration token
- * generation, batched; rows do not interact).
+ * generation, batched; rows do not interact: at the same B and
+ * max_blocks_per_seq a row's results are the same bits whatever the other
+ * rows hold).
  *
  * For each row b, with T = d_seq_lens[b] tokens already cached: embeds
  * d_tokens[b]; per layer: RMSNorm, q/k/v projection, optional q/k head norm,
@@ -311,8 +313,10 @@ dk_status dk_decode_step_static(dk_model *model, dk_kv_pool *pool, const int32_t
  *                   may be the workspace of the decode steps (the next persistent
  *                   decode step re-initialises its part by itself)
  *   d_logits        device float32 [n][vocab] or NULL
- *   d_next_tokens   device int32 [n]; NULL together with d_logits skips the final
- *                   norm, lm_head and argmax (a chunk that is not the last of its prompt)
+ *   d_next_tokens   device int32 [n]; NULL together with d_logits (a chunk that is not the
+ *                   last of its prompt) ends the chunk with the last layer's K/V - in models
+ *                   with experts with its routing: neither the rest of that layer nor the
+ *                   final norm, lm_head and argmax are computed
  * Longer prompts are fed chunk after chunk.  The weights are streamed once per
  * chunk, so the cost of a chunk is that of one decode step of n rows.
  */

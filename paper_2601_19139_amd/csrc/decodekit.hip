@@ -293,7 +293,12 @@ Workspace carve(const dk_model_config &c, int B, int max_blocks, bool q4, bool a
     //    lighter matrix-core variant - no second set of tile registers, three blocks per compute
     //    unit, one round of at most 768 blocks - beats both (3B shape, ragged contexts up to 2 k:
     //    25.4 -> 22.5 us per launch; 0.6B shape, 16 rows of context 512: 15.1 -> 12.9 us); with 4 k
-    //    contexts or groups of 8 it is slower and is not taken.
+    //    contexts or groups of 8 it is slower and is not taken;
+    //  * both matrix-core variants walk 128 tokens a round, so a chunk of an odd multiple of 64 leaves half of the waves
+    //    idle in its last round.  The lighter one's chunks rounded down to 128 make more blocks than the chip holds where
+    //    rows fill their tables and gain where they do not (whole steps, 8B shape: 16 of 2500 5400 -> 5658, of 1700 4879 ->
+    //    5012, of 100 to 2300 4765 -> 4665; 4 bit, 12 of 500 to 2000 3131 -> 3034; 3B, 16 of 2400 2801 -> 2970), rounded up
+    //    they gain nothing; the other's rounded up, nothing (8B, 16 of 4096 5575 / 5576).
     const bool batched_attn = B > kMaxGemvBatch || c.n_experts > 0 || q4;   // (three terms: the vector-ALU kernel's float32 probabilities)
     w.pack_x = pack_terms(c, B, q4, c.hidden);
     w.pack_a = pack_terms(c, B, q4, (size_t)c.n_q_heads * d);
@@ -868,7 +873,7 @@ const char *dk_last_error(void) { return g_err; }
 
 // The kernel revisions change whenever a kernel's memory behaviour changes; the
 // benchmark quotes stored counter measurements only for a matching revision.
-const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r15, attention r10, moe r4, fused r9, prefill r2, sample r3)"; }
+const char *dk_version(void) { return "decodekit 0.9 (gfx950; gemv r4, gemm r16, attention r11, moe r4, fused r9, prefill r2, sample r4)"; }
 
 // ------------------------------------------------------------------- pool --
 dk_status dk_kv_pool_bytes(const dk_model_config *cfg, int32_t num_blocks, int32_t block_size,

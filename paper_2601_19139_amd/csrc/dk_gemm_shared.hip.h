@@ -55,7 +55,8 @@ constexpr size_t shared_gemm_lds_bytes(int MT) { return (size_t)2 * 512 * MT * 1
 // A block's 128 output rows are one head of k or v of a prompt chunk: head norm and rotation (k), rounding, and into the
 // pool, as prefill_append_kernel does it (same arithmetic).  That kernel is a launch of its own, 4.9 us per layer, for
 // values that this block has in its registers; here the head takes one trip through the LDS of the activation tiles and
-// the projection 0.3 us more (8B shape, 64 rows, 23.9 -> 24.2; 3B with 4-bit weights 19.4 -> 20.3).  buf: [rows][132] floats.  Called by all threads, which have left the activation tiles.
+// the projection 0.3 us more at the 8B shape (64 rows, 23.9 -> 24.2), 0.9 at the 3B shape with 4-bit weights (19.4 -> 20.3).
+// buf: [rows][132] floats.  Called by all threads, which have left the activation tiles.
 template <int MT, int W>
 __device__ __forceinline__ void append_head(const GemmArgs &a, int head, const float (&v)[MT][4], float *buf)
 {
