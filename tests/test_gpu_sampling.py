@@ -127,7 +127,6 @@ def test_sampler_matches_oracle(dk, orc, V, B, T, top_k, top_p):
     ("half_excluded", 3001, 2000, 0.8),   # ... and fewer others than top_k
     ("ties", 5000, 300, 1.0),         # the 300th largest is one of 500 equal ones
     ("wide", 20000, 0, 0.999),        # weights down to 1e-30: most of them negligible
-    ("tail", 20000, 0, 0.6),          # negligible weights that together move the threshold by hundreds of tokens
 ])
 def test_threshold_searches(dk, orc, row, V, top_k, top_p):
     """The searches over whole rows (no small top_k) where digits, ties and negligible weights meet: the kept set must
@@ -143,16 +142,6 @@ def test_threshold_searches(dk, orc, row, V, top_k, top_p):
         l[::2] = -np.inf
     elif row == "ties":
         l[100:600] = 2.0
-    elif row == "tail":
-        # the largest weight 1, 2000 of 3e-4 to 6e-4, the others 0.95 of what counts as negligible: 1, 0.9 and 0.17 in all
-        w = np.full(V, 0.95 * (1.0 - top_p) / (2 * V))
-        w[rng.permutation(V)[:2000]] = np.linspace(3e-4, 6e-4, 2000)
-        w[V // 2] = 1.0
-        l = np.log(w).astype(np.float32)
-        few = w.copy()
-        few[w < (1.0 - top_p) / (2 * V)] = 0.0
-        kept_of = [int((np.cumsum(np.sort(w)[::-1]) < top_p * x.sum()).sum()) for x in (w, few)]
-        assert kept_of[0] > kept_of[1] + 100, kept_of
     else:
         l *= 20.0
     B = 16
@@ -169,6 +158,36 @@ def test_threshold_searches(dk, orc, row, V, top_k, top_p):
             assert m_p < 1e-6 or got[b] in kept, (step, b, got[b])
             if m_u > 1e-5 and m_p > 1e-6:
                 assert got[b] == orc.sample(l, 1.0, top_k, top_p, u), (step, b, got[b])
+                exact += 1
+    assert exact >= 4 * B
+
+
+def test_negligible_weights_that_move_the_nucleus(dk, orc):
+    """The largest weight 1, 2000 of 3e-4 to 6e-4, and 18000 just below what counts as negligible: 1, 0.9 and 0.17 in all.
+    Without the last ones the nucleus would end more than 100 tokens earlier."""
+    import torch
+    V, B, top_p = 20000, 16, 0.6
+    rng = np.random.default_rng(V)
+    w = np.full(V, 0.95 * (1.0 - top_p) / (2 * V))
+    w[rng.permutation(V)[:2000]] = np.linspace(3e-4, 6e-4, 2000)
+    w[V // 2] = 1.0
+    l = np.log(w).astype(np.float32)
+    few = np.where(w < (1.0 - top_p) / (2 * V), 0.0, w)
+    ends = [int((np.cumsum(np.sort(w)[::-1]) < top_p * x.sum()).sum()) for x in (w, few)]
+    assert ends[0] > ends[1] + 100, ends
+    d_logits = torch.from_numpy(np.tile(l, (B, 1))).cuda()
+    scratch = torch.full((dk.sample_scratch_bytes(B, V),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    exact = 0
+    for step in range(6):
+        dk.sample_tokens(d_logits, 1.0, 0, top_p, 77, step, scratch, out)
+        got = out.cpu().numpy()
+        for b in range(B):
+            u = orc.sample_uniform(77, step, b)
+            m_u, m_p, kept = oracle_margins(l, 1.0, 0, top_p, u)
+            assert m_p < 1e-6 or got[b] in kept, (step, b, got[b])
+            if m_u > 1e-5 and m_p > 1e-6:
+                assert got[b] == orc.sample(l, 1.0, 0, top_p, u), (step, b, got[b])
                 exact += 1
     assert exact >= 4 * B
 
